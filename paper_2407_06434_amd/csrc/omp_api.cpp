@@ -289,6 +289,8 @@ WorkView work_view(void *mem, int64_t M, int64_t N, int64_t B, int S, int precis
   w.R32 = at<float>(mem, L.R32);
   w.R16 = is_half(precision) ? at<uint16_t>(mem, L.R16) : nullptr;
   w.fp16 = precision == OMP_PREC_FP16 ? 1 : 0;
+  const double ku = (double)L.Mp / 16777216.0;
+  w.gamma_k = ku / (1.0 - ku);
   w.rscale = L.rscale ? at<float>(mem, L.rscale) : nullptr;
   w.rscale_next = L.rscale_next ? at<float>(mem, L.rscale_next) : nullptr;
   w.part = at<uint64_t>(mem, L.part);

@@ -82,6 +82,7 @@ struct WorkView {
   float *R32;     // [Bp][Mp] residual, FP32
   uint16_t *R16;  // [Bp][Mp] residual, BF16 (BF16 form) or FP16 scaled by rscale (FP16 form)
   int fp16;       // 1: R16 and A16 hold FP16 (FP16 form)
+  double gamma_k; // Mp u / (1 - Mp u), u = 2^-24: the accumulation term of the 16-bit pick's error bound
   float *rscale;  // [Bp] FP16 form: power-of-two scale of the residual stored in R16 (else nullptr)
   float *rscale_next; // [Bp] FP16 form: the scale the residual kernel stores the next residual with
   uint64_t *part; // [Bp][ntile*ncand] packed (score, index) keys from the GEMM epilogue

@@ -41,6 +41,7 @@
 
 #include <cmath>
 #include <cstring>
+#include <type_traits>
 
 #include "../../include/batched_omp.h"
 #include "omp_internal.h"
@@ -90,6 +91,46 @@ __device__ inline double bf16_used(uint16_t h) {
   return (h & 0x7F80u) == 0 ? 0.0 : (double)__uint_as_float((uint32_t)h << 16);
 }
 __device__ inline double f16_used(uint16_t h) { return (h & 0x7C00u) == 0 ? 0.0 : (double)f16_to_f32(h); }
+
+// Stores chunk i of a residual: r in FP32, in the 16-bit forms its copy (BF16, or FP16
+// of sig r; isig = 1 / sig, a power of two), and adds ||r||^2 and the copy's squared
+// error to the lane's sums. The BF16 copy's error r - bf16(r) is formed in FP32: it is
+// a multiple of r's last place no larger than half a BF16 place, so the difference
+// is exact.
+template <bool BF16>
+__device__ inline void store_residual(const WorkView &w, int64_t i, const float4 &r, float sig, double isig, double &nrm,
+                                      double &dlt) {
+  reinterpret_cast<float4 *>(w.R32)[i] = r;
+  if constexpr (BF16) {
+    const float v[4] = {r.x, r.y, r.z, r.w};
+    uint32_t pk[2];
+    double e[4];
+    if (w.fp16) {
+#pragma unroll
+      for (int q = 0; q < 2; ++q) {
+        const uint16_t lo = f32_to_f16_rne(v[2 * q] * sig), hi = f32_to_f16_rne(v[2 * q + 1] * sig);
+        pk[q] = (uint32_t)lo | ((uint32_t)hi << 16);
+        e[2 * q] = (double)v[2 * q] - f16_used(lo) * isig;
+        e[2 * q + 1] = (double)v[2 * q + 1] - f16_used(hi) * isig;
+      }
+    } else {
+      typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
+#pragma unroll
+      for (int q = 0; q < 2; ++q) {
+        const bf16x2 h = {(__bf16)v[2 * q], (__bf16)v[2 * q + 1]};  // v_cvt_pk_bf16_f32, round to nearest even
+        pk[q] = __builtin_bit_cast(uint32_t, h);
+#pragma unroll
+        for (int t = 0; t < 2; ++t) {
+          const uint32_t c = t ? pk[q] & 0xFFFF0000u : pk[q] << 16;
+          e[2 * q + t] = (double)(v[2 * q + t] - ((c & 0x7F800000u) ? __uint_as_float(c) : 0.f));
+        }
+      }
+    }
+    reinterpret_cast<uint2 *>(w.R16)[i] = make_uint2(pk[0], pk[1]);
+    dlt += e[0] * e[0] + e[1] * e[1] + e[2] * e[2] + e[3] * e[3];
+  }
+  nrm += (double)r.x * r.x + (double)r.y * r.y + (double)r.z * r.z + (double)r.w * r.w;
+}
 
 // The power of two 2^-e with x 2^-e in [1/2, 1) (1 for x = 0 or non-finite x): the
 // FP16 form stores sigma v so that every stored value lies in [-1, 1].
@@ -153,6 +194,72 @@ __device__ inline uint64_t wave_max(uint64_t v) {
     m = x > m ? x : m;
   }
   return m;
+}
+
+// Sum of the values lanes 0 .. 7 hold (the per-slice norms), returned to every
+// lane: three DPP steps within the row and one read. Bit for bit wave_sum's result
+// where the other lanes hold zero.
+__device__ inline double sum8(double v) {
+  v += dppd<DPP_XOR1>(v);
+  v += dppd<DPP_XOR2>(v);
+  v += dppd<DPP_HALF_MIRROR>(v);
+  return __longlong_as_double((long long)readlane64((uint64_t)__double_as_longlong(v), 0));
+}
+
+__device__ inline uint32_t wave_max32(uint32_t v) {
+  v = max(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, DPP_XOR1, 0xF, 0xF, false));
+  v = max(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, DPP_XOR2, 0xF, 0xF, false));
+  v = max(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, DPP_HALF_MIRROR, 0xF, 0xF, false));
+  v = max(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, DPP_MIRROR, 0xF, 0xF, false));
+  const uint32_t a = max((uint32_t)__builtin_amdgcn_readlane((int)v, 0), (uint32_t)__builtin_amdgcn_readlane((int)v, 16));
+  const uint32_t b = max((uint32_t)__builtin_amdgcn_readlane((int)v, 32), (uint32_t)__builtin_amdgcn_readlane((int)v, 48));
+  return max(a, b);
+}
+
+// Lane masks built on the scalar unit, so that a masked value costs the vector unit
+// one select instead of a compare per condition and a select.
+__device__ inline uint64_t lanes_below(int n) { return n <= 0 ? 0ull : n >= 64 ? ~0ull : (1ull << n) - 1ull; }
+// The lanes of rows j < i < k (row i = lane + 64 p), for j = 0, 1, ...: each next()
+// moves on by one column (two scalar instructions).
+template <int RPL>
+struct RowMask {
+  uint64_t m[RPL], in[RPL], sh[RPL];
+  __device__ inline explicit RowMask(int k) {
+#pragma unroll
+    for (int p = 0; p < RPL; ++p) {
+      in[p] = lanes_below(k - 64 * p);
+      sh[p] = ~0ull;
+      m[p] = 0;
+    }
+  }
+  __device__ inline void next() {
+#pragma unroll
+    for (int p = RPL - 1; p >= 0; --p) {
+      const bool on = p == 0 || sh[p > 0 ? p - 1 : 0] == 0ull;  // all rows of the registers before are passed
+      sh[p] = on ? sh[p] << 1 : sh[p];
+      m[p] = in[p] & sh[p];
+    }
+  }
+};
+// The lanes of columns i < j (i = lane + 64 p), for j going down by one with each next().
+template <int RPL>
+struct ColMask {
+  uint64_t m[RPL];
+  __device__ inline explicit ColMask(int j) {
+#pragma unroll
+    for (int p = 0; p < RPL; ++p) m[p] = lanes_below(j - 64 * p);
+  }
+  __device__ inline void next() {
+#pragma unroll
+    for (int p = 0; p < RPL; ++p) {
+      const bool on = p == RPL - 1 || m[p < RPL - 1 ? p + 1 : p] == 0ull;
+      m[p] = on ? m[p] >> 1 : m[p];
+    }
+  }
+};
+// v where the lane's bit is set, else 0.
+__device__ inline float keep_lanes(float v, uint64_t mask) {
+  return __builtin_amdgcn_inverse_ballot_w64(mask) ? v : 0.f;
 }
 
 // Select element p (wave-uniform) of a small per-lane register array without
@@ -223,9 +330,8 @@ __device__ inline double residual_norm(const WorkView &w, int64_t b) {
 // u = 2^-24; scaling by the FP32 1/||a|| adds 2 u (s + T) <= 2 u (||r|| + T).
 // This is far tighter than the worst case u_bf16 ||a|| ||r||: rounding errors
 // have norm ~ 2^-8 / sqrt(3) relative, not 2^-8.
-__device__ inline double bf16_tau(double rn, double dn, double E, int64_t K) {
+__device__ inline double bf16_tau(double rn, double dn, double E, double gk) {
   const double u = 1.0 / 16777216.0;
-  const double gk = (double)K * u / (1.0 - (double)K * u);
   const double Rt = rn + dn;
   const double T = (1.0 + 2.0 * E) * dn + E * Rt + gk * (1.0 + E) * Rt;
   return (T * (1.0 + 4.0 * u) + 2.0 * u * (rn + T)) * (1.0 + 1e-9) + 1e-30;
@@ -365,20 +471,45 @@ struct RescoreQueue {
   double bs2 = -1.0;  // best exact score of any other atom (near-tie flagging)
   double bar = 0.0, bnu2 = 0.0;
   int bn = 0x7fffffff;
+  // a_n^T r of NA atoms; signals of at most 256 samples have one chunk per lane
+  template <int NA>
+  __device__ __attribute__((always_inline)) void dots(const DictView &d, const int (&n)[NA], int lane,
+                                                      double (&ar)[NA]) {
+    if constexpr (RR) {
+      atom_dots_reg<NA, 2>(d, n, rr, lane, ar);
+    } else {
+      if (d.Mp <= 256) atom_dots<NA, 1>(d, n, r4, lane, ar);
+      else atom_dots<NA, 2>(d, n, r4, lane, ar);
+    }
+  }
+  // The only candidate: it is the pick whatever its score, so none is formed.
+  __device__ __attribute__((always_inline)) void only(int atom, const DictView &d, int lane) {
+    const int n[1] = {atom};
+    double ar[1];
+    bnu2 = d.nu2[atom];
+    dots<1>(d, n, lane, ar);
+    bar = ar[0];
+    bn = atom;
+  }
   template <int NA>
   __device__ __attribute__((always_inline)) void rescore(const DictView &d, const int (&n)[NA], int lane) {
     double nu2[NA];
 #pragma unroll
     for (int i = 0; i < NA; ++i) nu2[i] = n[i] >= 0 ? d.nu2[n[i]] : 1.0;
     double ar[NA];
-    if constexpr (RR)
-      atom_dots_reg<NA, 2>(d, n, rr, lane, ar);
-    else
-      atom_dots<NA, 2>(d, n, r4, lane, ar);
+    dots<NA>(d, n, lane, ar);
+    // one square root and division for all candidates: lane i works on candidate i
+    double arl = ar[0], nul = nu2[0];
+#pragma unroll
+    for (int i = 1; i < NA; ++i) {
+      arl = lane == i ? ar[i] : arl;
+      nul = lane == i ? nu2[i] : nul;
+    }
+    const double scl = fabs(arl) / sqrt(nul);
 #pragma unroll
     for (int i = 0; i < NA; ++i) {
       if (n[i] < 0) continue;
-      const double sc = fabs(ar[i]) / sqrt(nu2[i]);
+      const double sc = __longlong_as_double((long long)readlane64((uint64_t)__double_as_longlong(scl), i));
       if (better(sc, n[i], bs, bn)) {
         if (n[i] != bn) bs2 = bs;  // (an atom may be re-scored twice: it is not its own runner-up)
         bs = sc;
@@ -456,6 +587,7 @@ __device__ __attribute__((always_inline)) inline void scan_keys(const uint32_t (
                                                                 int *mlist, int &ncand, int &nmaybe) {
 #pragma unroll
   for (int j = 0; j < KB; ++j) {
+    if (t0 + 64 * j >= nkeys) break;  // wave-uniform: the remaining groups hold no key
     const int t = t0 + 64 * j + (int)(threadIdx.x & 63);
     const uint32_t sb = kb[j] & 0x7FFFFFE0u;  // score bits
     const bool cand = key_valid(kb[j]) && sb >= thr_bits;
@@ -557,7 +689,8 @@ __device__ int select_bf16(const DictView &d, const WorkView &w, int64_t b, floa
                            const uint32_t (&kv)[KREG], bool kreg, const float4 (&rr)[RREG], int *neartie) {
   // Key scores carry the scale ks of the 16-bit residual copy (1 in the BF16 form, a
   // power of two in the FP16 form): a score s is stored as ks s, exactly.
-  const double smax = (double)smax_key / ks;
+  const double iks = w.fp16 ? 1.0 / ks : 1.0;  // exact (a power of two)
+  const double smax = (double)smax_key * iks;
   const int nkeys = w.ntile * w.ncand;
   const uint32_t *keys = reinterpret_cast<const uint32_t *>(w.part) + b * nkeys;
   const float4 *r4 = reinterpret_cast<const float4 *>(w.R32) + b * (d.Mp / 4);
@@ -571,7 +704,7 @@ __device__ int select_bf16(const DictView &d, const WorkView &w, int64_t b, floa
   // s >= mthr / (1 + et) lowered by 1e-12 relative (a superset of the list), both
   // in the keys' scale
   const uint32_t thr_bits = float_bits_floor(thr * ks);
-  const uint32_t mthr_bits = float_bits_floor(mthr / (1.0 + et) * (1.0 - 1e-12) * ks);
+  const uint32_t mthr_bits = float_bits_floor(mthr * (1.0 / (1.0 + et)) * (1.0 - 1e-12) * ks);
   int *mlist = clist + solve_cand_len(nkeys);
   RescoreQueue<RR> q(r4, rr);
   // Candidates and possibly open subgroups, from the keys in registers or, for
@@ -592,11 +725,16 @@ __device__ int select_bf16(const DictView &d, const WorkView &w, int64_t b, floa
     }
   }
   wave_lds_sync();
-  for (int i = 0; i < ncand; ++i) {
-    const int e = __builtin_amdgcn_readfirstlane(clist[i]);
-    q.push(key_atom(w, e >> 5, e & 31), d, lane);
+  if (ncand == 1 && nmaybe == 0) {  // a second best atom, if any, is below every window
+    const int e = __builtin_amdgcn_readfirstlane(clist[0]);
+    q.only(key_atom(w, e >> 5, e & 31), d, lane);
+  } else {
+    for (int i = 0; i < ncand; ++i) {
+      const int e = __builtin_amdgcn_readfirstlane(clist[i]);
+      q.push(key_atom(w, e >> 5, e & 31), d, lane);
+    }
+    q.flush(d, lane);
   }
-  q.flush(d, lane);
 
   // The listed subgroups (all bounding keys if the list overflowed) against
   // the exact winner; an open subgroup is re-scored whole.
@@ -606,7 +744,7 @@ __device__ int select_bf16(const DictView &d, const WorkView &w, int64_t b, floa
   const int npass = movf ? nkeys / NKEEP : nmaybe;
   for (int i = 0; i < npass; ++i) {
     const int slot = movf ? i * NKEEP + NKEEP - 1 : __builtin_amdgcn_readfirstlane(mlist[i]);
-    const double theta = key_score(keys[slot]) / ks;
+    const double theta = key_score(keys[slot]) * iks;
     if (!(theta * (1.0 + et) + tau >= (w.flag_ties ? (1.0 - TIE_REL) * q.bs : q.bs))) continue;
     const int tile = slot / w.ncand;
     const int sgl = (slot % w.ncand) / NKEEP;  // ((wn * subs_per_half + ig) * 2 + h)
@@ -625,7 +763,7 @@ __device__ int select_bf16(const DictView &d, const WorkView &w, int64_t b, floa
   }
   *cdot = q.bar;
   *nu2 = q.bnu2;
-  *neartie = (w.flag_ties && q.bs2 >= (1.0 - TIE_REL) * q.bs) ? 1 : 0;
+  *neartie = (w.flag_ties && q.bs2 >= 0.0 && q.bs2 >= (1.0 - TIE_REL) * q.bs) ? 1 : 0;
   return q.bn == 0x7fffffff ? -1 : q.bn;
 }
 
@@ -936,8 +1074,7 @@ __global__ __launch_bounds__(64 * SOLVE_WAVES) void k_solve(DictView d, WorkView
     xo[p] = i < S ? w.xh[b * S + i] : 0.f;
   }
   const int nkeys = w.ntile * w.ncand;
-  // FP32 form: the largest valid 64-bit key (a valid key has a non-zero index
-  // word). BF16 form: (score bits << 32) | 1 of the best valid 32-bit key.
+  // FP32 form: the largest valid 64-bit key (a valid key has a non-zero index word).
   uint64_t kmax = 0;
   // RR (512 < M <= 1024, residual-vector forms): the residual is read in this
   // round too, so the pick's exact scores need only the atoms.
@@ -955,26 +1092,30 @@ __global__ __launch_bounds__(64 * SOLVE_WAVES) void k_solve(DictView d, WorkView
   }
   // BF16 form: up to 64 KREG keys stay in registers for the pick
   uint32_t kv[KREG];
+  uint32_t hmax = 0;  // 16-bit forms: score bits | 1 of the best valid key, 0 when there is none
   const bool kreg = BF16 && nkeys <= 64 * KREG;
   if (BF16) {
     const uint32_t *keys = reinterpret_cast<const uint32_t *>(w.part) + b * nkeys;
+#pragma unroll
+    for (int j = 0; j < KREG; ++j) kv[j] = 0x80000000u;
     if (kreg) {
 #pragma unroll
       for (int j = 0; j < KREG; ++j) {
+        if (64 * j >= nkeys) break;  // wave-uniform: no load and no work for groups without keys
         const int t = 64 * j + lane;
-        const uint32_t v = keys[t < nkeys ? t : 0];
-        kv[j] = t < nkeys ? v : 0x80000000u;
-        const uint64_t m = ((uint64_t)(kv[j] & ~31u) << 32) | 1ull;
-        kmax = (key_valid(kv[j]) && m > kmax) ? m : kmax;
+        kv[j] = keys[t < nkeys ? t : 0];
+        if (64 * j + 64 > nkeys) kv[j] = t < nkeys ? kv[j] : 0x80000000u;
+      }
+#pragma unroll
+      for (int j = 0; j < KREG; ++j) {
+        if (64 * j >= nkeys) break;
+        hmax = max(hmax, key_valid(kv[j]) ? (kv[j] & ~31u) | 1u : 0u);
       }
     } else {
-#pragma unroll
-      for (int j = 0; j < KREG; ++j) kv[j] = 0x80000000u;
 #pragma unroll 4
       for (int t = lane; t < nkeys; t += 64) {
         const uint32_t v = keys[t];
-        const uint64_t m = ((uint64_t)(v & ~31u) << 32) | 1ull;
-        kmax = (key_valid(v) && m > kmax) ? m : kmax;
+        hmax = max(hmax, key_valid(v) ? (v & ~31u) | 1u : 0u);
       }
     }
   } else {
@@ -995,7 +1136,7 @@ __global__ __launch_bounds__(64 * SOLVE_WAVES) void k_solve(DictView d, WorkView
     // slot scheduler: a signal that stopped at its last pick leaves now that
     // its final residual is known
     if (SLOTS && !(fl & FLAG_EMPTY)) {
-      rn = sqrt(wave_sum(pn));
+      rn = sqrt(sum8(pn));
       stopfl = fl;
       goto stop;
     }
@@ -1003,13 +1144,14 @@ __global__ __launch_bounds__(64 * SOLVE_WAVES) void k_solve(DictView d, WorkView
   }
 
   // 0. Stop test on the current residual (Algorithm 1 stops once ||r|| <= eps).
-  rn = sqrt(wave_sum(pn));
+  rn = sqrt(sum8(pn));
   if (rn <= (double)eps_b) {
     stopfl = fl | FLAG_DONE;
     goto stop;
   }
-  kmax = wave_max(kmax);
-  if (kmax == 0ull) {  // nothing selectable is left
+  if (BF16) hmax = wave_max32(hmax);
+  else kmax = wave_max(kmax);
+  if (BF16 ? hmax == 0u : kmax == 0ull) {  // nothing selectable is left
     stopfl = fl | FLAG_DONE | OMP_SIG_EXHAUSTED;
     goto stop;
   }
@@ -1064,9 +1206,9 @@ __global__ __launch_bounds__(64 * SOLVE_WAVES) void k_solve(DictView d, WorkView
   double cdot = 0.0, nu2 = 0.0;
   float g[RPL];
   if (BF16) {
-    const double tau = bf16_tau(rn, sqrt(wave_sum(pd)), (double)d.aerr_max[0], d.Mp);
+    const double tau = bf16_tau(rn, sqrt(sum8(pd)), (double)d.aerr_max[0], w.gamma_k);
     int neartie = 0;
-    nstar = select_bf16<RR>(d, w, b, __uint_as_float((uint32_t)(kmax >> 32)), ks, tau, lane, &widened, &cdot,
+    nstar = select_bf16<RR>(d, w, b, __uint_as_float(hmax & ~31u), ks, tau, lane, &widened, &cdot,
                             &nu2, clist, kv, kreg, rr, &neartie);
     // FP16 form: the next residual copy is scaled by ||r_k||, which bounds ||r_k+1||
     if (w.fp16 && lane == 0) w.rscale_next[b] = pow2_scale(rn);
@@ -1089,7 +1231,8 @@ __global__ __launch_bounds__(64 * SOLVE_WAVES) void k_solve(DictView d, WorkView
       if constexpr (RR)
         atom_dots_reg<1, 4>(d, na, rr, lane, ar);
       else
-        atom_dots<1, 4>(d, na, r4, lane, ar);
+        if (d.Mp <= 256) atom_dots<1, 1>(d, na, r4, lane, ar);
+        else atom_dots<1, 4>(d, na, r4, lane, ar);
       cdot = ar[0];
     }
   }
@@ -1113,12 +1256,14 @@ __global__ __launch_bounds__(64 * SOLVE_WAVES) void k_solve(DictView d, WorkView
   wave_lds_sync();
   if (w.refactor) cholesky_lds<RPL>(Vs, k, lane);
 
+  // Row starts in the packed factor, of the rows i < k (the other lanes read row 0
+  // and the value is dropped), and the lanes that hold them.
   float z[RPL], rd[RPL];
-  int tri[RPL];  // i (i + 1) / 2: start of row i in the packed factor
+  int tri[RPL];
 #pragma unroll
   for (int p = 0; p < RPL; ++p) {
     const int i = lane + 64 * p;
-    tri[p] = i * (i + 1) / 2;
+    tri[p] = i < k ? i * (i + 1) / 2 : 0;
     rd[p] = i < k ? 1.0f / Vs[tri[p] + i] : 0.f;  // reciprocal diagonal, all rows at once
     z[p] = 0.f;
   }
@@ -1130,46 +1275,48 @@ __global__ __launch_bounds__(64 * SOLVE_WAVES) void k_solve(DictView d, WorkView
   //    broadcast and one FMA on the critical path. Finally z_i = g_i / V_ii.
   //    Columns are handled four at a time, the loop rounded up to a whole
   //    block (columns j >= k are all zero).
+  //    On a full chip the solve is bound by instruction issue (counters, 4 wavefronts per
+  //    SIMD: vector instructions fill every cycle), not by latency. So row masks advance on
+  //    the scalar unit, addresses are a per-lane base plus wave-uniform offsets, reads are
+  //    unmasked, and key groups, scores and chunks that do not exist are skipped: 6 vector
+  //    instructions per column instead of 10, 7 per atom of the residual instead of 17.
+  //    Whole solves, before and after: 256 x 1024, S = 32, B = 10,000 in BF16 1.86 -> 1.66 ms;
+  //    512 x 2048, S = 64, B = 5000 in FP16 4.28 -> 3.80 ms; 1024 x 4096, S = 64, B = 4096
+  //    in BF16 5.85 -> 5.77 ms.
   {
     constexpr int QB = 4;
     float va[QB][RPL], vx[QB][RPL];
+    RowMask<RPL> rows(k);  // lanes of the rows below column j, j advancing by one
+    // Unmasked reads stay inside the factor: a block's last column is at most k + 2 when
+    // its first is below k (blocks past it read column 0), and the packed rows past row
+    // k - 1 hold at least k + 1 more entries.
 #pragma unroll
     for (int q = 0; q < QB; ++q) {
-      const float rj = readlane(pick(rd, q >> 6), q & 63);
+      const float rj = lane_elem(rd, q);
+      rows.next();
 #pragma unroll
-      for (int p = 0; p < RPL; ++p) {
-        const int i = lane + 64 * p;
-        const bool in = i > q && i < k;
-        const float v = Vs[in ? tri[p] + q : 0];
-        va[q][p] = in ? v * rj : 0.f;
-      }
+      for (int p = 0; p < RPL; ++p) va[q][p] = keep_lanes(Vs[tri[p] + q] * rj, rows.m[p]);
     }
     for (int j0 = 0; j0 < k; j0 += QB) {
+      const int jb = j0 + QB < k ? j0 + QB : 0;
 #pragma unroll
-      for (int q = 0; q < QB; ++q)
+      for (int p = 0; p < RPL; ++p) {
+        const float *col = Vs + tri[p] + jb;
 #pragma unroll
-        for (int p = 0; p < RPL; ++p) {
-          const int i = lane + 64 * p, j = j0 + QB + q;
-          const bool in = i > j && i < k;
-          vx[q][p] = Vs[in ? tri[p] + j : 0];
-        }
+        for (int q = 0; q < QB; ++q) vx[q][p] = col[q];
+      }
 #pragma unroll
       for (int q = 0; q < QB; ++q) {
-        const int j = j0 + q;
-        const float gj = readlane(pick(g, j >> 6), j & 63);
+        const float gj = lane_elem(g, j0 + q);
 #pragma unroll
         for (int p = 0; p < RPL; ++p) g[p] = fmaf(-va[q][p], gj, g[p]);
       }
 #pragma unroll
       for (int q = 0; q < QB; ++q) {
-        const int j = j0 + QB + q;
-        const int jc = j < 64 * RPL ? j : 0;
-        const float rj = readlane(pick(rd, jc >> 6), jc & 63);
+        const float rj = lane_elem(rd, j0 + QB + q);  // (past k: any value, the column is dropped)
+        rows.next();
 #pragma unroll
-        for (int p = 0; p < RPL; ++p) {
-          const int i = lane + 64 * p;
-          va[q][p] = (i > j && i < k) ? vx[q][p] * rj : 0.f;
-        }
+        for (int p = 0; p < RPL; ++p) va[q][p] = keep_lanes(vx[q][p] * rj, rows.m[p]);
       }
     }
 #pragma unroll
@@ -1234,45 +1381,42 @@ __global__ __launch_bounds__(64 * SOLVE_WAVES) void k_solve(DictView d, WorkView
     constexpr int QB = 4;
     const int jt = ((K + QB - 1) / QB) * QB - 1;  // top row of the first block
     float va[QB][RPL], vx[QB][RPL];
+    int ic[RPL];  // the lane's column, 0 past the factor (the value is dropped)
+#pragma unroll
+    for (int p = 0; p < RPL; ++p) ic[p] = lane + 64 * p < K ? lane + 64 * p : 0;
+    ColMask<RPL> cm(jt);  // lanes of the columns left of row j, j going down by one
+    int ro = jt * (jt + 1) / 2;  // start of row j
 #pragma unroll
     for (int q = 0; q < QB; ++q) {
       const int j = jt - q;
-      const bool row = j < K;
-      const float rj = readlane(pick(rd, j >> 6), j & 63);
+      const float rj = lane_elem(rd, j);
+      const int rr = j < K ? ro : 0;
 #pragma unroll
-      for (int p = 0; p < RPL; ++p) {
-        const int i = lane + 64 * p;
-        const bool in = row && i < j;
-        const float v = Vs[in ? j * (j + 1) / 2 + i : 0];
-        va[q][p] = in ? v * rj : 0.f;
-      }
+      for (int p = 0; p < RPL; ++p) va[q][p] = keep_lanes(Vs[rr + ic[p]] * rj, j < K ? cm.m[p] : 0ull);
+      cm.next();
+      ro -= j;
     }
     for (int j0 = jt; j0 >= 0; j0 -= QB) {
+      if (j0 >= QB) {  // wave-uniform: a whole block of rows below this one
 #pragma unroll
-      for (int q = 0; q < QB; ++q)
+        for (int q = 0; q < QB; ++q) {
 #pragma unroll
-        for (int p = 0; p < RPL; ++p) {
-          const int i = lane + 64 * p, j = j0 - QB - q;
-          const bool in = j >= 0 && i < j;
-          vx[q][p] = Vs[in ? j * (j + 1) / 2 + i : 0];
+          for (int p = 0; p < RPL; ++p) vx[q][p] = Vs[ro + ic[p]];
+          ro -= j0 - QB - q;
         }
+      }
 #pragma unroll
       for (int q = 0; q < QB; ++q) {
-        const int j = j0 - q;
-        const float tj = readlane(pick(t, j >> 6), j & 63);
+        const float tj = lane_elem(t, j0 - q);
 #pragma unroll
         for (int p = 0; p < RPL; ++p) t[p] = fmaf(-va[q][p], tj, t[p]);
       }
 #pragma unroll
       for (int q = 0; q < QB; ++q) {
-        const int j = j0 - QB - q;
-        const int jc = j >= 0 ? j : 0;
-        const float rj = readlane(pick(rd, jc >> 6), jc & 63);
+        const float rj = lane_elem(rd, j0 - QB - q);
 #pragma unroll
-        for (int p = 0; p < RPL; ++p) {
-          const int i = lane + 64 * p;
-          va[q][p] = (j >= 0 && i < j) ? vx[q][p] * rj : 0.f;
-        }
+        for (int p = 0; p < RPL; ++p) va[q][p] = keep_lanes(vx[q][p] * rj, cm.m[p]);
+        cm.next();
       }
     }
   }
@@ -1289,63 +1433,50 @@ __global__ __launch_bounds__(64 * SOLVE_WAVES) void k_solve(DictView d, WorkView
     // does (the same FMA order per element), its 16-bit copy, ||r||^2 and, in
     // the 16-bit forms, the copy's error norm, and stores the norms in slice 0
     // (the other slices' entries stay at the zero the set-up wrote).
-    const int64_t nc4 = d.Mp / 4;
+    const uint32_t nc4 = (uint32_t)(d.Mp / 4);
     const float4 *A4 = reinterpret_cast<const float4 *>(d.A32);
     const float4 *Y4 = reinterpret_cast<const float4 *>(w.Yp) + b * nc4;
-    float4 *R4 = reinterpret_cast<float4 *>(w.R32) + b * nc4;
     // FP16 form: the copy is fp16(sigma r) with the scale chosen from ||r_k|| above
     const float sig = (BF16 && w.fp16) ? pow2_scale(rn) : 1.f;
+    const double isig = (BF16 && w.fp16) ? 1.0 / (double)sig : 1.0;
     double nrm = 0.0, dlt = 0.0;
-    for (int64_t c = lane; c < nc4; c += 64) {
-      float4 r = Y4[c];
-      // rounds of four atoms, their loads issued together; the sums run in
-      // support order (lanes past nc4 are inactive in the last pass: lane_elem,
-      // not pick)
+    // (past the end of the support: the pick's row, times x = 0)
+#pragma unroll
+    for (int p = 0; p < RPL; ++p) si[p] = lane + 64 * p < k ? si[p] : nstar;
+    // Rounds of four atoms, their loads issued together; the sums run in support
+    // order. The row's address is wave-uniform (scalar) and the lane's offset 32 bits,
+    // so an atom costs a lane two broadcasts and, per chunk, one load and four FMAs.
+    // (Lanes past nc4 are inactive in the last pass: lane_elem, not pick.)
+    auto chunks = [&](auto cn, uint32_t c) {
+      constexpr int CN = decltype(cn)::value;  // chunks per lane: c, c + 64
+      float4 r[CN];
+#pragma unroll
+      for (int e = 0; e < CN; ++e) r[e] = Y4[c + 64 * e];
       for (int j0 = 0; j0 < K; j0 += 4) {
-        float4 a[4];
+        float4 a[4][CN];
         float xj[4];
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
-          const int j = j0 + u < K ? j0 + u : K - 1;  // past K: a repeated load, not summed
-          const int sj = j < k ? lane_elem(si, j) : nstar;
-          xj[u] = -lane_elem(x, j);
-          a[u] = A4[(int64_t)sj * nc4 + c];
+          const char *row = reinterpret_cast<const char *>(A4 + (int64_t)lane_elem(si, j0 + u) * nc4);
+          xj[u] = -lane_elem(x, j0 + u);
+#pragma unroll
+          for (int e = 0; e < CN; ++e) a[u][e] = *reinterpret_cast<const float4 *>(row + (c + 64 * e) * 16u);
         }
 #pragma unroll
         for (int u = 0; u < 4; ++u)
-          if (j0 + u < K) {
-            r.x = fmaf(xj[u], a[u].x, r.x); r.y = fmaf(xj[u], a[u].y, r.y);
-            r.z = fmaf(xj[u], a[u].z, r.z); r.w = fmaf(xj[u], a[u].w, r.w);
+#pragma unroll
+          for (int e = 0; e < CN; ++e) {
+            r[e].x = fmaf(xj[u], a[u][e].x, r[e].x); r[e].y = fmaf(xj[u], a[u][e].y, r[e].y);
+            r[e].z = fmaf(xj[u], a[u][e].z, r[e].z); r[e].w = fmaf(xj[u], a[u][e].w, r[e].w);
           }
       }
-      R4[c] = r;
-      if (BF16 && w.fp16) {
-        ushort4 h;
-        h.x = f32_to_f16_rne(r.x * sig);
-        h.y = f32_to_f16_rne(r.y * sig);
-        h.z = f32_to_f16_rne(r.z * sig);
-        h.w = f32_to_f16_rne(r.w * sig);
-        reinterpret_cast<ushort4 *>(w.R16)[b * nc4 + c] = h;
-        const double e0 = (double)r.x - f16_used(h.x) / (double)sig;
-        const double e1 = (double)r.y - f16_used(h.y) / (double)sig;
-        const double e2 = (double)r.z - f16_used(h.z) / (double)sig;
-        const double e3 = (double)r.w - f16_used(h.w) / (double)sig;
-        dlt += e0 * e0 + e1 * e1 + e2 * e2 + e3 * e3;
-      } else if (BF16) {
-        ushort4 h;
-        h.x = f32_to_bf16_rne(r.x);
-        h.y = f32_to_bf16_rne(r.y);
-        h.z = f32_to_bf16_rne(r.z);
-        h.w = f32_to_bf16_rne(r.w);
-        reinterpret_cast<ushort4 *>(w.R16)[b * nc4 + c] = h;
-        const double e0 = (double)r.x - bf16_used(h.x);
-        const double e1 = (double)r.y - bf16_used(h.y);
-        const double e2 = (double)r.z - bf16_used(h.z);
-        const double e3 = (double)r.w - bf16_used(h.w);
-        dlt += e0 * e0 + e1 * e1 + e2 * e2 + e3 * e3;
-      }
-      nrm += (double)r.x * r.x + (double)r.y * r.y + (double)r.z * r.z + (double)r.w * r.w;
-    }
+#pragma unroll
+      for (int e = 0; e < CN; ++e) store_residual<BF16>(w, b * nc4 + c + 64 * e, r[e], sig, isig, nrm, dlt);
+    };
+    uint32_t c0 = 0;
+    for (; c0 + 128 <= nc4; c0 += 128) chunks(std::integral_constant<int, 2>(), c0 + lane);
+    for (; c0 < nc4; c0 += 64)
+      if (c0 + lane < nc4) chunks(std::integral_constant<int, 1>(), c0 + lane);
     nrm = wave_sum(nrm);
     if (BF16) dlt = wave_sum(dlt);
     if (lane == 0) {
@@ -2014,13 +2145,13 @@ __global__ __launch_bounds__(256) void k_residual(DictView d, WorkView w, int LP
   const int64_t c0 = (int64_t)slice * sl4;
   const float4 *A4 = reinterpret_cast<const float4 *>(d.A32) + c0;
   const float4 *Y4 = reinterpret_cast<const float4 *>(w.Yp) + b * nc4 + c0;
-  float4 *R4 = reinterpret_cast<float4 *>(w.R32) + b * nc4 + c0;
   const float *xi = xs + item * SP;
   const int *si = ss + item * SP;
   double nrm = 0.0, dlt = 0.0;
   // FP16 form: the copy is fp16(sigma r) with the scale the solve chose from ||r|| before
   // this update (so |sigma r_m| <= 1)
   const float sig = (BF16 && w.fp16) ? w.rscale_next[b] : 1.f;
+  const double isig = (BF16 && w.fp16) ? 1.0 / (double)sig : 1.0;
   for (int64_t c = sl; c < sl4; c += LP) {
     float4 r = Y4[c];
     int j = 0;
@@ -2040,33 +2171,7 @@ __global__ __launch_bounds__(256) void k_residual(DictView d, WorkView w, int LP
       const float x0 = xi[j];
       r.x = fmaf(x0, a.x, r.x); r.y = fmaf(x0, a.y, r.y); r.z = fmaf(x0, a.z, r.z); r.w = fmaf(x0, a.w, r.w);
     }
-    R4[c] = r;
-    if (BF16 && w.fp16) {
-      ushort4 h;
-      h.x = f32_to_f16_rne(r.x * sig);
-      h.y = f32_to_f16_rne(r.y * sig);
-      h.z = f32_to_f16_rne(r.z * sig);
-      h.w = f32_to_f16_rne(r.w * sig);
-      reinterpret_cast<ushort4 *>(w.R16)[b * nc4 + c0 + c] = h;
-      const double e0 = (double)r.x - f16_used(h.x) / (double)sig;
-      const double e1 = (double)r.y - f16_used(h.y) / (double)sig;
-      const double e2 = (double)r.z - f16_used(h.z) / (double)sig;
-      const double e3 = (double)r.w - f16_used(h.w) / (double)sig;
-      dlt += e0 * e0 + e1 * e1 + e2 * e2 + e3 * e3;
-    } else if (BF16) {
-      ushort4 h;
-      h.x = f32_to_bf16_rne(r.x);
-      h.y = f32_to_bf16_rne(r.y);
-      h.z = f32_to_bf16_rne(r.z);
-      h.w = f32_to_bf16_rne(r.w);
-      reinterpret_cast<ushort4 *>(w.R16)[b * nc4 + c0 + c] = h;
-      const double e0 = (double)r.x - bf16_used(h.x);
-      const double e1 = (double)r.y - bf16_used(h.y);
-      const double e2 = (double)r.z - bf16_used(h.z);
-      const double e3 = (double)r.w - bf16_used(h.w);
-      dlt += e0 * e0 + e1 * e1 + e2 * e2 + e3 * e3;
-    }
-    nrm += (double)r.x * r.x + (double)r.y * r.y + (double)r.z * r.z + (double)r.w * r.w;
+    store_residual<BF16>(w, b * nc4 + c0 + c, r, sig, isig, nrm, dlt);
   }
   // sum over the item's LP lanes (aligned groups): DPP within rows, then
   // permutes across rows for LP > 16
