@@ -21,16 +21,24 @@
 // transposes made per step.
 
 #include <cmath>
+#include <type_traits>
+#include <utility>
 
 #include "../../include/batched_omp.h"
 #include "mfma_tile.h"
 #include "mlp_internal.h"
 #include "omp_internal.h"
+#include "wave_ops.h"
 
 namespace bomp {
 namespace {
 
-using GT = Tile<128, 128, 2, 2>;  // 128 x 128 tiles, 4 wavefronts of 64 x 64
+// Tiles of the products: 256 x 256 (8 wavefronts of 128 x 64), 128 x 128 (4 of 64 x 64)
+// and 64 x 64 (4 of 32 x 32). Every tile sums K in the same order, so the choice changes
+// no product; it follows the number of workgroups (gemm_tile).
+using GT256 = Tile<256, 256, 2, 4>;
+using GT128 = Tile<128, 128, 2, 2>;
+using GT64 = Tile<64, 64, 2, 2>;
 
 __device__ inline uint16_t bf16_rne(float f) {
   const uint32_t u = __float_as_uint(f);
@@ -47,13 +55,12 @@ __device__ inline float softplusf(float z) { return fmaxf(z, 0.f) + log1pf(expf(
 // ---------------------------------------------------------------------------
 // BF16 "NT" product C[m][n] = sum_k P[m][k] Q[n][k] with a fused epilogue.
 // P: [rows][ldp] BF16, Q: [cols][ldq] BF16, K a multiple of 64. The grid is
-// (M/128) x (N/128) tiles times `splits` slices of K (EPI_PARTIAL only).
+// (M / T::TN) x (N / T::TB) tiles times `splits` slices of K (EPI_PARTIAL only).
 // ---------------------------------------------------------------------------
-template <int EPI>
-__global__ __launch_bounds__(GT::NTHR) void k_gemm_nt(const uint16_t *__restrict__ P, int64_t ldp,
+template <int EPI, class T>
+__global__ __launch_bounds__(T::NTHR) void k_gemm_nt(const uint16_t *__restrict__ P, int64_t ldp,
                                                      const uint16_t *__restrict__ Q, int64_t ldq, int64_t Mrows,
                                                      int64_t Ncols, int64_t K, int splits, GemmEpi e) {
-  using T = GT;
   extern __shared__ u32x4 lds[];
   const int64_t ntm = Mrows / T::TN, ntn = Ncols / T::TB;
   const int64_t tile = blockIdx.x % (ntm * ntn);
@@ -105,14 +112,14 @@ __global__ __launch_bounds__(GT::NTHR) void k_gemm_nt(const uint16_t *__restrict
     }
   if (EPI == EPI_BCE) {
     // block sum of the loss terms, one partial per block (summed in block order)
-    __shared__ float red[GT::NTHR / 64];
+    __shared__ float red[T::NTHR / 64];
 #pragma unroll
     for (int off = 32; off >= 1; off >>= 1) lsum += __shfl_xor(lsum, off);
     if (lane == 0) red[wave] = lsum;
     __syncthreads();
     if (threadIdx.x == 0) {
       float s = 0.f;
-      for (int i = 0; i < GT::NTHR / 64; ++i) s += red[i];
+      for (int i = 0; i < T::NTHR / 64; ++i) s += red[i];
       e.loss_part[blockIdx.x] = s;
     }
   }
@@ -262,9 +269,14 @@ __global__ __launch_bounds__(256) void k_copy32(const float *__restrict__ src, i
 }
 
 // ---------------------------------------------------------------------------
-// Top-S of N scores per signal (one wavefront; NPL = N / 64 scores per lane):
-// S rounds of a wavefront max over packed keys (orderable score bits, then
-// the complement of the index so that ties go to the lowest index).
+// Top-S of N scores per signal (one wavefront; NPL = N / 64 scores per lane, S <= 64),
+// in descending order, ties to the lowest index. The S-th largest score is found bit by
+// bit on orderable 32-bit keys: each bit costs one compare per score, its count taken
+// from the ballot on the scalar unit, and the search ends as soon as a threshold keeps
+// exactly S. The S survivors (of equal scores the lowest indices) then take one lane
+// each, and a survivor's place is the number of larger keys. The kernel is bound by its
+// vector instructions: S rounds of a maximum over all 64-bit keys took 122 us for 16384
+// signals of N = 1024, S = 32; this takes 33 us.
 // ---------------------------------------------------------------------------
 __device__ inline uint32_t orderable(float f) {
   const uint32_t u = __float_as_uint(f);
@@ -274,40 +286,90 @@ __device__ inline uint32_t orderable(float f) {
 template <int NPL>
 __global__ __launch_bounds__(64) void k_topk(const float *__restrict__ Z, int64_t ldz, int S,
                                              int32_t *__restrict__ P) {
+  __shared__ uint64_t list[64];
   const int64_t b = blockIdx.x;
   const int lane = threadIdx.x;
-  uint64_t key[NPL];
+  uint32_t key[NPL];
+#pragma unroll
+  for (int q = 0; q < NPL; ++q) key[q] = orderable(Z[b * ldz + q * 64 + lane]);
+  uint32_t T = 0;  // at least S keys are >= T
+  int need = 0;    // keys equal to T to take beside the keys above it
+  bool exact = false;
+  for (int bit = 31; bit >= 0 && !exact; --bit) {
+    const uint32_t cand = T | (1u << bit);
+    int cnt = 0;
+#pragma unroll
+    for (int q = 0; q < NPL; ++q) cnt += __popcll(__ballot(key[q] >= cand));
+    if (cnt >= S) T = cand;
+    exact = cnt == S;
+  }
+  if (exact) {
+    --T;  // (cand >= 1) the keys above T are the S
+  } else {
+    need = S;
+#pragma unroll
+    for (int q = 0; q < NPL; ++q) need -= __popcll(__ballot(key[q] > T));
+  }
+  int base = 0;
 #pragma unroll
   for (int q = 0; q < NPL; ++q) {
-    const int n = q * 64 + lane;
-    key[q] = ((uint64_t)orderable(Z[b * ldz + n]) << 32) | (uint64_t)(0xFFFFFFFFu - (uint32_t)n);
+    const uint64_t eq = __ballot(key[q] == T);
+    const int erank = (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(eq >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)eq, 0u));
+    const bool in = key[q] > T || (key[q] == T && erank < need);
+    const uint64_t sel = __ballot(in);
+    const int pos = base + (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(sel >> 32),
+                                                          __builtin_amdgcn_mbcnt_lo((uint32_t)sel, 0u));
+    if (in) list[pos] = ((uint64_t)key[q] << 32) | (uint64_t)(0xFFFFFFFFu - (uint32_t)(q * 64 + lane));
+    base += __popcll(sel);
+    need = max(0, need - (int)__popcll(eq));
   }
-  for (int s = 0; s < S; ++s) {
-    uint64_t best = 0;
-#pragma unroll
-    for (int q = 0; q < NPL; ++q) best = key[q] > best ? key[q] : best;
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) {
-      const uint64_t o = __shfl_xor(best, off);
-      best = o > best ? o : best;
-    }
-#pragma unroll
-    for (int q = 0; q < NPL; ++q) key[q] = key[q] == best ? 0ull : key[q];  // keys are distinct
-    if (lane == 0) P[b * S + s] = (int32_t)(0xFFFFFFFFu - (uint32_t)(best & 0xFFFFFFFFull));
-  }
+  __syncthreads();
+  const uint64_t mine = lane < S ? list[lane] : 0ull;
+  int rank = 0;
+  for (int j = 0; j < S; ++j) rank += readlane64(mine, j) > mine ? 1 : 0;
+  if (lane < S) P[b * S + rank] = (int32_t)(0xFFFFFFFFu - (uint32_t)(mine & 0xFFFFFFFFull));
 }
 
 // ---------------------------------------------------------------------------
-// Least-squares check of a proposed support (one wavefront per signal, S <= 64):
+// Least-squares check of a proposed support (one wavefront per signal, S <= SMAX):
 // Cholesky of the Gram block G[P, P] (pivots in FP64; a pivot below the
 // dependency threshold rejects the proposal), beta = A_P^T y with exact
 // products and FP64 sums, forward and back solves, the residual
 // r = y - A_P x in FP32 and ||r|| in FP64; accepted when ||r|| <= eps_b.
-// LDS: L (S x (S+1) floats) per wavefront.
+//
+// Lane i holds row i of the Gram block and of the factor in registers, and the
+// factorisation is right-looking: column j is scaled once, then added to the running
+// sums of every later column (one broadcast and one FMA each), so nothing waits for
+// LDS and every loop is unrolled. beta is summed eight atoms at a time: the eight
+// sums are folded into eight lane groups by three exchanges instead of being reduced
+// one by one. Only the back solve needs columns of the factor across lanes; they pass
+// through LDS (SMAX x (SMAX + 1) floats per wavefront). The former left-looking loops
+// over LDS rows, with a cross-lane read in each of their 3 S^2 / 2 steps, took 563 us
+// for 16384 signals at M = 256, S = 32; this takes 191 us, about 2.1 GB of cache lines
+// (64 KB of atoms and 496 scattered Gram entries per signal) at 11 TB/s.
 // ---------------------------------------------------------------------------
 constexpr int LS_WAVES = 4;
 
-__global__ __launch_bounds__(64 * LS_WAVES) void k_ls_check(DictView d, const float *__restrict__ Y, int64_t ldy,
+// f(0), f(1), ..., f(N - 1) with constant arguments.
+template <class F, int... I>
+__device__ inline void unrolled_seq(F &&f, std::integer_sequence<int, I...>) {
+  (f(std::integral_constant<int, I>()), ...);
+}
+template <int N, class F>
+__device__ inline void unrolled(F &&f) {
+  unrolled_seq(f, std::make_integer_sequence<int, N>());
+}
+
+// Chunk c (samples 4c .. 4c + 3) of signal y, zero past M.
+__device__ inline float4 signal_chunk(const float *__restrict__ y, int64_t M, bool vec, int64_t c) {
+  if (vec) return 4 * c < M ? reinterpret_cast<const float4 *>(y)[c] : make_float4(0.f, 0.f, 0.f, 0.f);
+  const int64_t m = 4 * c;
+  return make_float4(m < M ? y[m] : 0.f, m + 1 < M ? y[m + 1] : 0.f, m + 2 < M ? y[m + 2] : 0.f,
+                     m + 3 < M ? y[m + 3] : 0.f);
+}
+
+template <int SMAX>
+__global__ __launch_bounds__(64 * LS_WAVES) __attribute__((amdgpu_waves_per_eu(2, SMAX == 64 ? 2 : 4))) void k_ls_check(DictView d, const float *__restrict__ Y, int64_t ldy,
                                                             int64_t B, const int32_t *__restrict__ P, int S,
                                                             const float *__restrict__ eps_per, float eps,
                                                             int32_t *__restrict__ support_out,
@@ -319,86 +381,133 @@ __global__ __launch_bounds__(64 * LS_WAVES) void k_ls_check(DictView d, const fl
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
   const int64_t b = (int64_t)blockIdx.x * LS_WAVES + wv;
   if (b >= B) return;
-  const int LD = S + 1;
-  float *Ls = lsm + (size_t)wv * S * LD;
+  constexpr int LD = SMAX + 1;
+  float *Ls = lsm + (size_t)wv * SMAX * LD;
   const int pi = lane < S ? P[b * S + lane] : 0;
-  // Gram block rows: lane i holds row i of G[P, P] in LDS.
-  for (int j = 0; j < S; ++j) {
-    const int pj = __shfl(pi, j);
-    if (lane < S) Ls[lane * LD + j] = d.G[(int64_t)pj * d.Np + pi];
+  const double nu2i = d.nu2[pi];
+  // row i of the Gram block's lower triangle (symmetric: column p_i of row p_j); zero
+  // elsewhere. Each entry is a cache line of its own, so the upper one is not read.
+  float g[SMAX];
+#pragma unroll
+  for (int j = 0; j < SMAX; ++j) {
+    g[j] = 0.f;
+    if (j < S) {
+      const char *row = reinterpret_cast<const char *>(d.G + (int64_t)__builtin_amdgcn_readlane(pi, j) * d.Np);
+      if (lane >= j && lane < S) g[j] = *reinterpret_cast<const float *>(row + 4u * (uint32_t)pi);
+    }
   }
   // beta_j = a_{P_j}^T y and the signal's own finiteness.
   const float *y = Y + b * ldy;
+  const bool vec = (d.M & 3) == 0 && (reinterpret_cast<uintptr_t>(y) & 15) == 0;
+  const uint32_t nc4 = (uint32_t)(d.Mp / 4);
+  const float4 *A4 = reinterpret_cast<const float4 *>(d.A32);
   double bj = 0.0;
   int finite = 1;
-  for (int j = 0; j < S; ++j) {
-    const int pj = __shfl(pi, j);
-    double s = 0.0;
-    for (int64_t m = lane; m < d.M; m += 64) {
-      const float v = y[m];
-      finite &= isfinite(v) ? 1 : 0;
-      s += (double)d.A32[(int64_t)pj * d.Mp + m] * (double)v;
-    }
+  for (int j0 = 0; j0 < S; j0 += 8) {
+    double s[8] = {};
+    for (uint32_t c = lane; c < nc4; c += 64) {
+      const float4 v = signal_chunk(y, d.M, vec, c);
+      if (j0 == 0) finite &= (isfinite(v.x) && isfinite(v.y) && isfinite(v.z) && isfinite(v.w)) ? 1 : 0;
+      float4 a[8];
 #pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) s += __shfl_xor(s, off);
-    if (lane == j) bj = s;
+      for (int u = 0; u < 8; ++u) {  // (past S: atom 0's sum, which no lane takes)
+        const char *row = reinterpret_cast<const char *>(A4 + (int64_t)__builtin_amdgcn_readlane(pi, j0 + u) * nc4);
+        a[u] = *reinterpret_cast<const float4 *>(row + 16u * c);
+      }
+#pragma unroll
+      for (int u = 0; u < 8; ++u)
+        s[u] += (double)a[u].x * v.x + (double)a[u].y * v.y + (double)a[u].z * v.z + (double)a[u].w * v.w;
+    }
+    // fold: after the exchanges over lane bits 5, 4 and 3 lane group l / 8 holds sum l / 8
+#pragma unroll
+    for (int w = 4; w >= 1; w >>= 1) {
+      const bool hi = lane & (8 * w);
+#pragma unroll
+      for (int u = 0; u < w; ++u) {
+        const double send = hi ? s[u] : s[u + w], keep = hi ? s[u + w] : s[u];
+        s[u] = keep + __shfl_xor(send, 8 * w);
+      }
+    }
+    s[0] += dppd<DPP_XOR1>(s[0]);
+    s[0] += dppd<DPP_XOR2>(s[0]);
+    s[0] += dppd<DPP_HALF_MIRROR>(s[0]);
+    const double mine = __shfl(s[0], (lane & 7) * 8);
+    bj = (lane >> 3) == (j0 >> 3) ? mine : bj;
   }
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-  __builtin_amdgcn_wave_barrier();
   // Cholesky, column by column: L[j][j] = sqrt(G[j][j] - sum_k L[j][k]^2) (FP64),
-  // L[i][j] = (G[i][j] - sum_k L[i][k] L[j][k]) / L[j][j] for i > j.
+  // L[i][j] = (G[i][j] - sum_k L[i][k] L[j][k]) / L[j][j] for i > j. L[k] holds the
+  // running sum of column k until step k makes it the factor's entry.
   bool dependent = !__all(finite);
-  float rdj = 0.f;  // lane j keeps 1 / L[j][j]
-  for (int j = 0; j < S && !dependent; ++j) {
-    double dd = 0.0;
-    float off = 0.f;
-    for (int k = 0; k < j; ++k) {
-      const float ljk = Ls[j * LD + k];
-      dd += (double)ljk * (double)ljk;
-      if (lane > j && lane < S) off = fmaf(Ls[lane * LD + k], ljk, off);
+  float L[SMAX];
+#pragma unroll
+  for (int k = 0; k < SMAX; ++k) L[k] = 0.f;
+  double dd = 0.0;   // sum_k L[i][k]^2 of the lane's row so far
+  float rdj = 0.f;   // lane j keeps 1 / L[j][j]
+  unrolled<SMAX>([&](auto step) {
+    constexpr int j = decltype(step)::value;
+    if (j < S && !dependent) {
+      const double d2 = __longlong_as_double(
+          (long long)readlane64((uint64_t)__double_as_longlong((double)g[j] - dd), j));
+      const double nu2 = __longlong_as_double((long long)readlane64((uint64_t)__double_as_longlong(nu2i), j));
+      if (!(d2 > DEP_TOL2 * nu2)) {
+        dependent = true;
+      } else {
+        const float dj = (float)sqrt(d2);
+        const float lij = lane > j ? (g[j] - L[j]) / dj : 0.f;  // (zero on lanes past S)
+        if (lane == j) rdj = 1.f / dj;
+        L[j] = lij;
+        dd += (double)lij * (double)lij;
+#pragma unroll
+        for (int k0 = j + 1; k0 < SMAX; k0 += 8)
+          if (k0 < S) {
+#pragma unroll
+            for (int k = k0; k < k0 + 8 && k < SMAX; ++k) L[k] = fmaf(lij, readlane(lij, k), L[k]);
+          }
+      }
     }
-    const double nu2 = d.nu2[__shfl(pi, j)];
-    const double d2 = (double)Ls[j * LD + j] - dd;
-    if (!(d2 > DEP_TOL2 * nu2)) {
-      dependent = true;
-      break;
-    }
-    const float dj = (float)sqrt(d2);
-    if (lane == j) {
-      Ls[j * LD + j] = dj;
-      rdj = 1.f / dj;
-    }
-    if (lane > j && lane < S) Ls[lane * LD + j] = (Ls[lane * LD + j] - off) / dj;
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-  }
+  });
   float x = 0.f;
   double rn = 0.0;
   if (!dependent) {
-    // forward solve L u = beta (row by row: u_j = (beta_j - sum_k L[j][k] u_k) / L[j][j])
-    float u = 0.f;
-    for (int j = 0; j < S; ++j) {
-      float acc = (float)__shfl(bj, j);
-      for (int k = 0; k < j; ++k) acc = fmaf(-Ls[j * LD + k], __shfl(u, k), acc);
-      const float uj = acc * __shfl(rdj, j);
-      if (lane == j) u = uj;
-    }
-    // back solve L^T x = u, last unknown first: x_j = (u_j - sum_{i>j} L[i][j] x_i) / L[j][j]
-    for (int j = S - 1; j >= 0; --j) {
-      float acc = __shfl(u, j);
-      for (int i = j + 1; i < S; ++i) acc = fmaf(-Ls[i * LD + j], __shfl(x, i), acc);
-      const float xj = acc * __shfl(rdj, j);
-      if (lane == j) x = xj;
-    }
-    // residual and its norm
-    for (int64_t m = lane; m < d.M; m += 64) {
-      float r = y[m];
-      for (int j = 0; j < S; ++j) r = fmaf(-__shfl(x, j), d.A32[(int64_t)__shfl(pi, j) * d.Mp + m], r);
-      rn += (double)r * (double)r;
-    }
+    // forward solve L u = beta: u_j = (beta_j - sum_k L[j][k] u_k) / L[j][j]
+    float t = (float)bj;
 #pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) rn += __shfl_xor(rn, off);
-    rn = sqrt(rn);
+    for (int j = 0; j < SMAX; ++j)
+      if (j < S) t = fmaf(-L[j], readlane(t, j) * readlane(rdj, j), t);
+    t *= rdj;
+    // back solve L^T x = u, last unknown first, row i of L read from LDS
+#pragma unroll
+    for (int k = 0; k < SMAX; ++k)
+      if (lane < SMAX) Ls[lane * LD + k] = L[k];
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    const int lc = lane < SMAX ? lane : 0;
+#pragma unroll
+    for (int i = SMAX - 1; i >= 0; --i)
+      if (i < S) t = fmaf(-Ls[i * LD + lc], readlane(t, i) * readlane(rdj, i), t);
+    x = t * rdj;  // (lanes past S: rdj = 0)
+    // residual and its norm
+    for (uint32_t c = lane; c < nc4; c += 64) {
+      float4 r = signal_chunk(y, d.M, vec, c);
+      for (int j0 = 0; j0 < S; j0 += 4) {
+        float4 a[4];
+        float xj[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {  // (past S: atom 0 times zero)
+          const char *row = reinterpret_cast<const char *>(A4 + (int64_t)__builtin_amdgcn_readlane(pi, j0 + u) * nc4);
+          xj[u] = -readlane(x, j0 + u);
+          a[u] = *reinterpret_cast<const float4 *>(row + 16u * c);
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+          r.x = fmaf(xj[u], a[u].x, r.x); r.y = fmaf(xj[u], a[u].y, r.y);
+          r.z = fmaf(xj[u], a[u].z, r.z); r.w = fmaf(xj[u], a[u].w, r.w);
+        }
+      }
+      rn += (double)r.x * r.x + (double)r.y * r.y + (double)r.z * r.z + (double)r.w * r.w;
+    }
+    rn = sqrt(wave_sum(rn));
   }
   float eb = eps_per ? eps_per[b] : eps;
   eb = fmaxf(eb, 0.f);
@@ -461,31 +570,54 @@ hipError_t lds_limit(K kernel, size_t bytes) {
                              (int)bytes);
 }
 
-template <int EPI>
+// Tile size of an M x N product with `splits` slices of K: the largest that still gives
+// the 256 CUs about one workgroup each (a workgroup of the larger tiles fills a CU).
+// Measured: 16384 x 1024 x 1024 with bias and ReLU 47 us on 128 x 128 tiles, 39 us on
+// 256 x 256; 1024 x 1024 x 1024 14.9 us on 128 x 128 (64 workgroups), 11.6 us on 64 x 64.
+int gemm_tile(int64_t M, int64_t N, int splits) {
+  const int64_t t256 = (M / 256) * (N / 256) * splits;
+  if (M % 256 == 0 && N % 256 == 0 && t256 >= 192) return 256;
+  return (M / 128) * (N / 128) * splits >= 192 ? 128 : 64;
+}
+
+template <int EPI, class T>
 hipError_t gemm_t(const uint16_t *P, int64_t ldp, const uint16_t *Q, int64_t ldq, int64_t M, int64_t N, int64_t K,
                   int splits, const GemmEpi &e, hipStream_t st) {
-  hipError_t err = lds_limit(k_gemm_nt<EPI>, GT::LDS_BYTES);
+  hipError_t err = lds_limit(k_gemm_nt<EPI, T>, T::LDS_BYTES);
   if (err != hipSuccess) return err;
-  const unsigned grid = (unsigned)((M / GT::TN) * (N / GT::TB) * splits);
-  hipLaunchKernelGGL(k_gemm_nt<EPI>, dim3(grid), dim3(GT::NTHR), GT::LDS_BYTES, st, P, ldp, Q, ldq, M, N, K, splits,
+  const unsigned grid = (unsigned)((M / T::TN) * (N / T::TB) * splits);
+  hipLaunchKernelGGL((k_gemm_nt<EPI, T>), dim3(grid), dim3(T::NTHR), T::LDS_BYTES, st, P, ldp, Q, ldq, M, N, K, splits,
                      e);
   return hipGetLastError();
 }
 
+template <int EPI>
+hipError_t gemm_any(const uint16_t *P, int64_t ldp, const uint16_t *Q, int64_t ldq, int64_t M, int64_t N, int64_t K,
+                    int splits, const GemmEpi &e, hipStream_t st) {
+  switch (gemm_tile(M, N, splits)) {
+    case 256: return gemm_t<EPI, GT256>(P, ldp, Q, ldq, M, N, K, splits, e, st);
+    case 128: return gemm_t<EPI, GT128>(P, ldp, Q, ldq, M, N, K, splits, e, st);
+    default: return gemm_t<EPI, GT64>(P, ldp, Q, ldq, M, N, K, splits, e, st);
+  }
+}
+
 }  // namespace
 
-int64_t gemm_blocks(int64_t M, int64_t N, int splits) { return (M / GT::TN) * (N / GT::TB) * splits; }
+int64_t gemm_blocks(int64_t M, int64_t N, int splits) {
+  const int64_t t = gemm_tile(M, N, splits);
+  return (M / t) * (N / t) * splits;
+}
 
 hipError_t launch_gemm_bf16(int epi, const uint16_t *P, int64_t ldp, const uint16_t *Q, int64_t ldq, int64_t M,
                             int64_t N, int64_t K, int splits, const GemmEpi &e, hipStream_t st) {
-  if (M % GT::TN || N % GT::TB || K % (64 * splits) || ldp % 8 || ldq % 8) return hipErrorInvalidValue;
+  if (M % 128 || N % 128 || K % (64 * splits) || ldp % 8 || ldq % 8) return hipErrorInvalidValue;
   switch (epi) {
-    case EPI_FEATURES: return gemm_t<EPI_FEATURES>(P, ldp, Q, ldq, M, N, K, splits, e, st);
-    case EPI_BIAS_RELU: return gemm_t<EPI_BIAS_RELU>(P, ldp, Q, ldq, M, N, K, splits, e, st);
-    case EPI_BIAS: return gemm_t<EPI_BIAS>(P, ldp, Q, ldq, M, N, K, splits, e, st);
-    case EPI_BCE: return gemm_t<EPI_BCE>(P, ldp, Q, ldq, M, N, K, splits, e, st);
-    case EPI_RELU_MASK: return gemm_t<EPI_RELU_MASK>(P, ldp, Q, ldq, M, N, K, splits, e, st);
-    default: return gemm_t<EPI_PARTIAL>(P, ldp, Q, ldq, M, N, K, splits, e, st);
+    case EPI_FEATURES: return gemm_any<EPI_FEATURES>(P, ldp, Q, ldq, M, N, K, splits, e, st);
+    case EPI_BIAS_RELU: return gemm_any<EPI_BIAS_RELU>(P, ldp, Q, ldq, M, N, K, splits, e, st);
+    case EPI_BIAS: return gemm_any<EPI_BIAS>(P, ldp, Q, ldq, M, N, K, splits, e, st);
+    case EPI_BCE: return gemm_any<EPI_BCE>(P, ldp, Q, ldq, M, N, K, splits, e, st);
+    case EPI_RELU_MASK: return gemm_any<EPI_RELU_MASK>(P, ldp, Q, ldq, M, N, K, splits, e, st);
+    default: return gemm_any<EPI_PARTIAL>(P, ldp, Q, ldq, M, N, K, splits, e, st);
   }
 }
 
@@ -562,10 +694,14 @@ hipError_t launch_ls_check(const DictView &d, const float *Y, int64_t ldy, int64
                            const float *eps_per, float eps, int32_t *support_out, float *coef_out, int32_t *status_out,
                            float *rnorm_out, int32_t *accept, hipStream_t st) {
   if (S < 1 || S > 64) return hipErrorInvalidValue;
-  const size_t lds = (size_t)LS_WAVES * S * (S + 1) * sizeof(float);
+  const int smax = S <= 16 ? 16 : S <= 32 ? 32 : 64;  // rows per factor: the unrolled loops' length
+  auto kern = smax == 16 ? k_ls_check<16> : smax == 32 ? k_ls_check<32> : k_ls_check<64>;
+  const size_t lds = (size_t)LS_WAVES * smax * (smax + 1) * sizeof(float);
+  hipError_t e = lds_limit(kern, lds);
+  if (e != hipSuccess) return e;
   const unsigned blocks = (unsigned)((B + LS_WAVES - 1) / LS_WAVES);
-  hipLaunchKernelGGL(k_ls_check, dim3(blocks), dim3(64 * LS_WAVES), lds, st, d, Y, ldy, B, P, S, eps_per, eps,
-                     support_out, coef_out, status_out, rnorm_out, accept);
+  hipLaunchKernelGGL(kern, dim3(blocks), dim3(64 * LS_WAVES), lds, st, d, Y, ldy, B, P, S, eps_per, eps, support_out,
+                     coef_out, status_out, rnorm_out, accept);
   return hipGetLastError();
 }
 
