@@ -8,7 +8,8 @@
 // v_mfma_f32_32x32x16_bf16 for BF16, v_mfma_f32_32x32x16_f16 for FP16). Operands are staged through LDS in
 // 128-byte K slices, double buffered, with direct global-to-LDS loads (16
 // bytes per lane, no register round trip); the 16-bit products also double-buffer
-// their fragments in registers (mainloop_pipelined). A staged row is 8 chunks of 16
+// their fragments in registers (mainloop_pipelined) or, on small tiles, keep several
+// slices in flight (mainloop_staged). A staged row is 8 chunks of 16
 // bytes; chunk c of row r sits at slot c ^ ((r >> 1) & 7) of the row, so the
 // 16 lanes of one LDS read phase (16 consecutive rows, one chunk) hit 16
 // distinct 4-bank groups. Lane l of a fragment reads row (l mod 32) at chunk
@@ -301,6 +302,77 @@ __device__ inline void mainloop_serial(const u32x4 *__restrict__ P, int64_t prs,
                                          16, 0, 0);
     }
     const u32x4 *L = lds + buf * T::STAGE;
+#pragma unroll
+    for (int q = 0; q < T::CH / 2; ++q) {
+      u32x4 af[T::FN], bf[T::FB];
+#pragma unroll
+      for (int i = 0; i < T::FN; ++i) af[i] = L[aoff[i] + ((2 * q + h) ^ asw[i])];
+#pragma unroll
+      for (int j = 0; j < T::FB; ++j) bf[j] = L[boff[j] + ((2 * q + h) ^ bsw[j])];
+#pragma unroll
+      for (int i = 0; i < T::FN; ++i)
+#pragma unroll
+        for (int j = 0; j < T::FB; ++j) Op::mma(af[i], bf[j], acc[i][j]);
+    }
+  }
+  __syncthreads();
+}
+
+// Waits until at most N of the wavefront's vector memory operations are outstanding.
+template <int N>
+__device__ inline void wait_vm() {
+  static_assert(N >= 0 && N < 64, "vmcnt holds six bits");
+  __builtin_amdgcn_s_waitcnt((N & 15) | (7 << 4) | (15 << 8) | ((N >> 4) << 14));
+}
+
+// Staged main loop (16-bit operands, small tiles): the same sums in the same order as
+// mainloop_pipelined, with NST LDS buffers and NST - 1 slices in flight. A small tile has
+// a few hundred cycles of work per slice against 1500 to 2000 of memory latency, so with
+// two buffers it waits for every slice; the lines of the next slices have to be under way.
+// (NST * STAGE * 16 bytes of LDS.) Ends with a barrier.
+template <class Op, class T, int NST>
+__device__ inline void mainloop_staged(const u32x4 *__restrict__ P, int64_t prs, const u32x4 *__restrict__ Q,
+                                       int64_t qrs, int nslices, u32x4 *lds, f32x16 (&acc)[T::FN][T::FB]) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int wn = wave % T::WN, wb = wave / T::WN;
+  const int h = lane >> 5, r32 = lane & 31;
+#pragma unroll
+  for (int i = 0; i < T::FN; ++i)
+#pragma unroll
+    for (int j = 0; j < T::FB; ++j) acc[i][j] = f32x16{};
+  const u32x4 *src[T::LPW];
+#pragma unroll
+  for (int i = 0; i < T::LPW; ++i) src[i] = stage_src<T>(P, prs, Q, qrs, i);
+  auto issue = [&](int s) {
+#pragma unroll
+    for (int i = 0; i < T::LPW; ++i)
+      dma16(reinterpret_cast<const void *>(src[i] + (int64_t)s * T::CH),
+            (lds_void_t *)(lds + (s % NST) * T::STAGE + (i * T::NW + wave) * 64));
+  };
+  int aoff[T::FN], asw[T::FN], boff[T::FB], bsw[T::FB];
+#pragma unroll
+  for (int i = 0; i < T::FN; ++i) {
+    const int row = wn * T::FN * 32 + i * 32 + r32;
+    aoff[i] = row * T::CH;
+    asw[i] = (row >> 1) & 7;
+  }
+#pragma unroll
+  for (int j = 0; j < T::FB; ++j) {
+    const int row = T::TN + wb * T::FB * 32 + j * 32 + r32;
+    boff[j] = row * T::CH;
+    bsw[j] = (row >> 1) & 7;
+  }
+  __builtin_amdgcn_s_waitcnt(0);  // only this loop's loads are counted below
+#pragma unroll
+  for (int s = 0; s < NST - 1; ++s)
+    if (s < nslices) issue(s);
+  for (int s = 0; s < nslices; ++s) {
+    // slice s has landed here when no more than the loads of the NST - 2 later slices are out
+    if (s + NST - 2 < nslices) wait_vm<(NST - 2) * T::LPW>();
+    else wait_vm<0>();
+    __syncthreads();  // ... and everywhere; slice s - 1 is no longer read
+    if (s + NST - 1 < nslices) issue(s + NST - 1);
+    const u32x4 *L = lds + (s % NST) * T::STAGE;
 #pragma unroll
     for (int q = 0; q < T::CH / 2; ++q) {
       u32x4 af[T::FN], bf[T::FB];

@@ -46,32 +46,39 @@ __device__ inline uint16_t bf16_rne(float f) {
 }
 __device__ inline float bf16_to_f32(uint16_t h) { return __uint_as_float((uint32_t)h << 16); }
 
-__device__ inline float sigmoidf(float z) {
-  const float e = expf(-fabsf(z));
-  return z >= 0.f ? 1.f / (1.f + e) : e / (1.f + e);
-}
-__device__ inline float softplusf(float z) { return fmaxf(z, 0.f) + log1pf(expf(-fabsf(z))); }
+// sigmoid(z) and softplus(z) from e = exp(-|z|).
+__device__ inline float sigmoid_of(float z, float e) { return (z >= 0.f ? 1.f : e) / (1.f + e); }
+__device__ inline float softplus_of(float z, float e) { return fmaxf(z, 0.f) + log1pf(e); }
 
 // ---------------------------------------------------------------------------
 // BF16 "NT" product C[m][n] = sum_k P[m][k] Q[n][k] with a fused epilogue.
 // P: [rows][ldp] BF16, Q: [cols][ldq] BF16, K a multiple of 64. The grid is
 // (M / T::TN) x (N / T::TB) tiles times `splits` slices of K (EPI_PARTIAL only).
 // ---------------------------------------------------------------------------
+constexpr int GT64_STAGES = 4;  // LDS buffers of the 64 x 64 tiles' main loop (64 KiB)
+template <class T>
+constexpr size_t gemm_lds() {
+  return T::TN == 64 ? (size_t)GT64_STAGES * T::STAGE * 16 : T::LDS_BYTES;
+}
+
 template <int EPI, class T>
-__global__ __launch_bounds__(T::NTHR) void k_gemm_nt(const uint16_t *__restrict__ P, int64_t ldp,
-                                                     const uint16_t *__restrict__ Q, int64_t ldq, int64_t Mrows,
-                                                     int64_t Ncols, int64_t K, int splits, GemmEpi e) {
+__device__ inline void gemm_nt_tile(const uint16_t *__restrict__ P, int64_t ldp, const uint16_t *__restrict__ Q,
+                                    int64_t ldq, int64_t Mrows, int64_t Ncols, int64_t K, int splits, int64_t block,
+                                    const GemmEpi &e) {
   extern __shared__ u32x4 lds[];
   const int64_t ntm = Mrows / T::TN, ntn = Ncols / T::TB;
-  const int64_t tile = blockIdx.x % (ntm * ntn);
-  const int split = (int)(blockIdx.x / (ntm * ntn));
+  const int64_t tile = block % (ntm * ntn);
+  const int split = (int)(block / (ntm * ntn));
   const int64_t tm = tile % ntm, tn = tile / ntm;
   const int64_t kc = K / splits;  // elements of K per split (a multiple of 64)
   const int64_t prs = ldp / 8, qrs = ldq / 8;
   const u32x4 *Pp = reinterpret_cast<const u32x4 *>(P) + tm * T::TN * prs + (split * kc) / 8;
   const u32x4 *Qp = reinterpret_cast<const u32x4 *>(Q) + tn * T::TB * qrs + (split * kc) / 8;
   f32x16 acc[T::FN][T::FB];
-  mainloop<OpBF16, T>(Pp, prs, Qp, qrs, (int)(kc / 64), lds, acc);
+  if constexpr (T::TN == 64)
+    mainloop_staged<OpBF16, T, GT64_STAGES>(Pp, prs, Qp, qrs, (int)(kc / 64), lds, acc);
+  else
+    mainloop<OpBF16, T>(Pp, prs, Qp, qrs, (int)(kc / 64), lds, acc);
 
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int wn = wave % T::WN, wb = wave / T::WN;
@@ -98,8 +105,9 @@ __global__ __launch_bounds__(T::NTHR) void k_gemm_nt(const uint16_t *__restrict_
           if (m < e.mvalid) {
             const float z = c + e.bias[n];
             const float t = (float)((e.labels[m * e.ldl + (n >> 5)] >> (n & 31)) & 1u);
-            dz = (sigmoidf(z) - t) * e.scale;
-            lsum += softplusf(z) - t * z;
+            const float ez = expf(-fabsf(z));
+            dz = (sigmoid_of(z, ez) - t) * e.scale;
+            lsum += softplus_of(z, ez) - t * z;
           }
           reinterpret_cast<uint16_t *>(e.out)[o] = bf16_rne(dz);
         } else if (EPI == EPI_RELU_MASK) {
@@ -120,9 +128,29 @@ __global__ __launch_bounds__(T::NTHR) void k_gemm_nt(const uint16_t *__restrict_
     if (threadIdx.x == 0) {
       float s = 0.f;
       for (int i = 0; i < T::NTHR / 64; ++i) s += red[i];
-      e.loss_part[blockIdx.x] = s;
+      e.loss_part[block] = s;
     }
   }
+}
+
+template <int EPI, class T>
+__global__ __launch_bounds__(T::NTHR) void k_gemm_nt(const uint16_t *__restrict__ P, int64_t ldp,
+                                                    const uint16_t *__restrict__ Q, int64_t ldq, int64_t Mrows,
+                                                    int64_t Ncols, int64_t K, int splits, GemmEpi e) {
+  gemm_nt_tile<EPI, T>(P, ldp, Q, ldq, Mrows, Ncols, K, splits, blockIdx.x, e);
+}
+
+// The weight gradients of all three layers, dW_l = dOutT_l InT_l^T, in one launch: block
+// ranges of the layers one after another, so the small products of a layer share the chip.
+template <class T>
+__global__ __launch_bounds__(T::NTHR) void k_wgrad(WgradBatch g, int64_t K, int splits) {
+  int l = 0;
+  while (l < 2 && (int64_t)blockIdx.x >= g.end[l]) ++l;
+  GemmEpi e = {};
+  e.out = g.out[l];
+  e.ldo = g.in[l];
+  gemm_nt_tile<EPI_PARTIAL, T>(g.dOutT[l], K, g.InT[l], K, g.rows[l], g.in[l], K, splits,
+                               blockIdx.x - (l ? g.end[l - 1] : 0), e);
 }
 
 // ---------------------------------------------------------------------------
@@ -150,60 +178,112 @@ __global__ __launch_bounds__(64) void k_prep_signals(const float *__restrict__ Y
 }
 
 // Zero-padded copy of B rows of a BF16 matrix into [Bp][cols]; row b is source
-// row rows[b] when `rows` is given.
+// row rows[b] when `rows` is given. With `sup` also the rows' multi-hot labels from
+// supports [.][S] (-1 padded; the same row map): bits [Bp][words], gathered in LDS.
 __global__ __launch_bounds__(256) void k_pad_rows16(const uint16_t *__restrict__ src, int64_t lds_,
                                                     const int32_t *__restrict__ rows, int64_t B, int64_t cols,
-                                                    uint16_t *__restrict__ dst) {
+                                                    uint16_t *__restrict__ dst, const int32_t *__restrict__ sup, int S,
+                                                    int64_t words, uint32_t *__restrict__ bits) {
+  extern __shared__ uint32_t lab[];
   const int64_t b = blockIdx.x;
   const int64_t sb = b < B ? (rows ? (int64_t)rows[b] : b) : 0;
-  for (int64_t c = threadIdx.x; c < cols; c += blockDim.x) dst[b * cols + c] = b < B ? src[sb * lds_ + c] : 0;
-}
-
-// Multi-hot labels from supports [.][S] (-1 padded; row rows[b] when given):
-// bits [Bp][n/32]. One wavefront per row; the atomics order nothing (OR).
-__global__ __launch_bounds__(64) void k_labels(const int32_t *__restrict__ sup, const int32_t *__restrict__ rows,
-                                               int64_t B, int S, int64_t words, uint32_t *__restrict__ bits) {
-  const int64_t b = blockIdx.x;
-  for (int64_t t = threadIdx.x; t < words; t += 64) bits[b * words + t] = 0u;
-  __syncthreads();
-  if (b >= B) return;
-  const int64_t sb = rows ? (int64_t)rows[b] : b;
-  for (int j = threadIdx.x; j < S; j += 64) {
-    const int n = sup[sb * S + j];
-    if (n >= 0 && n < words * 32) atomicOr(&bits[b * words + (n >> 5)], 1u << (n & 31));
+  const uint16_t *s = src + sb * lds_;
+  uint16_t *o = dst + b * cols;
+  if (((cols | lds_) & 7) == 0 && ((reinterpret_cast<uintptr_t>(src) | reinterpret_cast<uintptr_t>(dst)) & 15) == 0) {
+    for (int64_t c = threadIdx.x; c < cols / 8; c += blockDim.x)
+      reinterpret_cast<uint4 *>(o)[c] = b < B ? reinterpret_cast<const uint4 *>(s)[c] : make_uint4(0, 0, 0, 0);
+  } else {
+    for (int64_t c = threadIdx.x; c < cols; c += blockDim.x) o[c] = b < B ? s[c] : 0;
   }
-}
-
-// BF16 transpose dst[c][r] = src[r][c]; R and C multiples of 64.
-__global__ __launch_bounds__(256) void k_transpose16(const uint16_t *__restrict__ src, int64_t R, int64_t C,
-                                                     uint16_t *__restrict__ dst) {
-  __shared__ uint16_t t[64][66];
-  const int64_t tc = blockIdx.x % (C / 64), tr = blockIdx.x / (C / 64);
-  const int tx = threadIdx.x & 63, ty = threadIdx.x >> 6;
-  for (int i = ty; i < 64; i += 4) t[i][tx] = src[(tr * 64 + i) * C + tc * 64 + tx];
+  if (!sup) return;
+  for (int64_t t = threadIdx.x; t < words; t += blockDim.x) lab[t] = 0u;
   __syncthreads();
-  for (int i = ty; i < 64; i += 4) dst[(tc * 64 + i) * R + tr * 64 + tx] = t[tx][i];
+  if (b < B)
+    for (int j = threadIdx.x; j < S; j += blockDim.x) {
+      const int n = sup[sb * S + j];
+      if (n >= 0 && n < words * 32) atomicOr(&lab[n >> 5], 1u << (n & 31));
+    }
+  __syncthreads();
+  for (int64_t t = threadIdx.x; t < words; t += blockDim.x) bits[b * words + t] = lab[t];
 }
 
-// Column sums of a BF16 [R][C] matrix in row chunks: part[chunk][c].
-__global__ __launch_bounds__(256) void k_colsum16(const uint16_t *__restrict__ src, int64_t R, int64_t C,
-                                                  int64_t rows_per_chunk, float *__restrict__ part) {
-  const int64_t c = (int64_t)(blockIdx.x % (C / 256)) * 256 + threadIdx.x;
-  const int64_t chunk = blockIdx.x / (C / 256);
-  const int64_t r0 = chunk * rows_per_chunk, r1 = min(R, r0 + rows_per_chunk);
-  float s = 0.f;
-  for (int64_t r = r0; r < r1; ++r) s += bf16_to_f32(src[r * C + c]);
-  part[chunk * C + c] = s;
-}
-
-// Sum of the loss partials, in block order.
-__global__ __launch_bounds__(64) void k_loss_sum(const float *__restrict__ part, int64_t n, float scale,
-                                                 float *__restrict__ out) {
-  double s = 0.0;
-  for (int64_t i = threadIdx.x; i < n; i += 64) s += part[i];
+// BF16 transposes dst[c][r] = src[r][c] of all matrices of a batch (R rows, a multiple of
+// 64; C a multiple of 64) in one launch, and of the matrices with `part` the column sums
+// of every group of `rpc` rows (a multiple of 64): part[group][c]. A block takes 64 columns
+// of one group, 64 x 64 tiles through LDS, so the sums cost no pass of their own: 10 us
+// for a batch of 1024 on 1024-wide layers, where six transposes of 4.4 us and three column
+// sums of 16.5 us (64 threads' serial loads per column) took 75.
+__global__ __launch_bounds__(256) void k_transposes16(TransposeBatch g, int64_t R, int64_t rpc) {
+  __shared__ uint16_t t[64][72];
+  __shared__ float red[8][64];
+  int m = 0;
+  while (m < 5 && (int64_t)blockIdx.x >= g.end[m]) ++m;
+  const int64_t blk = blockIdx.x - (m ? g.end[m - 1] : 0), C = g.cols[m];
+  const int64_t tc = blk % (C / 64), grp = blk / (C / 64);
+  const int64_t r0 = grp * rpc, r1 = min(R, r0 + rpc);
+  const int tid = threadIdx.x;
+  float sum = 0.f;
+  for (int64_t r = r0; r < r1; r += 64) {
+    // 64 rows of 8 chunks of 16 bytes: two chunks per thread
 #pragma unroll
-  for (int off = 32; off >= 1; off >>= 1) s += __shfl_xor(s, off);
-  if (threadIdx.x == 0) out[0] = (float)(s * scale);
+    for (int q = 0; q < 2; ++q) {
+      const int f = tid + 256 * q, row = f >> 3, c8 = f & 7;
+      *reinterpret_cast<uint4 *>(&t[row][c8 * 8]) =
+          *reinterpret_cast<const uint4 *>(g.src[m] + (r + row) * C + tc * 64 + c8 * 8);
+    }
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+      const int f = tid + 256 * q, col = f & 63, r8 = f >> 6;  // eight rows of one column
+      uint16_t v[8];
+      float s8 = 0.f;
+#pragma unroll
+      for (int i = 0; i < 8; ++i) {
+        v[i] = t[r8 * 8 + i][col];
+        s8 += bf16_to_f32(v[i]);
+      }
+      red[r8][col] = s8;
+      uint4 o;
+      o.x = v[0] | ((uint32_t)v[1] << 16);
+      o.y = v[2] | ((uint32_t)v[3] << 16);
+      o.z = v[4] | ((uint32_t)v[5] << 16);
+      o.w = v[6] | ((uint32_t)v[7] << 16);
+      *reinterpret_cast<uint4 *>(g.dst[m] + (tc * 64 + col) * R + r + r8 * 8) = o;
+    }
+    __syncthreads();
+    if (g.part[m] && tid < 64) {
+#pragma unroll
+      for (int i = 0; i < 8; ++i) sum += red[i][tid];
+    }
+  }
+  if (g.part[m] && tid < 64) g.part[m][grp * C + tc * 64 + tid] = sum;
+}
+
+// The sums that end a gradient, in one launch: block 0 adds the loss partials in block
+// order, the others the split or group partials of up to six arrays.
+__global__ __launch_bounds__(256) void k_grad_sums(SumBatch g, const float *__restrict__ loss_part, int64_t nloss,
+                                                   float scale, float *__restrict__ loss_out) {
+  if (blockIdx.x == 0) {
+    if (threadIdx.x >= 64 || !loss_out) return;
+    double s = 0.0;
+    for (int64_t i = threadIdx.x; i < nloss; i += 64) s += loss_part[i];
+#pragma unroll
+    for (int off = 32; off >= 1; off >>= 1) s += __shfl_xor(s, off);
+    if (threadIdx.x == 0) loss_out[0] = (float)(s * scale);
+    return;
+  }
+  const int64_t blk = blockIdx.x - 1;
+  int m = 0;
+  while (m < 5 && blk >= g.end[m]) ++m;
+  const int64_t i = (blk - (m ? g.end[m - 1] : 0)) * 256 + threadIdx.x;
+  if (i >= g.n[m]) return;
+  float v[16];
+#pragma unroll
+  for (int s = 0; s < 16; ++s) v[s] = s < g.parts[m] ? g.part[m][(int64_t)s * g.n[m] + i] : 0.f;
+  float sum = 0.f;
+#pragma unroll
+  for (int s = 0; s < 16; ++s) sum += v[s];
+  g.out[m][i] = sum;
 }
 
 // ---------------------------------------------------------------------------
@@ -250,16 +330,6 @@ __global__ __launch_bounds__(256) void k_adam_b(LayerView L, const float *__rest
   L.mb[o] = m;
   L.vb[o] = v;
   L.b32[o] -= lr * (m * c1) / (sqrtf(v * c2) + eps);
-}
-
-// Gradient export: sum the partials into a dense FP32 array.
-__global__ __launch_bounds__(256) void k_sum_parts(const float *__restrict__ part, int parts, int64_t n,
-                                                   float *__restrict__ out) {
-  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (i >= n) return;
-  float g = 0.f;
-  for (int s = 0; s < parts; ++s) g += part[(int64_t)s * n + i];
-  out[i] = g;
 }
 
 // Plain FP32 copies and zero fills (kernels, so that captured graphs hold no memset).
@@ -573,7 +643,8 @@ hipError_t lds_limit(K kernel, size_t bytes) {
 // Tile size of an M x N product with `splits` slices of K: the largest that still gives
 // the 256 CUs about one workgroup each (a workgroup of the larger tiles fills a CU).
 // Measured: 16384 x 1024 x 1024 with bias and ReLU 47 us on 128 x 128 tiles, 39 us on
-// 256 x 256; 1024 x 1024 x 1024 14.9 us on 128 x 128 (64 workgroups), 11.6 us on 64 x 64.
+// 256 x 256; 1024 x 1024 x 1024 14.9 us on 128 x 128 (64 workgroups), 11.6 us on 64 x 64
+// with two LDS buffers and 9.5 us with four (64 MB through L2 at 7 TB/s).
 int gemm_tile(int64_t M, int64_t N, int splits) {
   const int64_t t256 = (M / 256) * (N / 256) * splits;
   if (M % 256 == 0 && N % 256 == 0 && t256 >= 192) return 256;
@@ -583,10 +654,10 @@ int gemm_tile(int64_t M, int64_t N, int splits) {
 template <int EPI, class T>
 hipError_t gemm_t(const uint16_t *P, int64_t ldp, const uint16_t *Q, int64_t ldq, int64_t M, int64_t N, int64_t K,
                   int splits, const GemmEpi &e, hipStream_t st) {
-  hipError_t err = lds_limit(k_gemm_nt<EPI, T>, T::LDS_BYTES);
+  hipError_t err = lds_limit(k_gemm_nt<EPI, T>, gemm_lds<T>());
   if (err != hipSuccess) return err;
   const unsigned grid = (unsigned)((M / T::TN) * (N / T::TB) * splits);
-  hipLaunchKernelGGL((k_gemm_nt<EPI, T>), dim3(grid), dim3(T::NTHR), T::LDS_BYTES, st, P, ldp, Q, ldq, M, N, K, splits,
+  hipLaunchKernelGGL((k_gemm_nt<EPI, T>), dim3(grid), dim3(T::NTHR), gemm_lds<T>(), st, P, ldp, Q, ldq, M, N, K, splits,
                      e);
   return hipGetLastError();
 }
@@ -628,30 +699,79 @@ hipError_t launch_prep_signals(const float *Y, int64_t ldy, int64_t B, int64_t M
 }
 
 hipError_t launch_pad_rows16(const uint16_t *src, int64_t ld, const int32_t *rows, int64_t B, int64_t cols,
-                             int64_t Bp, uint16_t *dst, hipStream_t st) {
-  hipLaunchKernelGGL(k_pad_rows16, dim3((unsigned)Bp), dim3(256), 0, st, src, ld, rows, B, cols, dst);
+                             int64_t Bp, uint16_t *dst, hipStream_t st, const int32_t *sup, int S, int64_t n_out,
+                             uint32_t *bits) {
+  const size_t lds = sup ? (size_t)(n_out / 32) * 4 : 0;  // at most 2 KiB (n_out <= 16384)
+  hipLaunchKernelGGL(k_pad_rows16, dim3((unsigned)Bp), dim3(256), lds, st, src, ld, rows, B, cols, dst, sup, S,
+                     n_out / 32, bits);
   return hipGetLastError();
 }
 
-hipError_t launch_labels(const int32_t *sup, const int32_t *rows, int64_t B, int S, int64_t n_out, int64_t Bp,
-                         uint32_t *bits, hipStream_t st) {
-  hipLaunchKernelGGL(k_labels, dim3((unsigned)Bp), dim3(64), 0, st, sup, rows, B, S, n_out / 32, bits);
+int64_t transpose_rows(int64_t R) {
+  const int64_t per = (R + COLSUM_GROUPS - 1) / COLSUM_GROUPS;
+  return (per + 63) / 64 * 64;
+}
+
+hipError_t launch_transposes16(TransposeBatch g, int64_t R, hipStream_t st) {
+  if (R % 64) return hipErrorInvalidValue;
+  const int64_t rpc = transpose_rows(R), groups = (R + rpc - 1) / rpc;
+  int64_t blocks = 0;
+  for (int m = 0; m < 6; ++m) {
+    if (g.cols[m] % 64) return hipErrorInvalidValue;
+    blocks += g.cols[m] / 64 * groups;
+    g.end[m] = blocks;
+  }
+  hipLaunchKernelGGL(k_transposes16, dim3((unsigned)blocks), dim3(256), 0, st, g, R, rpc);
   return hipGetLastError();
 }
 
-hipError_t launch_transpose16(const uint16_t *src, int64_t R, int64_t C, uint16_t *dst, hipStream_t st) {
-  hipLaunchKernelGGL(k_transpose16, dim3((unsigned)((R / 64) * (C / 64))), dim3(256), 0, st, src, R, C, dst);
+namespace {
+template <class T>
+hipError_t wgrad_t(WgradBatch g, int64_t K, int splits, hipStream_t st) {
+  hipError_t err = lds_limit(k_wgrad<T>, gemm_lds<T>());
+  if (err != hipSuccess) return err;
+  int64_t blocks = 0;
+  for (int l = 0; l < 3; ++l) {
+    blocks += (g.rows[l] / T::TN) * (g.in[l] / T::TB) * splits;
+    g.end[l] = blocks;
+  }
+  hipLaunchKernelGGL(k_wgrad<T>, dim3((unsigned)blocks), dim3(T::NTHR), gemm_lds<T>(), st, g, K, splits);
   return hipGetLastError();
 }
 
-hipError_t launch_colsum16(const uint16_t *src, int64_t R, int64_t C, int chunks, float *part, hipStream_t st) {
-  const int64_t rpc = (R + chunks - 1) / chunks;
-  hipLaunchKernelGGL(k_colsum16, dim3((unsigned)((C / 256) * chunks)), dim3(256), 0, st, src, R, C, rpc, part);
-  return hipGetLastError();
+// 128 x 128 tiles of the three layers together, or 64 x 64 ones where those are too few
+int64_t wgrad_area(const WgradBatch &g) { return g.rows[0] * g.in[0] + g.rows[1] * g.in[1] + g.rows[2] * g.in[2]; }
+}  // namespace
+
+// The batch is split over up to WSPLITS_MAX workgroups per tile only where the 64 x 64
+// tiles of the three layers together leave CUs idle: every split writes and reads the
+// whole gradient once more (four of them moved 108 MB for 1024-wide layers, where the
+// products themselves read 25 MB: products and sums 61 us, without the split 18 us).
+int wgrad_splits(const WgradBatch &g, int64_t K) {
+  int sp = 1;
+  while (sp < WSPLITS_MAX && wgrad_area(g) / 4096 * sp < 256 && K % (128 * sp) == 0) sp *= 2;
+  return sp;
 }
 
-hipError_t launch_loss_sum(const float *part, int64_t n, float scale, float *out, hipStream_t st) {
-  hipLaunchKernelGGL(k_loss_sum, dim3(1), dim3(64), 0, st, part, n, scale, out);
+hipError_t launch_wgrad(const WgradBatch &g, int64_t K, int splits, hipStream_t st) {
+  for (int l = 0; l < 3; ++l)
+    if (g.rows[l] % 128 || g.in[l] % 128) return hipErrorInvalidValue;
+  if (K % (64 * splits)) return hipErrorInvalidValue;
+  return wgrad_area(g) / 16384 * splits >= 512 ? wgrad_t<GT128>(g, K, splits, st) : wgrad_t<GT64>(g, K, splits, st);
+}
+
+hipError_t launch_grad_sums(SumBatch g, const float *loss_part, int64_t nloss, float scale, float *loss_out,
+                            hipStream_t st) {
+  int64_t blocks = 0;
+  for (int m = 0; m < 6; ++m) {
+    if (g.parts[m] > 16) return hipErrorInvalidValue;
+    if (!g.out[m]) g.n[m] = 0;
+    blocks += (g.n[m] + 255) / 256;
+    g.end[m] = blocks;
+  }
+  if (blocks == 0 && !loss_out) return hipSuccess;
+  hipLaunchKernelGGL(k_grad_sums, dim3((unsigned)(blocks + 1)), dim3(256), 0, st, g, loss_part, nloss, scale,
+                     loss_out);
   return hipGetLastError();
 }
 
@@ -666,11 +786,6 @@ hipError_t launch_adam_b(const LayerView &L, const float *gpart, int chunks, flo
                          float c1, float c2, hipStream_t st) {
   hipLaunchKernelGGL(k_adam_b, dim3((unsigned)((L.n_out + 255) / 256)), dim3(256), 0, st, L, gpart, chunks, lr, b1,
                      b2, eps, c1, c2);
-  return hipGetLastError();
-}
-
-hipError_t launch_sum_parts(const float *part, int parts, int64_t n, float *out, hipStream_t st) {
-  hipLaunchKernelGGL(k_sum_parts, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, part, parts, n, out);
   return hipGetLastError();
 }
 

@@ -16,8 +16,6 @@ namespace bomp {
 namespace {
 
 constexpr uint32_t MLP_MAGIC = 0x4f4d4c50u;  // "OMLP"
-constexpr int WSPLITS = 4;                   // split of the batch reduction in the weight gradients
-constexpr int BCHUNKS = 16;                  // row chunks of the bias gradients
 constexpr float ADAM_B1 = 0.9f, ADAM_B2 = 0.999f, ADAM_EPS = 1e-8f;
 
 size_t al(size_t x) { return (x + WS_ALIGN - 1) / WS_ALIGN * WS_ALIGN; }
@@ -108,8 +106,8 @@ NetWork net_layout(int64_t ni, int64_t nh, int64_t no, int64_t M, int64_t B, cha
   for (int l = 0; l < 3; ++l) {
     int64_t in, out;
     layer_dims(ni, nh, no, l, &in, &out);
-    w.gW[l] = c.take<float>((size_t)WSPLITS * in * out);
-    w.gb[l] = c.take<float>((size_t)BCHUNKS * out);
+    w.gW[l] = c.take<float>((size_t)WSPLITS_MAX * in * out);
+    w.gb[l] = c.take<float>((size_t)COLSUM_GROUPS * out);
   }
   w.Y16 = c.take<uint16_t>(Bp * Mp);
   w.yinv = c.take<float>(Bp);
@@ -167,9 +165,11 @@ hipError_t forward(const Net &n, const NetWork &w, int64_t B, bool train, hipStr
   return launch_gemm_bf16(EPI_BCE, w.H2, n.nh, n.L[2].W16, n.nh, Bp, n.no, n.nh, 1, e, st);
 }
 
-// Backward pass after forward(train): dH2, dH1, the activation transposes and
-// the split partial sums of every gradient.
-hipError_t backward(const Net &n, const NetWork &w, hipStream_t st) {
+// Backward pass after forward(train): dH2, dH1, the activation transposes with the bias
+// gradients' group sums, and the weight gradients. With one split a weight gradient goes
+// straight to grads[l] where that is given; *splits and *groups tell how many partial sums
+// gW and gb hold.
+hipError_t backward(const Net &n, const NetWork &w, float *const grads[3], int *splits, int *groups, hipStream_t st) {
   const int64_t Bp = w.Bp;
   GemmEpi e = epi0();
   e.out = w.dH2;
@@ -181,23 +181,25 @@ hipError_t backward(const Net &n, const NetWork &w, hipStream_t st) {
   e.mask = w.H1;
   err = launch_gemm_bf16(EPI_RELU_MASK, w.dH2, n.nh, n.L[1].W16T, n.nh, Bp, n.nh, n.nh, 1, e, st);
   if (err != hipSuccess) return err;
-  const uint16_t *src[6] = {w.F, w.H1, w.H2, w.dZ, w.dH2, w.dH1};
-  uint16_t *dst[6] = {w.FT, w.H1T, w.H2T, w.dZT, w.dH2T, w.dH1T};
-  const int64_t cols[6] = {n.ni, n.nh, n.nh, n.no, n.nh, n.nh};
-  for (int i = 0; i < 6 && err == hipSuccess; ++i) err = launch_transpose16(src[i], Bp, cols[i], dst[i], st);
+  // db_l[o] = sum_b dOut[b][o], summed while dOut is transposed
+  const TransposeBatch t = {{w.F, w.H1, w.H2, w.dZ, w.dH2, w.dH1},
+                            {w.FT, w.H1T, w.H2T, w.dZT, w.dH2T, w.dH1T},
+                            {nullptr, nullptr, nullptr, w.gb[2], w.gb[1], w.gb[0]},
+                            {n.ni, n.nh, n.nh, n.no, n.nh, n.nh},
+                            {}};
+  err = launch_transposes16(t, Bp, st);
   if (err != hipSuccess) return err;
-  // dW_l[o][i] = sum_b dOut[b][o] In[b][i]; db_l[o] = sum_b dOut[b][o]
-  const uint16_t *dOutT[3] = {w.dH1T, w.dH2T, w.dZT};
-  const uint16_t *InT[3] = {w.FT, w.H1T, w.H2T};
-  const uint16_t *dOut[3] = {w.dH1, w.dH2, w.dZ};
-  for (int l = 0; l < 3 && err == hipSuccess; ++l) {
-    GemmEpi g = epi0();
-    g.out = w.gW[l];
-    g.ldo = n.L[l].n_in;
-    err = launch_gemm_bf16(EPI_PARTIAL, dOutT[l], Bp, InT[l], Bp, n.L[l].n_out, n.L[l].n_in, Bp, WSPLITS, g, st);
-    if (err == hipSuccess) err = launch_colsum16(dOut[l], Bp, n.L[l].n_out, BCHUNKS, w.gb[l], st);
+  const int64_t rpc = transpose_rows(Bp);
+  *groups = (int)((Bp + rpc - 1) / rpc);
+  // dW_l[o][i] = sum_b dOut[b][o] In[b][i]
+  WgradBatch g = {{w.dH1T, w.dH2T, w.dZT}, {w.FT, w.H1T, w.H2T}, {}, {}, {}, {}};
+  for (int l = 0; l < 3; ++l) {
+    g.rows[l] = n.L[l].n_out;
+    g.in[l] = n.L[l].n_in;
   }
-  return err;
+  *splits = wgrad_splits(g, Bp);
+  for (int l = 0; l < 3; ++l) g.out[l] = *splits == 1 && grads && grads[l] ? grads[l] : w.gW[l];
+  return launch_wgrad(g, Bp, *splits, st);
 }
 
 }  // namespace
@@ -314,8 +316,8 @@ int omp_mlp_forward(const omp_mlp_t *mlp, const uint16_t *F, int64_t B, float *Z
 
 static int grad_common(const omp_mlp_t *mlp, const uint16_t *F, const int32_t *support, const int32_t *rows,
                        int64_t B, int32_t S,
-                       float *loss_out, void *workspace, size_t workspace_bytes, hipStream_t st, Net *net,
-                       NetWork *nw) {
+                       float *const grads[3], void *workspace, size_t workspace_bytes, hipStream_t st, Net *net,
+                       NetWork *nw, int *splits, int *groups) {
   if (!mlp_ok(mlp) || B < 1 || B > ((int64_t)1 << 24) || S < 1 || S > mlp->n_out) return OMP_EINVAL;
   if (!F || !support || !aligned(F, 2) || !aligned(support, 4) || !aligned(rows, 4)) return OMP_EINVAL;
   const size_t need = net_layout(mlp->n_in, mlp->n_hidden, mlp->n_out, 0, B, nullptr).total;
@@ -326,12 +328,9 @@ static int grad_common(const omp_mlp_t *mlp, const uint16_t *F, const int32_t *s
   const Net &n = *net;
   *nw = net_layout(n.ni, n.nh, n.no, 0, B, static_cast<char *>(workspace));
   const NetWork &w = *nw;
-  hipError_t e = launch_pad_rows16(F, n.ni, rows, B, n.ni, w.Bp, w.F, st);
-  if (e == hipSuccess) e = launch_labels(support, rows, B, S, n.no, w.Bp, w.labels, st);
+  hipError_t e = launch_pad_rows16(F, n.ni, rows, B, n.ni, w.Bp, w.F, st, support, S, n.no, w.labels);
   if (e == hipSuccess) e = forward(n, w, B, true, st);
-  if (e == hipSuccess && loss_out)
-    e = launch_loss_sum(w.loss_part, gemm_blocks(w.Bp, n.no, 1), 1.f / (float)B, loss_out, st);
-  if (e == hipSuccess) e = backward(n, w, st);
+  if (e == hipSuccess) e = backward(n, w, grads, splits, groups, st);
   if (e != hipSuccess) return device_error(e);
   return OMP_OK;
 }
@@ -342,15 +341,24 @@ int omp_mlp_grad(const omp_mlp_t *mlp, const uint16_t *F, const int32_t *support
   hipStream_t st = static_cast<hipStream_t>(stream);
   Net n;
   NetWork w;
-  int rc = grad_common(mlp, F, support, rows, B, S, loss_out, workspace, workspace_bytes, st, &n, &w);
-  if (rc != OMP_OK || !grads_out) return rc;
-  hipError_t e = hipSuccess;
-  for (int l = 0; l < 3 && e == hipSuccess; ++l) {
-    if (grads_out[2 * l])
-      e = launch_sum_parts(w.gW[l], WSPLITS, n.L[l].n_in * n.L[l].n_out, grads_out[2 * l], st);
-    if (e == hipSuccess && grads_out[2 * l + 1])
-      e = launch_sum_parts(w.gb[l], BCHUNKS, n.L[l].n_out, grads_out[2 * l + 1], st);
+  int splits = 1, groups = 1;
+  float *direct[3] = {};
+  for (int l = 0; l < 3 && grads_out; ++l) direct[l] = grads_out[2 * l];
+  int rc = grad_common(mlp, F, support, rows, B, S, direct, workspace, workspace_bytes, st, &n, &w, &splits, &groups);
+  if (rc != OMP_OK) return rc;
+  SumBatch g;
+  std::memset(&g, 0, sizeof(g));
+  for (int l = 0; l < 3 && grads_out; ++l) {
+    g.part[l] = w.gW[l];
+    g.out[l] = splits > 1 ? grads_out[2 * l] : nullptr;
+    g.n[l] = n.L[l].n_in * n.L[l].n_out;
+    g.parts[l] = splits;
+    g.part[3 + l] = w.gb[l];
+    g.out[3 + l] = grads_out[2 * l + 1];
+    g.n[3 + l] = n.L[l].n_out;
+    g.parts[3 + l] = groups;
   }
+  hipError_t e = launch_grad_sums(g, w.loss_part, gemm_blocks(w.Bp, n.no, 1), 1.f / (float)B, loss_out, st);
   if (e != hipSuccess) return device_error(e);
   return OMP_OK;
 }
@@ -361,15 +369,18 @@ int omp_mlp_train_step(omp_mlp_t *mlp, const uint16_t *F, const int32_t *support
   hipStream_t st = static_cast<hipStream_t>(stream);
   Net n;
   NetWork w;
-  int rc = grad_common(mlp, F, support, rows, B, S, loss_out, workspace, workspace_bytes, st, &n, &w);
+  int splits = 1, groups = 1;
+  int rc = grad_common(mlp, F, support, rows, B, S, nullptr, workspace, workspace_bytes, st, &n, &w, &splits, &groups);
   if (rc != OMP_OK) return rc;
   const int64_t t = mlp->step + 1;
   const float c1 = (float)(1.0 / (1.0 - std::pow((double)ADAM_B1, (double)t)));
   const float c2 = (float)(1.0 / (1.0 - std::pow((double)ADAM_B2, (double)t)));
-  hipError_t e = hipSuccess;
+  SumBatch none;
+  std::memset(&none, 0, sizeof(none));
+  hipError_t e = launch_grad_sums(none, w.loss_part, gemm_blocks(w.Bp, n.no, 1), 1.f / (float)B, loss_out, st);
   for (int l = 0; l < 3 && e == hipSuccess; ++l) {
-    e = launch_adam_w(n.L[l], w.gW[l], WSPLITS, lr, ADAM_B1, ADAM_B2, ADAM_EPS, c1, c2, 1, st);
-    if (e == hipSuccess) e = launch_adam_b(n.L[l], w.gb[l], BCHUNKS, lr, ADAM_B1, ADAM_B2, ADAM_EPS, c1, c2, st);
+    e = launch_adam_w(n.L[l], w.gW[l], splits, lr, ADAM_B1, ADAM_B2, ADAM_EPS, c1, c2, 1, st);
+    if (e == hipSuccess) e = launch_adam_b(n.L[l], w.gb[l], groups, lr, ADAM_B1, ADAM_B2, ADAM_EPS, c1, c2, st);
   }
   if (e != hipSuccess) return device_error(e);
   mlp->step = t;

@@ -50,18 +50,44 @@ hipError_t launch_gemm_bf16(int epi, const uint16_t *P, int64_t ldp, const uint1
                             int64_t N, int64_t K, int splits, const GemmEpi &e, hipStream_t st);
 hipError_t launch_prep_signals(const float *Y, int64_t ldy, int64_t B, int64_t M, int64_t Mp, int64_t Bp,
                                uint16_t *Y16, float *yinv, hipStream_t st);
+// With `sup`: the rows' multi-hot labels into bits [Bp][n_out / 32] too.
 hipError_t launch_pad_rows16(const uint16_t *src, int64_t ld, const int32_t *rows, int64_t B, int64_t cols,
-                             int64_t Bp, uint16_t *dst, hipStream_t st);
-hipError_t launch_labels(const int32_t *sup, const int32_t *rows, int64_t B, int S, int64_t n_out, int64_t Bp,
-                         uint32_t *bits, hipStream_t st);
-hipError_t launch_transpose16(const uint16_t *src, int64_t R, int64_t C, uint16_t *dst, hipStream_t st);
-hipError_t launch_colsum16(const uint16_t *src, int64_t R, int64_t C, int chunks, float *part, hipStream_t st);
-hipError_t launch_loss_sum(const float *part, int64_t n, float scale, float *out, hipStream_t st);
+                             int64_t Bp, uint16_t *dst, hipStream_t st, const int32_t *sup = nullptr, int S = 0,
+                             int64_t n_out = 0, uint32_t *bits = nullptr);
+// Six transposes in one launch, with column sums per group of transpose_rows(R) rows where
+// `part` is set (at most COLSUM_GROUPS groups).
+constexpr int COLSUM_GROUPS = 16;
+struct TransposeBatch {
+  const uint16_t *src[6];  // [R][cols]
+  uint16_t *dst[6];        // [cols][R]
+  float *part[6];          // [groups][cols] or nullptr
+  int64_t cols[6], end[6];  // end: filled by the launcher
+};
+int64_t transpose_rows(int64_t R);
+hipError_t launch_transposes16(TransposeBatch g, int64_t R, hipStream_t st);
+// dW_l [rows][in] = dOutT_l [rows][K] InT_l [in][K]^T for the three layers; with `splits`
+// slices of K, out_l holds [splits][rows][in] partial sums.
+constexpr int WSPLITS_MAX = 4;
+struct WgradBatch {
+  const uint16_t *dOutT[3], *InT[3];
+  float *out[3];
+  int64_t rows[3], in[3], end[3];  // end: filled by the launcher
+};
+int wgrad_splits(const WgradBatch &g, int64_t K);
+hipError_t launch_wgrad(const WgradBatch &g, int64_t K, int splits, hipStream_t st);
+// out_m[i] = sum over parts_m (at most 16) of part_m[.][i] (out nullptr: left out), and the loss.
+struct SumBatch {
+  const float *part[6];
+  float *out[6];
+  int64_t n[6], end[6];  // end: filled by the launcher
+  int parts[6];
+};
+hipError_t launch_grad_sums(SumBatch g, const float *loss_part, int64_t nloss, float scale, float *loss_out,
+                            hipStream_t st);
 hipError_t launch_adam_w(const LayerView &L, const float *gpart, int splits, float lr, float b1, float b2, float eps,
                          float c1, float c2, int update, hipStream_t st);
 hipError_t launch_adam_b(const LayerView &L, const float *gpart, int chunks, float lr, float b1, float b2, float eps,
                          float c1, float c2, hipStream_t st);
-hipError_t launch_sum_parts(const float *part, int parts, int64_t n, float *out, hipStream_t st);
 hipError_t launch_copy32(const float *src, int64_t n, float *dst, hipStream_t st);
 hipError_t launch_topk(const float *Z, int64_t ldz, int64_t N, int64_t B, int S, int32_t *P, hipStream_t st);
 hipError_t launch_ls_check(const DictView &d, const float *Y, int64_t ldy, int64_t B, const int32_t *P, int S,

@@ -48,3 +48,31 @@ def test_proposal_and_check_at_the_edges(S, M, N):
     scale = np.maximum(np.abs(X[acc]), 1e-2 * np.abs(X[acc]).max(axis=1, keepdims=True))
     assert np.all(np.abs(out.coef.cpu().numpy()[acc] - X[acc]) <= 1e-4 * scale)
     assert np.allclose(out.rnorm.cpu().numpy()[acc], rn[acc], rtol=1e-4, atol=1e-6)
+
+
+@pytest.mark.parametrize("ni,nh,no,B", [(256, 512, 768, 1), (512, 256, 256, 700), (256, 256, 512, 1281),
+                                        (768, 256, 256, 2300)])
+def test_gradients_at_ragged_batches(ni, nh, no, B):
+    """Loss and gradients where the layers differ in size and the batch fills its row groups
+    and batch slices unevenly. Tolerances of the suite's gradient test: the same BF16 rounding
+    points on both sides, one flipped rounding moves an entry by 2^-8 of its largest term."""
+    torch = _torch()
+    from oracle import learned_oracle as lo
+    from paper_2407_06434_amd import omp, workloads
+    g = np.random.default_rng(ni + B)
+    p = workloads.mlp_init_params(ni, nh, no, seed=B)
+    F = lo.bf16_round(np.abs(g.normal(size=(B, ni))))
+    sup = np.argsort(g.random((B, no)), axis=1)[:, :9].astype(np.int32)
+    sup[0, 4:] = -1
+    dev = torch.device("cuda:0")
+    bits = (F.astype(np.float32).view(np.uint32) >> 16).astype(np.uint16).view(np.int16)
+    net = omp.MLP(p)
+    print(f"case gradients ni={ni} nh={nh} no={no} B={B}", flush=True)
+    loss, got = net.grad(torch.from_numpy(bits).to(dev), torch.from_numpy(sup).to(dev))
+    want_loss, want = lo.backward({k: v.astype(np.float64) for k, v in p.items()}, F, lo.multi_hot(sup, no),
+                                  lo.bf16_round)
+    assert abs(float(loss) - want_loss) <= 1e-3 * abs(want_loss)
+    for k in want:
+        e = got[k].cpu().numpy().astype(np.float64) - want[k]
+        assert np.abs(e).max() <= 1e-2 * np.abs(want[k]).max(), k
+        assert np.linalg.norm(e) <= 2e-3 * np.linalg.norm(want[k]), k
