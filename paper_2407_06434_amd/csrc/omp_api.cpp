@@ -68,6 +68,7 @@ struct WorkLayout {
   size_t Yp, R32, R16, part, mask, k, flags, pnorm, pdelta, Sb, epsb, sup, u, xh, V, P, Pk, D, P64, D64, V64, u64,
       rscale, rscale_next, total;
   int pchunks;
+  int gpanel, gkeys;  // Gram-domain select: by panels (else slices), and key slots per signal
 };
 
 WorkLayout work_layout(int64_t M, int64_t N, int64_t B, int S, int precision, int cfg, bool gram_dom = false,
@@ -84,15 +85,16 @@ WorkLayout work_layout(int64_t M, int64_t N, int64_t B, int S, int precision, in
   const size_t Bp = (size_t)L.Bp, Sz = (size_t)S;
   Carve c;
   L.Yp = c.take<float>(Bp * L.Mp);
-  L.R32 = c.take<float>(Bp * L.Mp);
+  L.R32 = gram_dom ? L.Yp : c.take<float>(Bp * L.Mp);  // Gram-domain form: y itself, there is no residual
   L.R16 = is_half(precision) ? c.take<uint16_t>(Bp * L.Mp) : 0;
   L.rscale = precision == OMP_PREC_FP16 ? c.take<float>(Bp) : 0;
   L.rscale_next = precision == OMP_PREC_FP16 ? c.take<float>(Bp) : 0;
-  // (the Gram-domain select writes GSLICE keys per signal, twice that with near-tie flagging)
-  // (the Gram-domain select writes GSLICE keys per signal, twice that with near-tie
-  // flagging; v0 two keys, the FP64 form two (score, index) pairs of doubles)
+  // (the Gram-domain select writes one key per signal and atom slice or panel, two with
+  // near-tie flagging; v0 two keys, the FP64 form two (score, index) pairs of doubles)
+  L.gpanel = gram_dom && gram_panels(B, L.Mp, L.Np, ties) ? 1 : 0;
+  L.gkeys = L.gpanel ? (int)(L.Np / GPANEL) : GSLICE;
   L.part = c.take<uint64_t>(Bp * (size_t)std::max<int64_t>((int64_t)L.ntile * L.g.keys_per_tile,
-                                                            gram_dom ? GSLICE * (ties ? 2 : 1) : 4));
+                                                            gram_dom ? L.gkeys * (ties ? 2 : 1) : 4));
   L.mask = c.take<uint32_t>(Bp * (L.Np / 32));
   L.k = c.take<int32_t>(Bp);
   L.flags = c.take<int32_t>(Bp);
@@ -311,6 +313,7 @@ WorkView work_view(void *mem, int64_t M, int64_t N, int64_t B, int S, int precis
   w.gram_fly = 0;
   w.refactor = 0;
   w.gram_dom = gram_dom ? 1 : 0;
+  w.gpanel = L.gpanel;
   const bool f64 = precision == OMP_PREC_FP64;
   w.P = L.P ? at<float>(mem, L.P) : nullptr;
   w.v0 = (v0 || f64) ? 1 : 0;
@@ -323,8 +326,8 @@ WorkView work_view(void *mem, int64_t M, int64_t N, int64_t B, int S, int precis
   w.Pk = L.pchunks > 1 ? at<float>(mem, L.Pk) : nullptr;
   w.flag_ties = ties ? 1 : 0;
   w.fuse_res = 0;
-  if (gram_dom) {  // one key (two with near-tie flagging) per (signal, atom slice) from the Gram-domain select
-    w.ntile = GSLICE;
+  if (gram_dom) {  // one key (two with near-tie flagging) per (signal, atom slice or panel) from the Gram-domain select
+    w.ntile = L.gkeys;
     w.ncand = ties ? 2 : 1;
   }
   return w;

@@ -103,6 +103,7 @@ struct WorkView {
   int gram_fly;   // 1: Gram rows of the picks computed from the atoms (ablation A2)
   int refactor;   // 1: the factor of A_S^T A_S rebuilt from the Gram at every step (ablation A3)
   int gram_dom;   // 1: Gram-domain form (correlations from P and G, no residual vectors)
+  int gpanel;     // Gram-domain form: 1: the select keeps panels of G in LDS (gram_panels)
   float *P;       // [Bp][Np] Gram-domain form: P = Y A^T, the correlations of y (else nullptr)
   float *Pk;      // [pchunks][Bp][Np] split-K partial products of P (pchunks > 1), else nullptr
   int pchunks;    // K chunks of the P product (1: no split)
@@ -120,6 +121,19 @@ struct WorkView {
 // Gram-domain select: the atoms are split into this many contiguous slices, one
 // per XCD, each giving one key per signal.
 constexpr int GSLICE = 8;
+
+// Whether the Gram-domain select keeps column panels of G (GPANEL columns, all Np rows) in
+// LDS instead of reading G through the caches: up to Np = 1024, where a panel fits (128
+// KiB), from 512 signals on. Whole solves, us, caches against panels: 64 x 256, S = 8: 106
+// and 94 at B = 512, 485 and 223 at B = 10,000; 256 x 1024, S = 32: 467 and 392 at B = 512,
+// 2876 and 1660 at B = 10,000. Panels of 16 columns for wider dictionaries lose (512 x
+// 2048, S = 32, B = 5000: 1857 against 2223), as every panel walks over all signals.
+// A panel gives a key per signal, and the keys must fit in the space of the residual copy
+// that this form does not keep, so that no workspace grows.
+constexpr int GPANEL = 32;
+inline bool gram_panels(int64_t B, int64_t Mp, int64_t Np, bool ties) {
+  return Np <= 1024 && B >= 512 && Np / GPANEL * 8 * (ties ? 2 : 1) <= 4 * Mp;
+}
 
 // K chunks of the Gram-domain form's product P = Y A^T on 128 x 128 tiles: split
 // until about 512 workgroups run, each chunk keeping at least 16 K slices of 32

@@ -39,6 +39,7 @@
 // update. V is kept packed (row i at offset i(i+1)/2), the packed storage of
 // Section 3.3, and is staged through LDS for the two triangular solves.
 
+#include <algorithm>
 #include <cmath>
 #include <cstring>
 #include <type_traits>
@@ -1455,6 +1456,12 @@ stop:
   stop_signal<SLOTS>(w, sv, b, stopfl, k, rn, lane);
 }
 
+// Key of atom n with correlation c (0: not a candidate), as the FP32 select writes it.
+__device__ inline uint64_t v0_key(float c, float iv, bool taken, int64_t n) {
+  return (iv > 0.f && !taken) ? ((uint64_t)__float_as_uint(fabsf(c) * iv) << 32) | (0xFFFFFFFFull - (uint64_t)n)
+                              : 0ull;
+}
+
 // ---------------------------------------------------------------------------
 // Gram-domain select (tall dictionaries; the Gram solver of Section 2.1): the
 // correlations of the current residual are c_n = P[b][n] - sum_j G[s_j][n] x_j
@@ -1546,6 +1553,168 @@ __global__ __launch_bounds__(64) void k_gram_select(DictView d, WorkView w) {
 }
 
 // ---------------------------------------------------------------------------
+// Gram-domain select with G kept in LDS (GPANEL rule in omp_internal.h): a workgroup
+// stages one panel of 32 columns of G, all Np rows of it (128 KiB at Np = 1024),
+// and walks through its share of the signals, so a row entry is read from LDS instead of
+// from the caches. k_gram_select is bound by those cache reads (4 N k bytes per signal and
+// step, 8.8 TB/s at 256 x 1024, B = 5000); here the same entries cost one LDS cycle per
+// signal and support row.
+//
+// A wavefront takes four signals at a time, 16 lanes and two atoms per lane each, so a
+// signal reads a whole row of the panel at once (four lanes per signal need fewer
+// instructions, but their 16-byte reads of rows at random meet in the same LDS banks:
+// counters gave four cycles per access instead of one, 31.5 us where this takes 18.3). The
+// lanes of a signal hold 16 of its (row, -x) pairs; a pair is broadcast to them by the row
+// broadcast of a DPP move. Addresses are wave-uniform bases plus constant lane offsets.
+// c_n accumulates in support order, the same FMAs as k_gram_select's. Panel p runs on XCD
+// p mod 8 whatever the signal group, so an XCD's L2 serves one eighth of G. One key per
+// (signal, panel).
+// Measured per step at 256 x 1024, S = 32, B = 5000: 37.0 -> 18.3 us, of which vector
+// instructions fill 10 and LDS reads 3.
+// ---------------------------------------------------------------------------
+constexpr int GP_WAVES = 16;
+
+// Lane T of each 16-lane row, to the row (DPP row broadcast).
+template <int T>
+__device__ inline int row_bcast(int v) {
+  return __builtin_amdgcn_update_dpp(0, v, 0x150 + T, 0xF, 0xF, true);
+}
+
+template <bool TIES>
+__global__ __launch_bounds__(64 * GP_WAVES) void k_gram_panel(DictView d, WorkView w, int panels, int64_t per) {
+  extern __shared__ float gp[];  // [Np][W]
+  constexpr int W = GPANEL, AW = W / 16;  // columns per panel, atoms per lane
+  static_assert(AW == 2, "a lane's atoms are one 8-byte read");
+  const int panel = blockIdx.x % panels;
+  // (b0 + 3 of a wavefront's last turn may pass B, not the workspace's padded Bp rows)
+  const int64_t lo = (int64_t)(blockIdx.x / panels) * per, hi = min(w.B, lo + per);
+  if (lo >= hi) return;
+  const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), l16 = lane & 15;
+  const int64_t Np = d.Np;
+  const int S = w.S;
+  {
+    constexpr int LPR = W / 4, RPI = 64 / LPR;  // lanes per row of the panel, rows per load
+    const float4 *G4 = reinterpret_cast<const float4 *>(d.G) + panel * LPR + lane % LPR;
+    for (int64_t r0 = wv * RPI; r0 < Np; r0 += GP_WAVES * RPI)
+      lds_load16(G4 + (r0 + lane / LPR) * (Np / 4), reinterpret_cast<float4 *>(gp) + r0 * LPR);
+  }
+  const int n0 = panel * W + l16 * AW;
+  float iv[AW];
+#pragma unroll
+  for (int a = 0; a < AW; ++a) iv[a] = d.inv_nu[n0 + a];
+  // constant lane offsets (bytes) from the first signal's rows of P, the mask and the pairs
+  const int sg = lane >> 4;
+  const uint32_t offP = (uint32_t)(sg * Np + n0) * 4u, offM = (uint32_t)(sg * (Np / 32) + n0 / 32) * 4u;
+  const uint32_t offS = (uint32_t)(sg * S + min(l16, S - 1)) * 4u, off0 = (uint32_t)(sg * S) * 4u;
+  auto at = [](auto *base, uint32_t off) {
+    return *reinterpret_cast<decltype(base)>(reinterpret_cast<const char *>(base) + off);
+  };
+
+  // What a step needs of the lane's signal, loaded one turn ahead.
+  struct Sig {
+    int fl, k, s, s0;
+    float x, c[AW];
+    uint32_t word;
+  };
+  auto load = [&](int64_t b0) {
+    Sig g;
+    g.fl = at((const int *)w.flags + b0, (uint32_t)sg * 4u);
+    g.k = at((const int *)w.k + b0, (uint32_t)sg * 4u);
+    const float2 t = at(reinterpret_cast<const float2 *>(w.P + b0 * Np), offP);
+    g.c[0] = t.x;
+    g.c[1] = t.y;
+    g.word = at((const uint32_t *)w.mask + b0 * (Np / 32), offM);
+    g.s0 = at((const int *)w.sup + b0 * S, off0);
+    g.s = at((const int *)w.sup + b0 * S, offS);
+    g.x = at((const float *)w.xh + b0 * S, offS);
+    return g;
+  };
+  int64_t b0 = lo + wv * 4;
+  Sig cur = {};
+  if (b0 < hi) cur = load(b0);
+  __builtin_amdgcn_s_waitcnt(0);  // this wavefront's part of the panel has landed ...
+  __syncthreads();                // ... and everyone's
+  const uint32_t lb = (uint32_t)l16 * AW * 4u;
+  for (; b0 < hi; b0 += 4 * GP_WAVES) {
+    Sig nxt = {};
+    if (b0 + 4 * GP_WAVES < hi) nxt = load(b0 + 4 * GP_WAVES);
+    const bool live = b0 + sg < hi && !(cur.fl & FLAG_DONE);
+    const int k = live ? cur.k : 0;
+    const int kmax = max(max(__builtin_amdgcn_readlane(k, 0), __builtin_amdgcn_readlane(k, 16)),
+                         max(__builtin_amdgcn_readlane(k, 32), __builtin_amdgcn_readlane(k, 48)));
+    float c[AW];
+#pragma unroll
+    for (int a = 0; a < AW; ++a) c[a] = cur.c[a];
+    const int s0 = k > 0 ? cur.s0 : 0;
+    for (int j0 = 0; j0 < kmax; j0 += 16) {
+      const int j = j0 + l16;
+      if (j0 > 0) {
+        const uint32_t o = (uint32_t)(sg * S + min(j, S - 1)) * 4u;
+        cur.s = at((const int *)w.sup + b0 * S, o);
+        cur.x = at((const float *)w.xh + b0 * S, o);
+      }
+      // past the support: the first row, times zero (row 0 of the panel when there is none)
+      const int so = (j < k ? cur.s : s0) * (W * 4);
+      const int nx = __float_as_int(j < k ? -cur.x : 0.f);
+      auto rows = [&](auto q4) {
+        constexpr int q = decltype(q4)::value;
+        const uint32_t o[4] = {(uint32_t)row_bcast<q>(so) + lb, (uint32_t)row_bcast<q + 1>(so) + lb,
+                               (uint32_t)row_bcast<q + 2>(so) + lb, (uint32_t)row_bcast<q + 3>(so) + lb};
+        const float xj[4] = {__int_as_float(row_bcast<q>(nx)), __int_as_float(row_bcast<q + 1>(nx)),
+                             __int_as_float(row_bcast<q + 2>(nx)), __int_as_float(row_bcast<q + 3>(nx))};
+        float v[4][AW];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+          const float2 t = *reinterpret_cast<const float2 *>(reinterpret_cast<const char *>(gp) + o[u]);
+          v[u][0] = t.x;
+          v[u][1] = t.y;
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+#pragma unroll
+          for (int a = 0; a < AW; ++a) c[a] = fmaf(v[u][a], xj[u], c[a]);
+      };
+      rows(std::integral_constant<int, 0>());
+      if (j0 + 4 < kmax) rows(std::integral_constant<int, 4>());
+      if (j0 + 8 < kmax) rows(std::integral_constant<int, 8>());
+      if (j0 + 12 < kmax) rows(std::integral_constant<int, 12>());
+    }
+    if constexpr (TIES) {
+      uint64_t best = 0, sec = 0;
+#pragma unroll
+      for (int a = 0; a < AW; ++a) {
+        const uint64_t key = v0_key(c[a], iv[a], (cur.word >> ((n0 + a) & 31)) & 1u, n0 + a);
+        sec = max(sec, min(best, key));
+        best = max(best, key);
+      }
+      const uint64_t top = row_max(best);
+      sec = row_max(best == top ? sec : best);  // keys are distinct
+      if (live && l16 == 0) {
+        uint64_t *dst = w.part + ((b0 + sg) * panels + panel) * 2;
+        dst[0] = top;
+        dst[1] = sec;
+      }
+    } else {
+      // the row's largest score (bits + 1, 0: not a candidate), then the lowest atom that has it
+      uint32_t sb[AW], m = 0;
+#pragma unroll
+      for (int a = 0; a < AW; ++a) {
+        const bool cand = iv[a] > 0.f && !((cur.word >> ((n0 + a) & 31)) & 1u);
+        sb[a] = cand ? __float_as_uint(fabsf(c[a]) * iv[a]) + 1u : 0u;
+        m = max(m, sb[a]);
+      }
+      m = row_max32(m);
+      uint32_t n = 0;  // complement of the atom: the largest is the lowest atom
+#pragma unroll
+      for (int a = AW - 1; a >= 0; --a) n = sb[a] == m ? ~(uint32_t)(n0 + a) : n;
+      n = row_max32(n);
+      if (live && l16 == 0) w.part[(b0 + sg) * panels + panel] = m ? ((uint64_t)(m - 1u) << 32) | n : 0ull;
+    }
+    cur = nxt;
+  }
+}
+
+// ---------------------------------------------------------------------------
 // Algorithm v0 of the paper (Section 2.3): the inverse Cholesky factor
 // F_k = V_k^{-T} (upper triangular) and D_k = A^T A_k F_k = A^T Q_k, Q_k = A_k F_k
 // having orthonormal columns. No correlation product and no residual vectors:
@@ -1575,12 +1744,6 @@ __device__ inline uint64_t block_max(uint64_t v, uint64_t *red) {
   for (int i = 1; i < V0_THREADS / 64; ++i) m = red[i] > m ? red[i] : m;
   __syncthreads();
   return m;
-}
-
-// Key of atom n with correlation c (0: not a candidate), as the FP32 select writes it.
-__device__ inline uint64_t v0_key(float c, float iv, bool taken, int64_t n) {
-  return (iv > 0.f && !taken) ? ((uint64_t)__float_as_uint(fabsf(c) * iv) << 32) | (0xFFFFFFFFull - (uint64_t)n)
-                              : 0ull;
 }
 
 // The block's best and second best keys (threads hold their own best and second),
@@ -2302,11 +2465,33 @@ hipError_t launch_residual_lp(const DictView &d, const WorkView &w, int precisio
   return hipGetLastError();
 }
 
+namespace {
+template <bool TIES>
+hipError_t launch_gram_panel(const DictView &d, const WorkView &w, hipStream_t st) {
+  const size_t lds = (size_t)d.Np * GPANEL * 4;
+  hipError_t e = allow_lds(k_gram_panel<TIES>, lds);
+  if (e != hipSuccess) return e;
+  // Signal groups: one workgroup per CU, two where two panels fit, none with fewer than 64
+  // signals (one turn of its wavefronts).
+  const int panels = w.ntile;
+  const int64_t slots = 256 * (lds <= LDS_LIMIT / 2 ? 2 : 1);
+  int64_t groups = std::max<int64_t>(1, std::min<int64_t>((w.B + 63) / 64, slots / panels));
+  const int64_t per = ((w.B + groups - 1) / groups + 15) / 16 * 16;
+  groups = (w.B + per - 1) / per;
+  hipLaunchKernelGGL((k_gram_panel<TIES>), dim3((unsigned)(panels * groups)), dim3(64 * GP_WAVES), lds, st, d, w,
+                     panels, per);
+  return hipGetLastError();
+}
+}  // namespace
+
 hipError_t launch_gram_select(const DictView &d, const WorkView &w, hipStream_t st) {
-  if (!w.gram_dom || !w.P || w.ntile != GSLICE || (w.ncand != 1 && w.ncand != 2) || w.R16 || w.Np != d.Np ||
-      w.S > OMP_MAX_S ||
-      d.Np % (32 * GSLICE))
+  if (!w.gram_dom || !w.P || (w.ncand != 1 && w.ncand != 2) || w.R16 || w.Np != d.Np || w.S > OMP_MAX_S)
     return hipErrorInvalidValue;
+  if (w.gpanel) {
+    if (w.ntile * GPANEL != d.Np || (size_t)d.Np * GPANEL * 4 > LDS_LIMIT) return hipErrorInvalidValue;
+    return w.ncand == 2 ? launch_gram_panel<true>(d, w, st) : launch_gram_panel<false>(d, w, st);
+  }
+  if (w.ntile != GSLICE || d.Np % (32 * GSLICE)) return hipErrorInvalidValue;
   hipLaunchKernelGGL(k_gram_select, dim3((unsigned)(w.B * GSLICE)), dim3(64), 0, st, d, w);
   return hipGetLastError();
 }

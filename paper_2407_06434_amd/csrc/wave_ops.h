@@ -46,7 +46,8 @@ __device__ inline double wave_sum(double v) {
   return (r0 + r1) + (r2 + r3);
 }
 
-__device__ inline uint64_t wave_max(uint64_t v) {
+// Maximum over each 16-lane row, to every lane of the row.
+__device__ inline uint64_t row_max(uint64_t v) {
   uint64_t w = dpp64<DPP_XOR1>(v);
   v = w > v ? w : v;
   w = dpp64<DPP_XOR2>(v);
@@ -54,7 +55,11 @@ __device__ inline uint64_t wave_max(uint64_t v) {
   w = dpp64<DPP_HALF_MIRROR>(v);
   v = w > v ? w : v;
   w = dpp64<DPP_MIRROR>(v);
-  v = w > v ? w : v;
+  return w > v ? w : v;
+}
+
+__device__ inline uint64_t wave_max(uint64_t v) {
+  v = row_max(v);
   uint64_t m = readlane64(v, 0);
 #pragma unroll
   for (int r = 16; r < 64; r += 16) {
@@ -74,11 +79,15 @@ __device__ inline double sum8(double v) {
   return __longlong_as_double((long long)readlane64((uint64_t)__double_as_longlong(v), 0));
 }
 
+__device__ inline uint32_t row_max32(uint32_t v) {
+  v = max(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, DPP_XOR1, 0xF, 0xF, true));
+  v = max(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, DPP_XOR2, 0xF, 0xF, true));
+  v = max(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, DPP_HALF_MIRROR, 0xF, 0xF, true));
+  return max(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, DPP_MIRROR, 0xF, 0xF, true));
+}
+
 __device__ inline uint32_t wave_max32(uint32_t v) {
-  v = max(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, DPP_XOR1, 0xF, 0xF, false));
-  v = max(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, DPP_XOR2, 0xF, 0xF, false));
-  v = max(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, DPP_HALF_MIRROR, 0xF, 0xF, false));
-  v = max(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, DPP_MIRROR, 0xF, 0xF, false));
+  v = row_max32(v);
   const uint32_t a = max((uint32_t)__builtin_amdgcn_readlane((int)v, 0), (uint32_t)__builtin_amdgcn_readlane((int)v, 16));
   const uint32_t b = max((uint32_t)__builtin_amdgcn_readlane((int)v, 32), (uint32_t)__builtin_amdgcn_readlane((int)v, 48));
   return max(a, b);
