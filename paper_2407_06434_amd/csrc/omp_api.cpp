@@ -283,6 +283,7 @@ WorkView work_view(void *mem, int64_t M, int64_t N, int64_t B, int S, int precis
   w.tile_cfg = L.g.cfg;
   w.ntile = L.ntile;
   w.ncand = L.g.keys_per_tile;
+  w.ncand_inv = (uint32_t)((((uint64_t)1 << 32) + (uint64_t)w.ncand - 1) / (uint64_t)w.ncand);
   w.tile_atoms = L.g.tile_atoms;
   w.wave_atoms = L.g.wave_atoms;
   w.sub_frags = L.g.sub_frags;
@@ -470,6 +471,16 @@ int solve_impl(const float *A, int64_t M, int64_t N, int64_t lda, const float *Y
   // ---- enqueue ----
   hipStream_t st = static_cast<hipStream_t>(stream);
   PhaseTimer timer(opts->phase_ms, opts->phase_launches, st);
+  // Small batches: all steps in one launch (a timed call reports every phase, so it runs
+  // step by step, as does a call that names a tile configuration).
+  bool loop = false;
+  if (!timer.on() && cfg == 0) {
+    const DictView dv = dict_view(opts->dict ? opts->dict->mem : static_cast<char *>(workspace) + wneed, M, N, prec);
+    WorkView wv = work_view(workspace, M, N, B, S, prec, cfg, gdom, ties, v0);
+    wv.gram_fly = opts->gram_on_the_fly;
+    wv.refactor = opts->refactor;
+    loop = solve_loop_signals(dv, wv, prec) > 0;
+  }
   // Everything the solve launches, on stream `cs`, each launch through the timer.
   auto enqueue = [&](hipStream_t cs) -> hipError_t {
     DictView d;
@@ -511,7 +522,8 @@ int solve_impl(const float *A, int64_t M, int64_t N, int64_t lda, const float *Y
     } else if (gdom && e == hipSuccess) {
       e = timer.run(OMP_PHASE_INIT, [&] { return launch_project(d, w, cs); });
     }
-    for (int it = 0; it < S && e == hipSuccess && !v0; ++it) {
+    if (loop && e == hipSuccess) e = launch_solve_loop(d, w, prec, cs);
+    for (int it = 0; it < S && e == hipSuccess && !v0 && !loop; ++it) {
       if (gdom) {
         // Gram-domain form: correlations from P and G; no residual vectors
         e = timer.run(OMP_PHASE_CORR, [&] { return launch_gram_select(d, w, cs); });
@@ -533,7 +545,7 @@ int solve_impl(const float *A, int64_t M, int64_t N, int64_t lda, const float *Y
 
   hipError_t e = hipSuccess;
   bool done = false;
-  if (!direct && opts->use_graph && !timer.on()) {
+  if (!direct && opts->use_graph && !timer.on() && !loop) {  // (three launches need no graph)
     // The whole solve replayed from a hipGraph cached under every argument. On
     // the first use the launches are captured. (A timed call launches directly:
     // events recorded by graph nodes cannot be read back with elapsed times.)

@@ -74,6 +74,7 @@ struct WorkView {
   int tile_cfg;      // correlation tile configuration (CorrGeom::cfg)
   int ntile;         // number of atom tiles of the correlation product
   int ncand;         // keys per (signal, tile) written by the select epilogue
+  uint32_t ncand_inv; // 2^32 / ncand rounded up: t / ncand = umulhi(t, ncand_inv) for t < 2^27
   int tile_atoms;    // atoms per tile
   int wave_atoms;    // atom stride between the wavefront rows of a tile (FN * 32)
   int sub_frags;     // BF16 form: 32-row fragments per subgroup
@@ -244,6 +245,10 @@ hipError_t launch_project(const DictView &d, const WorkView &w, hipStream_t st);
 hipError_t launch_gram_select(const DictView &d, const WorkView &w, hipStream_t st);
 // One OMP step per live signal: stop test, pick, Cholesky append, both solves.
 hipError_t launch_solve(const DictView &d, const WorkView &w, int precision, hipStream_t st);
+// All steps of a small batch in one launch (forms its own residuals); signals per workgroup,
+// 0 where it is not used.
+int solve_loop_signals(const DictView &d, const WorkView &w, int precision);
+hipError_t launch_solve_loop(const DictView &d, const WorkView &w, int precision, hipStream_t st);
 // Whether the solve holds the residual in registers (its own variant, which does not fuse the residual).
 bool solve_rr(const DictView &d, const WorkView &w);
 bool residual_in_solve(const DictView &d, int64_t B);

@@ -45,6 +45,7 @@
 #include <type_traits>
 
 #include "../../include/batched_omp.h"
+#include "mfma_tile.h"
 #include "omp_internal.h"
 #include "wave_ops.h"
 
@@ -359,8 +360,6 @@ __device__ __attribute__((always_inline)) inline void atom_dots_reg(const DictVi
   for (int i = 0; i < NA; ++i) av[i] = wave_sum(av[i]);
 }
 
-typedef __attribute__((address_space(3))) void lds_void_t;
-
 // Asynchronous global-to-LDS loads (gfx950 global_load_lds): lane l's element
 // lands at dst + l (lane order), dst being wave-uniform. Completion is awaited
 // with s_waitcnt before the LDS data is read.
@@ -481,11 +480,11 @@ __device__ inline int key_loc(uint32_t key) { return 31 - (int)(key & 31u); }
 // ig) * 2 + h) within it) at place loc = ii * 16 + r: the epilogue's row
 // 8 (r / 4) + 4 h + r % 4 of fragment ig * sub_frags + ii of wavefront row wn.
 __device__ inline int key_atom(const WorkView &w, int t, int loc) {
-  const int tile = t / w.ncand;
-  const int sgl = (t % w.ncand) / NKEEP;
+  const int tile = (int)__umulhi((uint32_t)t, w.ncand_inv);
+  const int sgl = (t - tile * w.ncand) / NKEEP;
   const int hh = sgl & 1;
-  const int ig = (sgl >> 1) % w.subs_per_half;
-  const int wn = (sgl >> 1) / w.subs_per_half;
+  const int ig = (sgl >> 1) & (w.subs_per_half - 1);  // one or two subgroups per half
+  const int wn = (sgl >> 1) >> (w.subs_per_half >> 1);
   const int ii = loc >> 4, r = loc & 15;
   return tile * w.tile_atoms + wn * w.wave_atoms + 32 * (ig * w.sub_frags + ii) + 8 * (r >> 2) + 4 * hh + (r & 3);
 }
@@ -961,15 +960,12 @@ __device__ inline void stop_signal(const WorkView &w, const SlotView &sv, int64_
 // pick; SLOTS: the slot scheduler's retire and admit; RR: the residual is held
 // in registers (512 < M <= 1024); RRF: that variant also forms the next residual
 // (a variant of its own, so that the one that does not keeps its registers).
-template <int RPL, bool BF16, bool SLOTS, bool RR, bool RRF = false>
-__global__ __launch_bounds__(64 * SOLVE_WAVES) void k_solve(DictView d, WorkView w, SlotView sv) {
-  extern __shared__ float smem[];
-  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-  const int64_t b = (int64_t)blockIdx.x * (blockDim.x >> 6) + wv;  // blocks of solve_waves(w) wavefronts
-  if (b >= w.B) return;
+// One step of signal b by the calling wavefront; Vs: its LDS region (solve_lds_per_wave).
+template <int RPL, bool BF16, bool SLOTS, bool RR, bool RRF>
+__device__ __attribute__((always_inline)) inline void solve_step(const DictView &d, const WorkView &w,
+                                                                 const SlotView &sv, int64_t b, int lane, float *Vs) {
   const int S = w.S;
   const int64_t VS = w.vstride;
-  float *Vs = smem + (size_t)wv * (VS + solve_list_len(w));
   int *clist = reinterpret_cast<int *>(Vs + VS);  // BF16 pick: candidate list (one entry per key at most)
 
   // ---- memory round 1: state, residual norms, keys, support, u and (RR) the
@@ -1454,6 +1450,248 @@ stop:
   // atom left) must not leave them writing this block's LDS after it ends.
   __builtin_amdgcn_s_waitcnt(0);
   stop_signal<SLOTS>(w, sv, b, stopfl, k, rn, lane);
+}
+
+template <int RPL, bool BF16, bool SLOTS, bool RR, bool RRF = false>
+__global__ __launch_bounds__(64 * SOLVE_WAVES) void k_solve(DictView d, WorkView w, SlotView sv) {
+  extern __shared__ float smem[];
+  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+  const int64_t b = (int64_t)blockIdx.x * (blockDim.x >> 6) + wv;  // blocks of solve_waves(w) wavefronts
+  if (b >= w.B) return;
+  solve_step<RPL, BF16, SLOTS, RR, RRF>(d, w, sv, b, lane, smem + (size_t)wv * (w.vstride + solve_list_len(w)));
+}
+
+// ---------------------------------------------------------------------------
+// Whole solve in one launch, for small batches (solve_loop_signals gives the rule). A
+// small step is all latency: two launches of 7 to 15 us each that keep a few CUs busy,
+// with their state read back from beyond the L2s. Here a workgroup of eight wavefronts
+// keeps G <= 8 signals to itself and runs all their steps: the product of its signals with
+// every atom, then solve_step, one wavefront per signal, with workgroup barriers between;
+// what one phase leaves for the next stays in the CU's caches.
+//
+// Product: atoms in units of 64, unit u to wavefront u mod 8. A unit's rows stream through
+// the wavefront's own two LDS buffers of 128 bytes per row (no barrier: the wavefront
+// waits for its own loads). FP32: lane l scores atom l; its sum is the
+// FMA chain that v_mfma_f32_32x32x2f32 runs in the batch kernels (per eight samples
+// 0, 4, 1, 5, 2, 6, 3, 7; the MFMA adds its two products one after the other with FMA
+// rounding, measured on 153,600 results), so picks are bit-identical to theirs. 16-bit
+// forms: the batch kernels' MFMAs on 64 x 32 fragments (column c holds signal c mod G)
+// and their keys, in the 128 x 128 tile's layout.
+// A step of a small problem takes 7 to 8 us this way at 64 x 256 (18 before), about 5 of
+// them solve_step: a single wavefront's 1000 instructions one after another.
+// ---------------------------------------------------------------------------
+constexpr int LOOP_WAVES = 8, LOOP_BUFS = 2;
+constexpr int LOOP_BUF_CHUNKS = 64 * 8;  // 64 rows of eight 16-byte chunks
+
+// LDS of the loop kernel, in bytes: the staging buffers, the signals' residuals (FP32 or
+// 16-bit), masks and 1 / ||a||. The steps' own regions lie in the staging buffers, which
+// they do not overlap in time.
+constexpr size_t LOOP_STAGE_BYTES = (size_t)LOOP_WAVES * LOOP_BUFS * LOOP_BUF_CHUNKS * 16;
+__host__ __device__ inline size_t loop_lds(int64_t Mp, int64_t Np, int G, bool half) {
+  return LOOP_STAGE_BYTES + (size_t)G * Mp * (half ? 2 : 4) + (size_t)G * (Np / 8) + (size_t)Np * 4;
+}
+
+// A wavefront's 8 KiB of a slice: eight loads of 1 KiB, load i from base + off[i] to LDS
+// chunk 64 i after `l`, M0 moved on between them (dma16 saves and restores it each time).
+// No load destination is a register; the caller waits (vmcnt) before it reads.
+__device__ inline void dma16x8(const void *base, const uint32_t (&off)[8], lds_void_t *l) {
+  const uint32_t la = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)l);
+  uint32_t saved;
+  asm volatile(
+      "s_mov_b32 %0, m0\n\ts_mov_b32 m0, %2\n\ts_nop 0\n\t"
+      "global_load_lds_dwordx4 %3, %1\n\ts_add_u32 m0, m0, 0x400\n\ts_nop 0\n\t"
+      "global_load_lds_dwordx4 %4, %1\n\ts_add_u32 m0, m0, 0x400\n\ts_nop 0\n\t"
+      "global_load_lds_dwordx4 %5, %1\n\ts_add_u32 m0, m0, 0x400\n\ts_nop 0\n\t"
+      "global_load_lds_dwordx4 %6, %1\n\ts_add_u32 m0, m0, 0x400\n\ts_nop 0\n\t"
+      "global_load_lds_dwordx4 %7, %1\n\ts_add_u32 m0, m0, 0x400\n\ts_nop 0\n\t"
+      "global_load_lds_dwordx4 %8, %1\n\ts_add_u32 m0, m0, 0x400\n\ts_nop 0\n\t"
+      "global_load_lds_dwordx4 %9, %1\n\ts_add_u32 m0, m0, 0x400\n\ts_nop 0\n\t"
+      "global_load_lds_dwordx4 %10, %1\n\ts_nop 0\n\t"
+      "s_mov_b32 m0, %0"
+      : "=&s"(saved)
+      : "s"(base), "s"(la), "v"(off[0]), "v"(off[1]), "v"(off[2]), "v"(off[3]), "v"(off[4]), "v"(off[5]), "v"(off[6]),
+        "v"(off[7])
+      : "memory", "scc");
+}
+
+// GM >= G: signals the FP32 product keeps sums for (the 16-bit forms keep columns: GM = 1).
+template <class Op, bool HALF, int GM>
+__global__ __launch_bounds__(64 * LOOP_WAVES) void k_solve_loop(DictView d, WorkView w, SlotView sv, int G) {
+  extern __shared__ u32x4 lsm[];
+  __shared__ uint64_t red[LOOP_WAVES][LOOP_WAVES];  // FP32: the wavefronts' best keys per signal
+  const int tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int64_t bg = (int64_t)blockIdx.x * G;  // the workgroup's first signal
+  const int ng = (int)min<int64_t>(G, w.B - bg);
+  const int64_t Mp = d.Mp, Np = d.Np;
+  constexpr int EPC = HALF ? 8 : 4;                 // elements per 16-byte chunk
+  const int rch = (int)(Mp / EPC), nsl = rch / 8;   // chunks per row, slices of eight chunks
+  const int nunit = (int)((d.N + 63) / 64), mw = (int)(Np / 32);
+  u32x4 *buf = lsm + (size_t)wv * LOOP_BUFS * LOOP_BUF_CHUNKS;
+  u32x4 *rl = lsm + LOOP_WAVES * LOOP_BUFS * LOOP_BUF_CHUNKS;         // [G][rch]
+  uint32_t *ml = reinterpret_cast<uint32_t *>(rl + (size_t)G * rch);  // [G][mw]
+  float *ivl = reinterpret_cast<float *>(ml + (size_t)G * mw);        // [Np]
+  float *solve_lds = reinterpret_cast<float *>(lsm);                  // [G][solve_lds_per_wave], over the buffers
+  const u32x4 *A = reinterpret_cast<const u32x4 *>(HALF ? (const void *)d.A16 : (const void *)d.A32);
+  const u32x4 *R = reinterpret_cast<const u32x4 *>(HALF ? (const void *)w.R16 : (const void *)w.R32);
+  const int nkeys = w.ntile * w.ncand;
+  {
+    const float *inv = d.inv_nu_h ? d.inv_nu_h : d.inv_nu;
+    for (int i = tid; i < Np; i += 64 * LOOP_WAVES) ivl[i] = inv[i];
+  }
+  if (HALF) {  // the keys of units without atoms: score 0, not selectable
+    uint32_t *keys = reinterpret_cast<uint32_t *>(w.part) + bg * nkeys;
+    for (int i = tid; i < ng * nkeys; i += 64 * LOOP_WAVES) keys[i] = 0x80000000u;
+  }
+  uint32_t roff[8];  // byte offsets of the lane's chunk in each load's row
+#pragma unroll
+  for (int i = 0; i < 8; ++i) {
+    const int row = 8 * i + (lane >> 3);
+    roff[i] = (uint32_t)(row * rch + lds_slot(row, lane & 7)) * 16u;
+  }
+  const int h = lane >> 5, r32 = lane & 31;
+  const int cg = r32 % G;  // 16-bit forms: the signal of the lane's column
+  for (int it = 0; it < w.S; ++it) {
+    // ---- the residuals and masks of the signals into LDS; stop when every signal has
+    int live = 0;
+    if (tid < ng) live = !(w.flags[bg + tid] & FLAG_DONE);
+    for (int i = tid; i < G * rch; i += 64 * LOOP_WAVES)
+      rl[i] = i < ng * rch ? R[bg * rch + i] : u32x4{0, 0, 0, 0};
+    for (int i = tid; i < ng * mw; i += 64 * LOOP_WAVES) ml[i] = w.mask[bg * mw + i];
+    if (!__syncthreads_or(live)) return;
+
+    // ---- product: the wavefront's steps are (unit, slice) pairs in order
+    const int myunits = nunit > wv ? (nunit - wv + LOOP_WAVES - 1) / LOOP_WAVES : 0;
+    const int nstep = myunits * nsl;
+    // (positions advance by counters: a division per step would cost as much as its FMAs)
+    int isl = 0, ibuf = 0;              // slice and buffer of the next issue
+    const u32x4 *isrc = A + (int64_t)wv * 64 * rch;  // its unit's rows at its slice
+    auto issue = [&]() {
+      dma16x8(isrc, roff, (lds_void_t *)(buf + ibuf * LOOP_BUF_CHUNKS));  // eight rows per load
+      isrc += 8;
+      ibuf = ibuf + 1 < LOOP_BUFS ? ibuf + 1 : 0;
+      if (++isl == nsl) {
+        isl = 0;
+        isrc += (int64_t)(LOOP_WAVES * 64 - 1) * rch;
+      }
+    };
+    __builtin_amdgcn_s_waitcnt(0);
+    for (int st = 0; st < LOOP_BUFS - 1 && st < nstep; ++st) issue();
+    int sl = 0, cbuf = 0, unit = wv;
+    float acc[GM] = {};                       // FP32: the atom's sum for each signal
+    uint64_t best[GM] = {};
+    f32x16 fa[2] = {f32x16{}, f32x16{}};      // 16-bit: two 32 x 32 fragments
+    for (int st = 0; st < nstep; ++st) {
+      if (st + 1 < nstep) {
+        issue();  // (its buffer was read in step st - 1, by this wavefront only)
+        wait_vm<8>();
+      } else {
+        wait_vm<0>();
+      }
+      __builtin_amdgcn_wave_barrier();
+      const u32x4 *L = buf + cbuf * LOOP_BUF_CHUNKS;
+      if constexpr (!HALF) {
+        u32x4 a[8];
+#pragma unroll
+        for (int c = 0; c < 8; ++c) a[c] = L[lane * 8 + lds_slot(lane, c)];
+#pragma unroll
+        for (int g = 0; g < GM; ++g) {  // (past G: the last signal again, not stored)
+          const u32x4 *r = rl + (g < G ? g : G - 1) * rch + sl * 8;
+#pragma unroll
+          for (int q = 0; q < 4; ++q) {
+            const u32x4 r0 = r[2 * q], r1 = r[2 * q + 1];
+#pragma unroll
+            for (int t = 0; t < 4; ++t) {
+              acc[g] = fmaf(__uint_as_float(a[2 * q][t]), __uint_as_float(r0[t]), acc[g]);
+              acc[g] = fmaf(__uint_as_float(a[2 * q + 1][t]), __uint_as_float(r1[t]), acc[g]);
+            }
+          }
+        }
+        if (sl == nsl - 1) {
+          const int n = unit * 64 + lane;
+          const float iv = ivl[n];
+#pragma unroll
+          for (int g = 0; g < GM; ++g) {
+            if (g >= G) break;
+            const float sc = fabsf(acc[g]) * iv;
+            const bool cand = iv > 0.f && !((ml[g * mw + (n >> 5)] >> (n & 31)) & 1u) && sc >= 0.f;
+            const uint64_t key =
+                cand ? ((uint64_t)__float_as_uint(sc) << 32) | (uint64_t)(0xFFFFFFFFu - (uint32_t)n) : 0ull;
+            best[g] = max(best[g], key);
+            acc[g] = 0.f;
+          }
+        }
+      } else {
+        const u32x4 *r = rl + cg * rch + sl * 8;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          const u32x4 b = r[2 * q + h];
+#pragma unroll
+          for (int i = 0; i < 2; ++i) {
+            const int row = i * 32 + r32;
+            Op::mma(L[row * 8 + lds_slot(row, 2 * q + h)], b, fa[i]);
+          }
+        }
+        if (sl == nsl - 1) {
+          // top three of the lane's 32 atoms as k_corr_select keeps them (subgroup of two fragments)
+          uint32_t k1 = 0, k2 = 0, k3 = 0;
+#pragma unroll
+          for (int i = 0; i < 2; ++i) {
+            float4 iv[4];  // of rows 8 (q / 4) + 4 h + q % 4
+#pragma unroll
+            for (int q = 0; q < 4; ++q) iv[q] = *reinterpret_cast<const float4 *>(ivl + unit * 64 + i * 32 + 8 * q + 4 * h);
+#pragma unroll
+            for (int q = 0; q < 16; ++q) {
+              const float4 v = iv[q >> 2];
+              const float sc = fabsf(fa[i][q]) * ((q & 3) == 0 ? v.x : (q & 3) == 1 ? v.y : (q & 3) == 2 ? v.z : v.w);
+              const uint32_t key = (__float_as_uint(sc) & ~31u) | (uint32_t)(31 - (i * 16 + q));
+              const uint32_t n1 = max(k1, key);
+              const uint32_t n2 = max(min(k1, k2), min(max(k1, k2), key));
+              const uint32_t n3 = max(min(k2, k3), min(max(k2, k3), key));
+              k1 = n1;
+              k2 = n2;
+              k3 = n3;
+            }
+            fa[i] = f32x16{};
+          }
+          if (r32 < ng) {
+            const uint32_t ks[NKEEP] = {k1, k2, k3};
+            uint32_t *dst = reinterpret_cast<uint32_t *>(w.part) + (bg + r32) * nkeys + (unit >> 1) * w.ncand +
+                            ((unit & 1) * 2 + h) * NKEEP;
+#pragma unroll
+            for (int q = 0; q < NKEEP; ++q) {
+              const int loc = 31 - (int)(ks[q] & 31u);
+              const int n = unit * 64 + (loc >> 4) * 32 + frag_row(lane, loc & 15);
+              const bool valid = ivl[n] > 0.f && !((ml[r32 * mw + (n >> 5)] >> (n & 31)) & 1u);
+              dst[q] = valid ? ks[q] : (ks[q] | 0x80000000u);
+            }
+          }
+        }
+      }
+      cbuf = cbuf + 1 < LOOP_BUFS ? cbuf + 1 : 0;
+      if (++sl == nsl) {
+        sl = 0;
+        unit += LOOP_WAVES;
+      }
+    }
+    if (!HALF) {
+#pragma unroll
+      for (int g = 0; g < GM; ++g) {
+        if (g >= G) break;
+        const uint64_t top = wave_max(best[g]);
+        if (lane == 0) red[g][wv] = top;
+      }
+    }
+    __syncthreads();
+    if (!HALF && wv < ng) {
+      const uint64_t top = wave_max(lane < LOOP_WAVES ? red[wv][lane] : 0ull);
+      if (lane == 0) w.part[bg + wv] = top;  // one key per signal, read back by the same lane
+    }
+    // ---- the step of every signal (its LDS region is its own; the buffers are not used)
+    if (wv < ng)
+      solve_step<1, HALF, false, false, false>(d, w, sv, bg + wv, lane,
+                                               solve_lds + (size_t)wv * (w.vstride + solve_list_len(w)));
+    __syncthreads();
+  }
 }
 
 // Key of atom n with correlation c (0: not a candidate), as the FP32 select writes it.
@@ -2436,6 +2674,53 @@ hipError_t launch_solve(const DictView &d, const WorkView &w, int precision, hip
 hipError_t launch_solve_slots(const DictView &d, const WorkView &w, const SlotView &sv, int precision,
                               hipStream_t st) {
   return launch_solve_any<true>(d, w, sv, precision, st);
+}
+
+// Signals per workgroup of the one-launch solve, or 0 where the step-by-step kernels run.
+// One workgroup per CU, so a batch of up to 256 G signals takes one turn of the chip. The
+// FP32 product costs N M G FMAs on one CU: measured whole solves, step by step against one
+// launch, us: 256 x 1024, S = 32: B = 256 1028 and 507, B = 1000 1079 and 729, B = 2000
+// 1151 and 1097; 256 x 2048: B = 500 1069 and 862, B = 1000 1079 and 1185; 800 x 1000, S =
+// 16: B = 1000 1191 and 894, B = 2000 1225 and 1419; 64 x 256, S = 8: B = 1 145 and 72, B =
+// 2000 176 and 113. Hence N G <= 4096. The 16-bit product costs the same for any G; what
+// grows is the reading of A by every CU: BF16 / FP16, B = 1000: 64 x 256 225 / 146 and 107
+// / 88, 256 x 1024 900 / 651 and 555 / 502, 1024 x 1024 2315 / 1276 and 1576 / 1188, 256 x
+// 1500 830 / 677 and 638 / 602, 256 x 2048 855 / 683 and 739 / 699, 500 x 1500 1316 / 870
+// and 968 / 888. Hence N <= 1024, or 768 KiB of 16-bit atoms.
+int solve_loop_signals(const DictView &d, const WorkView &w, int precision) {
+  const bool half = is_half(precision);
+  if (w.gram_dom || w.v0 || w.gram_fly || w.refactor || w.flag_ties || precision == OMP_PREC_FP64) return 0;
+  if (w.S > 64 || w.tile_cfg != 1 || w.B > 256 * LOOP_WAVES) return 0;
+  const int G = (int)((w.B + 255) / 256);
+  if (d.Mp > 1024 || d.N > 2048) return 0;
+  if (half ? d.N > 1024 && d.N * d.Mp * 2 > (int64_t)768 << 10 : d.N * G > 4096) return 0;
+  if (solve_lds_per_wave(w) * (size_t)G > LOOP_STAGE_BYTES) return 0;
+  return loop_lds(d.Mp, d.Np, G, half) + sizeof(uint64_t) * LOOP_WAVES * LOOP_WAVES <= LDS_LIMIT ? G : 0;
+}
+
+hipError_t launch_solve_loop(const DictView &d, const WorkView &w0, int precision, hipStream_t st) {
+  const int G = solve_loop_signals(d, w0, precision);
+  if (G < 1) return hipErrorInvalidValue;
+  WorkView w = w0;
+  const bool half = is_half(precision);
+  w.fuse_res = 1;
+  if (!half) {  // one key per signal
+    w.ntile = 1;
+    w.ncand = 1;
+  }
+  SlotView none;
+  memset(&none, 0, sizeof(none));
+  const size_t lds = loop_lds(d.Mp, d.Np, G, half);
+  auto kern = precision == OMP_PREC_BF16   ? k_solve_loop<OpBF16, true, 1>
+              : precision == OMP_PREC_FP16 ? k_solve_loop<OpF16, true, 1>
+              : G == 1                     ? k_solve_loop<OpF32, false, 1>
+              : G == 2                     ? k_solve_loop<OpF32, false, 2>
+              : G <= 4                     ? k_solve_loop<OpF32, false, 4>
+                                           : k_solve_loop<OpF32, false, 8>;
+  hipError_t e = allow_lds(kern, lds);
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL(kern, dim3((unsigned)((w.B + G - 1) / G)), dim3(64 * LOOP_WAVES), lds, st, d, w, none, G);
+  return hipGetLastError();
 }
 
 hipError_t launch_init_slots(const WorkView &w, const SlotView &sv, hipStream_t st) {
