@@ -508,10 +508,14 @@ int solve_impl(const float *A, int64_t M, int64_t N, int64_t lda, const float *Y
     if (f64) {
       // FP64 form: Algorithm v0 in FP64
       if (e == hipSuccess) e = timer.run(OMP_PHASE_INIT, [&] { return launch_project64(d, w, cs); });
-      if (e == hipSuccess) e = timer.run(OMP_PHASE_INIT, [&] { return launch_v0_first64(d, w, cs); });
-      for (int it = 0; it < S && e == hipSuccess; ++it)
-        e = timer.run(OMP_PHASE_UPDATE, [&] { return launch_v0_step64(d, w, cs); });
-      if (e == hipSuccess) e = timer.run(OMP_PHASE_OUTPUT, [&] { return launch_v0_coef64(w, cs); });
+      if (!timer.on()) {
+        if (e == hipSuccess) e = launch_v0_solve64(d, w, cs);
+      } else {  // a timed call reports every step
+        if (e == hipSuccess) e = timer.run(OMP_PHASE_INIT, [&] { return launch_v0_parts64(d, w, 1, 0, 0, cs); });
+        for (int it = 0; it < S && e == hipSuccess; ++it)
+          e = timer.run(OMP_PHASE_UPDATE, [&] { return launch_v0_parts64(d, w, 0, 1, 0, cs); });
+        if (e == hipSuccess) e = timer.run(OMP_PHASE_OUTPUT, [&] { return launch_v0_parts64(d, w, 0, 0, 1, cs); });
+      }
     } else if (v0) {
       // Algorithm v0: one kernel per step, the coefficients x = F u at the end
       if (e == hipSuccess) e = timer.run(OMP_PHASE_INIT, [&] { return launch_project(d, w, cs); });
@@ -545,7 +549,7 @@ int solve_impl(const float *A, int64_t M, int64_t N, int64_t lda, const float *Y
 
   hipError_t e = hipSuccess;
   bool done = false;
-  if (!direct && opts->use_graph && !timer.on() && !loop) {  // (three launches need no graph)
+  if (!direct && opts->use_graph && !timer.on() && !loop && !f64) {  // (a few launches need no graph)
     // The whole solve replayed from a hipGraph cached under every argument. On
     // the first use the launches are captured. (A timed call launches directly:
     // events recorded by graph nodes cannot be read back with elapsed times.)

@@ -276,12 +276,11 @@ hipError_t launch_v0_first(const DictView &d, const WorkView &w, hipStream_t st)
 hipError_t launch_v0_step(const DictView &d, const WorkView &w, hipStream_t st);
 hipError_t launch_v0_coef(const WorkView &w, hipStream_t st);
 // FP64 form: G64 = A32 A32^T and P64 = Yp A32^T (exact products, FP64 sums), then
-// the v0 kernels in FP64.
+// every signal's v0 steps and coefficients in one launch.
 hipError_t launch_gram64(const DictView &d, hipStream_t st);
 hipError_t launch_project64(const DictView &d, const WorkView &w, hipStream_t st);
-hipError_t launch_v0_first64(const DictView &d, const WorkView &w, hipStream_t st);
-hipError_t launch_v0_step64(const DictView &d, const WorkView &w, hipStream_t st);
-hipError_t launch_v0_coef64(const WorkView &w, hipStream_t st);
+hipError_t launch_v0_solve64(const DictView &d, const WorkView &w, hipStream_t st);
+hipError_t launch_v0_parts64(const DictView &d, const WorkView &w, int first, int steps, int last, hipStream_t st);
 
 // Outputs: dense X, support, coefficients, status, residual norm.
 hipError_t launch_finalize(const DictView &d, const WorkView &w, float *X_out,

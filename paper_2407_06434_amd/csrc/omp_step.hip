@@ -2280,8 +2280,7 @@ __device__ inline void pick_insert(double s, int n, Pick64 &p1, Pick64 &p2) {
   }
 }
 
-__global__ __launch_bounds__(V0_THREADS) void k_v0_first64(DictView d, WorkView w) {
-  __shared__ Pick64 red[2 * V0_THREADS / 64];
+__device__ inline void v0_first64(const DictView &d, const WorkView &w, Pick64 *red) {
   const int64_t b = blockIdx.x;
   const double *c = w.P64 + b * d.Np;
   Pick64 p1{-1.0, 0x7fffffff}, p2{-1.0, 0x7fffffff};
@@ -2292,15 +2291,13 @@ __global__ __launch_bounds__(V0_THREADS) void k_v0_first64(DictView d, WorkView 
   v0_store_pick64(w, b, p1, p2, red);
 }
 
-// One FP64 v0 step per live signal (the FP32 step's arithmetic in FP64).
-__global__ __launch_bounds__(V0_THREADS) void k_v0_step64(DictView d, WorkView w) {
-  extern __shared__ uint32_t v0s[];
-  __shared__ Pick64 red[2 * V0_THREADS / 64];
-  __shared__ double part4[V0_THREADS / 64];
+// One FP64 v0 step of a live signal (the FP32 step's arithmetic in FP64); the workgroup
+// leaves as a whole. False: the signal takes no further step.
+__device__ inline bool v0_step64(const DictView &d, const WorkView &w, uint32_t *v0s, Pick64 *red, double *part4) {
   const int64_t b = blockIdx.x;
   const int tid = threadIdx.x;
   int fl = w.flags[b];
-  if (fl & FLAG_DONE) return;
+  if (fl & FLAG_DONE) return false;
   const int k = w.k[b];
   const int S = w.S;
   const int64_t Np = d.Np, mwords = Np / 32;
@@ -2312,7 +2309,7 @@ __global__ __launch_bounds__(V0_THREADS) void k_v0_step64(DictView d, WorkView w
   const double s1 = pk[0], s2 = pk[2];
   if (rn <= (double)eps_b || !(s1 >= 0.0)) {
     if (tid == 0) w.flags[b] = fl | FLAG_DONE | (rn <= (double)eps_b ? 0 : OMP_SIG_EXHAUSTED);
-    return;
+    return false;
   }
   const int nstar = (int)pk[1];
   if (w.flag_ties && s2 >= 0.0 && s2 >= (1.0 - TIE_REL) * s1) fl |= OMP_SIG_NEARTIE;
@@ -2332,7 +2329,7 @@ __global__ __launch_bounds__(V0_THREADS) void k_v0_step64(DictView d, WorkView w
   const double d2 = nu2 - part4[0];
   if (!(d2 > DEP_TOL2 * nu2)) {
     if (tid == 0) w.flags[b] = fl | FLAG_DONE | OMP_SIG_DEPENDENT;
-    return;
+    return false;
   }
   const double g = 1.0 / sqrt(d2);
   const double uk = g * c[nstar];
@@ -2409,18 +2406,177 @@ __global__ __launch_bounds__(V0_THREADS) void k_v0_step64(DictView d, WorkView w
     w.k[b] = K;
     w.flags[b] = fl | (K >= w.Sb[b] ? FLAG_DONE : 0);
   }
+  return true;
 }
 
-// x = F u in FP64, rounded once to the FP32 coefficient outputs.
-__global__ __launch_bounds__(64) void k_v0_coef64(WorkView w) {
+// The whole FP64 solve of a signal with D in memory: the first pick, its steps, and x =
+// F u, rounded once to the FP32 coefficient outputs. Signals are independent of each other
+// in this form, so nothing but a workgroup barrier is needed between steps, and D, c and F
+// of the signals at work stay in the caches where a launch per step went through all of them.
+// (A timed call launches the parts one by one: `first`, `steps` steps, `last`.)
+__global__ __launch_bounds__(V0_THREADS) void k_v0_solve64(DictView d, WorkView w, int first, int steps, int last) {
+  extern __shared__ uint32_t v0s[];
+  __shared__ Pick64 red[2 * V0_THREADS / 64];
+  __shared__ double part4[V0_THREADS / 64];
   const int64_t b = blockIdx.x;
-  const int k = w.k[b];
   const int S = w.S;
+  if (first && !(w.flags[b] & FLAG_DONE)) v0_first64(d, w, red);
+  for (int it = 0; it < steps; ++it) {
+    __syncthreads();
+    if (!v0_step64(d, w, v0s, red, part4)) break;
+  }
+  if (!last) return;
+  __syncthreads();
+  const int k = w.k[b];
   const double *F = w.V64 + b * w.vstride;
-  for (int i = threadIdx.x; i < k; i += 64) {
+  for (int i = threadIdx.x; i < k; i += V0_THREADS) {
     double acc = 0.0;
     for (int j = i; j < k; ++j) acc += F[(int64_t)j * (j + 1) / 2 + i] * w.u64[b * S + j];
     w.xh[b * S + i] = (float)acc;
+  }
+}
+
+// ---------------------------------------------------------------------------
+// The same with D in registers, for dictionaries of up to 1024 (padded) atoms: thread n
+// holds c_n and row n of D (SM columns), F, z, u and the support lie in LDS, so a step
+// reads one row of G and nothing else. The arithmetic and its order are v0_step64's; the
+// columns a signal does not have yet are zero and their FMAs change nothing. A step is two
+// barriers and a few hundred instructions per wavefront; with a launch per step every
+// column of D came back from memory (8 GB at 256 x 1024, S = 32, B = 2000: 3.37 ms at 2.5
+// TB/s, against 1.08 ms now, 4 us a step).
+// ---------------------------------------------------------------------------
+template <int SM, int NTMAX>
+__global__ __launch_bounds__(NTMAX) void k_v0_reg64(DictView d, WorkView w) {
+  extern __shared__ double F[];  // packed by columns: column k at k (k + 1) / 2
+  __shared__ double zs[SM], us[SM], xs[SM], cstar, part[16];
+  __shared__ uint64_t rkey[2][16];
+  __shared__ int rn_[2][16], ss[SM];
+  const int64_t b = blockIdx.x, Np = d.Np;
+  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, nw = (int)(Np / 64);
+  int fl = w.flags[b];
+  if (fl & FLAG_DONE) return;
+  const double iv = d.inv_nu64[tid], y2 = w.pdelta[b * NSLICE_MAX];
+  const float eps_b = w.epsb[b];
+  const int Sb = w.Sb[b];
+  double c = w.P64[b * Np + tid], r2 = w.pnorm[b * NSLICE_MAX];
+  double D[SM];
+#pragma unroll
+  for (int j = 0; j < SM; ++j) D[j] = 0.0;
+  bool taken = !(iv > 0.0);
+  // Best atom of the workgroup other than `skip`: its key (score bits + 1, 0: none) and index;
+  // ties to the lowest index (atoms ascend with lanes and wavefronts). One barrier; `set`
+  // alternates between two buffers.
+  auto best_of = [&](int skip, int set, uint64_t *key) {
+    const double s = fabs(c) * iv;
+    const uint64_t mine =
+        (!taken && tid != skip && s >= 0.0) ? (uint64_t)__double_as_longlong(s) + 1ull : 0ull;
+    const uint64_t m = wave_max(mine);
+    const uint64_t who = __ballot(mine == m);
+    if (lane == 0) {
+      rkey[set][wv] = m;
+      rn_[set][wv] = wv * 64 + __ffsll((unsigned long long)who) - 1;
+    }
+    __syncthreads();
+    const uint64_t wk = lane < nw ? rkey[set][lane] : 0ull;
+    const uint64_t top = wave_max(wk);
+    const int at = __ffsll((unsigned long long)__ballot(wk == top)) - 1;  // (top 0: wave 0's, not used)
+    *key = top;
+    return rn_[set][at < nw ? at : 0];
+  };
+  int k = 0;
+  for (; k < w.S; ++k) {
+    uint64_t key, key2 = 0;
+    const int nstar = best_of(-1, 0, &key);
+    const double rn = sqrt(r2);
+    if (rn <= (double)eps_b || key == 0ull) {
+      fl |= FLAG_DONE | (rn <= (double)eps_b ? 0 : OMP_SIG_EXHAUSTED);
+      break;
+    }
+    const double Gr = d.G64[(int64_t)nstar * Np + tid], nu2 = d.nu2[nstar];
+    if (w.flag_ties) {
+      (void)best_of(nstar, 1, &key2);
+      const double s1 = __longlong_as_double((long long)(key - 1ull));
+      if (key2 != 0ull && __longlong_as_double((long long)(key2 - 1ull)) >= (1.0 - TIE_REL) * s1) fl |= OMP_SIG_NEARTIE;
+    }
+    if (tid == nstar) {  // z = row n* of D
+#pragma unroll
+      for (int j = 0; j < SM; ++j) zs[j] = D[j];
+      cstar = c;
+    }
+    __syncthreads();
+    const double zl = lane < k ? zs[lane < SM ? lane : 0] : 0.0;
+    const double d2 = nu2 - wave_sum(zl * zl);
+    if (!(d2 > DEP_TOL2 * nu2)) {  // dependent atom: stop without appending
+      fl |= FLAG_DONE | OMP_SIG_DEPENDENT;
+      break;
+    }
+    const double g = 1.0 / sqrt(d2);
+    const double uk = g * cstar;
+    double a = Gr;
+#pragma unroll
+    for (int j0 = 0; j0 < SM; j0 += 4)
+      if (j0 < k) {
+#pragma unroll
+        for (int j = j0; j < j0 + 4; ++j) a = fma(-zs[j], D[j], a);
+      }
+    a *= g;
+#pragma unroll
+    for (int j = 0; j < SM; ++j)
+      if (j == k) D[j] = a;  // wave-uniform
+    taken = taken || tid == nstar;
+    c = taken ? 0.0 : fma(-uk, a, c);
+    // new column of F by the last wavefront's lanes: f_i = -g sum_{j=i}^{k-1} F[i][j] z_j, f_k = g
+    if (wv == nw - 1 && lane <= k) {
+      double acc = 0.0;
+      for (int j = lane; j < k; ++j) acc += F[j * (j + 1) / 2 + lane] * zs[j];
+      F[k * (k + 1) / 2 + lane] = lane == k ? g : -g * acc;
+      if (lane == 0) {
+        us[k] = uk;
+        ss[k] = nstar;
+      }
+    }
+    const int K = k + 1;
+    r2 = rn * rn - uk * uk;
+    const double floor2 = 64.0 * (double)(K + 1) * (1.0 / 9007199254740992.0) * y2;
+    const double e2 = (double)eps_b * (double)eps_b;
+    if (!(r2 > floor2) || fabs(r2 - e2) <= floor2) {  // uniform: every thread has the same values
+      __syncthreads();
+      for (int i = tid; i < K; i += (int)Np) {
+        double acc = 0.0;
+        for (int j = i; j < K; ++j) acc += F[j * (j + 1) / 2 + i] * us[j];
+        xs[i] = acc;
+      }
+      __syncthreads();
+      const float *yb = w.Yp + b * w.Mp;
+      double acc = 0.0;
+      for (int64_t m = tid; m < d.M; m += Np) {
+        double rm = (double)yb[m];
+        for (int j = 0; j < K; ++j) rm -= xs[j] * (double)d.A32[(int64_t)ss[j] * d.Mp + m];
+        acc += rm * rm;
+      }
+      acc = wave_sum(acc);
+      if (lane == 0) part[wv] = acc;
+      __syncthreads();
+      r2 = 0.0;
+      for (int i = 0; i < nw; ++i) r2 += part[i];
+    }
+    if (K >= Sb) {
+      fl |= FLAG_DONE;
+      ++k;
+      break;
+    }
+  }
+  __syncthreads();
+  for (int i = tid; i < k; i += (int)Np) {
+    double acc = 0.0;
+    for (int j = i; j < k; ++j) acc += F[j * (j + 1) / 2 + i] * us[j];
+    w.xh[b * w.S + i] = (float)acc;
+    w.sup[b * w.S + i] = ss[i];
+  }
+  if (tid == 0) {
+    w.pnorm[b * NSLICE_MAX] = r2;
+    w.k[b] = k;
+    w.flags[b] = fl;
   }
 }
 
@@ -2818,27 +2974,37 @@ hipError_t launch_project64(const DictView &d, const WorkView &w, hipStream_t st
   return hipGetLastError();
 }
 
-hipError_t launch_v0_first64(const DictView &d, const WorkView &w, hipStream_t st) {
-  if (w.B == 0) return hipSuccess;
-  if (!w.P64 || !d.inv_nu64 || w.Np != d.Np) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(k_v0_first64, dim3((unsigned)w.B), dim3(V0_THREADS), 0, st, d, w);
+namespace {
+template <int SM, int NTMAX>
+hipError_t launch_v0_reg64(const DictView &d, const WorkView &w, hipStream_t st) {
+  const size_t lds = (size_t)w.S * (w.S + 1) / 2 * 8;
+  hipLaunchKernelGGL((k_v0_reg64<SM, NTMAX>), dim3((unsigned)w.B), dim3((unsigned)d.Np), lds, st, d, w);
   return hipGetLastError();
 }
+}  // namespace
 
-hipError_t launch_v0_step64(const DictView &d, const WorkView &w, hipStream_t st) {
+// Parts of the FP64 solve with D in memory: the first pick, `steps` steps, x = F u.
+hipError_t launch_v0_parts64(const DictView &d, const WorkView &w, int first, int steps, int last, hipStream_t st) {
   if (w.B == 0) return hipSuccess;
   if (!w.P64 || !w.D64 || !w.V64 || !w.u64 || !d.G64 || !d.inv_nu64 || w.Np != d.Np) return hipErrorInvalidValue;
   const size_t lds = (size_t)(2 * w.S + d.Np / 32) * 4;
-  hipError_t e = allow_lds(k_v0_step64, lds);
+  hipError_t e = allow_lds(k_v0_solve64, lds);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(k_v0_step64, dim3((unsigned)w.B), dim3(V0_THREADS), lds, st, d, w);
+  hipLaunchKernelGGL(k_v0_solve64, dim3((unsigned)w.B), dim3(V0_THREADS), lds, st, d, w, first, steps, last);
   return hipGetLastError();
 }
 
-hipError_t launch_v0_coef64(const WorkView &w, hipStream_t st) {
+// A thread per atom with its row of D in registers where the registers of a CU hold D: 1024
+// threads of 32 columns, or 512 of 64; else D in memory.
+hipError_t launch_v0_solve64(const DictView &d, const WorkView &w, hipStream_t st) {
+  const bool reg = d.Np <= 1024 && w.S <= (d.Np <= 512 ? 64 : 32);
+  if (!reg) return launch_v0_parts64(d, w, 1, w.S, 1, st);
   if (w.B == 0) return hipSuccess;
-  hipLaunchKernelGGL(k_v0_coef64, dim3((unsigned)w.B), dim3(64), 0, st, w);
-  return hipGetLastError();
+  if (!w.P64 || !w.D64 || !w.V64 || !w.u64 || !d.G64 || !d.inv_nu64 || w.Np != d.Np) return hipErrorInvalidValue;
+  if (w.S <= 8) return launch_v0_reg64<8, 1024>(d, w, st);
+  if (w.S <= 16) return launch_v0_reg64<16, 1024>(d, w, st);
+  if (w.S <= 32) return launch_v0_reg64<32, 1024>(d, w, st);
+  return launch_v0_reg64<64, 512>(d, w, st);
 }
 
 hipError_t launch_residual(const DictView &d, const WorkView &w, int precision, int kbound, hipStream_t st) {
