@@ -1467,7 +1467,8 @@ __global__ __launch_bounds__(64 * SOLVE_WAVES) void k_solve(DictView d, WorkView
 // with their state read back from beyond the L2s. Here a workgroup of eight wavefronts
 // keeps G <= 8 signals to itself and runs all their steps: the product of its signals with
 // every atom, then solve_step, one wavefront per signal, with workgroup barriers between;
-// what one phase leaves for the next stays in the CU's caches.
+// what one phase leaves for the next stays in the CU's caches. (16-bit forms: G <= 32 in
+// workgroups of 16 wavefronts, the wavefronts taking signals in turns.)
 //
 // Product: atoms in units of 64, unit u to wavefront u mod 8. A unit's rows stream through
 // the wavefront's own two LDS buffers of 128 bytes per row (no barrier: the wavefront
@@ -1480,7 +1481,7 @@ __global__ __launch_bounds__(64 * SOLVE_WAVES) void k_solve(DictView d, WorkView
 // A step of a small problem takes 7 to 8 us this way at 64 x 256 (18 before), about 5 of
 // them solve_step: a single wavefront's 1000 instructions one after another.
 // ---------------------------------------------------------------------------
-constexpr int LOOP_WAVES = 8, LOOP_BUFS = 2;
+constexpr int LOOP_WAVES = 8, LOOP_BUFS = 2;  // or twice the wavefronts with one buffer each
 constexpr int LOOP_BUF_CHUNKS = 64 * 8;  // 64 rows of eight 16-byte chunks
 
 // LDS of the loop kernel, in bytes: the staging buffers, the signals' residuals (FP32 or
@@ -1515,10 +1516,10 @@ __device__ inline void dma16x8(const void *base, const uint32_t (&off)[8], lds_v
 }
 
 // GM >= G: signals the FP32 product keeps sums for (the 16-bit forms keep columns: GM = 1).
-template <class Op, bool HALF, int GM>
-__global__ __launch_bounds__(64 * LOOP_WAVES) void k_solve_loop(DictView d, WorkView w, SlotView sv, int G) {
+template <class Op, bool HALF, int GM, int LW, int LB>
+__global__ __launch_bounds__(64 * LW) void k_solve_loop(DictView d, WorkView w, SlotView sv, int G) {
   extern __shared__ u32x4 lsm[];
-  __shared__ uint64_t red[LOOP_WAVES][LOOP_WAVES];  // FP32: the wavefronts' best keys per signal
+  __shared__ uint64_t red[LW][LW];  // FP32: the wavefronts' best keys per signal
   const int tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int64_t bg = (int64_t)blockIdx.x * G;  // the workgroup's first signal
   const int ng = (int)min<int64_t>(G, w.B - bg);
@@ -1526,8 +1527,8 @@ __global__ __launch_bounds__(64 * LOOP_WAVES) void k_solve_loop(DictView d, Work
   constexpr int EPC = HALF ? 8 : 4;                 // elements per 16-byte chunk
   const int rch = (int)(Mp / EPC), nsl = rch / 8;   // chunks per row, slices of eight chunks
   const int nunit = (int)((d.N + 63) / 64), mw = (int)(Np / 32);
-  u32x4 *buf = lsm + (size_t)wv * LOOP_BUFS * LOOP_BUF_CHUNKS;
-  u32x4 *rl = lsm + LOOP_WAVES * LOOP_BUFS * LOOP_BUF_CHUNKS;         // [G][rch]
+  u32x4 *buf = lsm + (size_t)wv * LB * LOOP_BUF_CHUNKS;
+  u32x4 *rl = lsm + LW * LB * LOOP_BUF_CHUNKS;         // [G][rch]
   uint32_t *ml = reinterpret_cast<uint32_t *>(rl + (size_t)G * rch);  // [G][mw]
   float *ivl = reinterpret_cast<float *>(ml + (size_t)G * mw);        // [Np]
   float *solve_lds = reinterpret_cast<float *>(lsm);                  // [G][solve_lds_per_wave], over the buffers
@@ -1536,11 +1537,11 @@ __global__ __launch_bounds__(64 * LOOP_WAVES) void k_solve_loop(DictView d, Work
   const int nkeys = w.ntile * w.ncand;
   {
     const float *inv = d.inv_nu_h ? d.inv_nu_h : d.inv_nu;
-    for (int i = tid; i < Np; i += 64 * LOOP_WAVES) ivl[i] = inv[i];
+    for (int i = tid; i < Np; i += 64 * LW) ivl[i] = inv[i];
   }
   if (HALF) {  // the keys of units without atoms: score 0, not selectable
     uint32_t *keys = reinterpret_cast<uint32_t *>(w.part) + bg * nkeys;
-    for (int i = tid; i < ng * nkeys; i += 64 * LOOP_WAVES) keys[i] = 0x80000000u;
+    for (int i = tid; i < ng * nkeys; i += 64 * LW) keys[i] = 0x80000000u;
   }
   uint32_t roff[8];  // byte offsets of the lane's chunk in each load's row
 #pragma unroll
@@ -1554,13 +1555,13 @@ __global__ __launch_bounds__(64 * LOOP_WAVES) void k_solve_loop(DictView d, Work
     // ---- the residuals and masks of the signals into LDS; stop when every signal has
     int live = 0;
     if (tid < ng) live = !(w.flags[bg + tid] & FLAG_DONE);
-    for (int i = tid; i < G * rch; i += 64 * LOOP_WAVES)
+    for (int i = tid; i < G * rch; i += 64 * LW)
       rl[i] = i < ng * rch ? R[bg * rch + i] : u32x4{0, 0, 0, 0};
-    for (int i = tid; i < ng * mw; i += 64 * LOOP_WAVES) ml[i] = w.mask[bg * mw + i];
+    for (int i = tid; i < ng * mw; i += 64 * LW) ml[i] = w.mask[bg * mw + i];
     if (!__syncthreads_or(live)) return;
 
     // ---- product: the wavefront's steps are (unit, slice) pairs in order
-    const int myunits = nunit > wv ? (nunit - wv + LOOP_WAVES - 1) / LOOP_WAVES : 0;
+    const int myunits = nunit > wv ? (nunit - wv + LW - 1) / LW : 0;
     const int nstep = myunits * nsl;
     // (positions advance by counters: a division per step would cost as much as its FMAs)
     int isl = 0, ibuf = 0;              // slice and buffer of the next issue
@@ -1568,21 +1569,24 @@ __global__ __launch_bounds__(64 * LOOP_WAVES) void k_solve_loop(DictView d, Work
     auto issue = [&]() {
       dma16x8(isrc, roff, (lds_void_t *)(buf + ibuf * LOOP_BUF_CHUNKS));  // eight rows per load
       isrc += 8;
-      ibuf = ibuf + 1 < LOOP_BUFS ? ibuf + 1 : 0;
+      ibuf = ibuf + 1 < LB ? ibuf + 1 : 0;
       if (++isl == nsl) {
         isl = 0;
-        isrc += (int64_t)(LOOP_WAVES * 64 - 1) * rch;
+        isrc += (int64_t)(LW * 64 - 1) * rch;
       }
     };
     __builtin_amdgcn_s_waitcnt(0);
-    for (int st = 0; st < LOOP_BUFS - 1 && st < nstep; ++st) issue();
+    for (int st = 0; st < LB - 1 && st < nstep; ++st) issue();
     int sl = 0, cbuf = 0, unit = wv;
     float acc[GM] = {};                       // FP32: the atom's sum for each signal
     uint64_t best[GM] = {};
     f32x16 fa[2] = {f32x16{}, f32x16{}};      // 16-bit: two 32 x 32 fragments
     for (int st = 0; st < nstep; ++st) {
-      if (st + 1 < nstep) {
+      if (LB == 1) {
         issue();  // (its buffer was read in step st - 1, by this wavefront only)
+        wait_vm<0>();
+      } else if (st + 1 < nstep) {
+        issue();
         wait_vm<8>();
       } else {
         wait_vm<0>();
@@ -1655,8 +1659,7 @@ __global__ __launch_bounds__(64 * LOOP_WAVES) void k_solve_loop(DictView d, Work
           }
           if (r32 < ng) {
             const uint32_t ks[NKEEP] = {k1, k2, k3};
-            uint32_t *dst = reinterpret_cast<uint32_t *>(w.part) + (bg + r32) * nkeys + (unit >> 1) * w.ncand +
-                            ((unit & 1) * 2 + h) * NKEEP;
+            uint32_t *dst = reinterpret_cast<uint32_t *>(w.part) + (bg + r32) * nkeys + (unit * 2 + h) * NKEEP;
 #pragma unroll
             for (int q = 0; q < NKEEP; ++q) {
               const int loc = 31 - (int)(ks[q] & 31u);
@@ -1667,10 +1670,10 @@ __global__ __launch_bounds__(64 * LOOP_WAVES) void k_solve_loop(DictView d, Work
           }
         }
       }
-      cbuf = cbuf + 1 < LOOP_BUFS ? cbuf + 1 : 0;
+      cbuf = cbuf + 1 < LB ? cbuf + 1 : 0;
       if (++sl == nsl) {
         sl = 0;
-        unit += LOOP_WAVES;
+        unit += LW;
       }
     }
     if (!HALF) {
@@ -1683,12 +1686,12 @@ __global__ __launch_bounds__(64 * LOOP_WAVES) void k_solve_loop(DictView d, Work
     }
     __syncthreads();
     if (!HALF && wv < ng) {
-      const uint64_t top = wave_max(lane < LOOP_WAVES ? red[wv][lane] : 0ull);
+      const uint64_t top = wave_max(lane < LW ? red[wv][lane] : 0ull);
       if (lane == 0) w.part[bg + wv] = top;  // one key per signal, read back by the same lane
     }
     // ---- the step of every signal (its LDS region is its own; the buffers are not used)
-    if (wv < ng)
-      solve_step<1, HALF, false, false, false>(d, w, sv, bg + wv, lane,
+    for (int s = wv; s < ng; s += LW)
+      solve_step<1, HALF, false, false, false>(d, w, sv, bg + s, lane,
                                                solve_lds + (size_t)wv * (w.vstride + solve_list_len(w)));
     __syncthreads();
   }
@@ -2838,20 +2841,24 @@ hipError_t launch_solve_slots(const DictView &d, const WorkView &w, const SlotVi
 // launch, us: 256 x 1024, S = 32: B = 256 1028 and 507, B = 1000 1079 and 729, B = 2000
 // 1151 and 1097; 256 x 2048: B = 500 1069 and 862, B = 1000 1079 and 1185; 800 x 1000, S =
 // 16: B = 1000 1191 and 894, B = 2000 1225 and 1419; 64 x 256, S = 8: B = 1 145 and 72, B =
-// 2000 176 and 113. Hence N G <= 4096. The 16-bit product costs the same for any G; what
-// grows is the reading of A by every CU: BF16 / FP16, B = 1000: 64 x 256 225 / 146 and 107
-// / 88, 256 x 1024 900 / 651 and 555 / 502, 1024 x 1024 2315 / 1276 and 1576 / 1188, 256 x
-// 1500 830 / 677 and 638 / 602, 256 x 2048 855 / 683 and 739 / 699, 500 x 1500 1316 / 870
-// and 968 / 888. Hence N <= 1024, or 768 KiB of 16-bit atoms.
+// 2000 176 and 113. Hence N G <= 4096. The 16-bit product costs the same for any G up to
+// 32; what grows is the reading of A by every CU and the turns of solve_step. More than
+// eight signals per workgroup take 16 wavefronts with one buffer each: the turns then share
+// the SIMDs, four wavefronts on each, as in k_solve. BF16, step by step against one launch,
+// us: 64 x 1024, S = 8: B = 100 127 and 94, B = 2048 144 and 111, B = 8192 298 and 240; 500
+// x 512, S = 64: B = 2048 2215 and 1436, B = 4000 2835 and 2919; 256 x 1024, S = 32: B = 500
+// 620 and 520, B = 4000 830 and 888; 512 x 1024: B = 1500 804 and 816; 256 x 1500: B = 500
+// 624 and 622; 128 x 1500, S = 16: B = 5000 572 and 447. Hence up to 512 KiB of 16-bit
+// atoms for G <= 8, 384 KiB beyond.
 int solve_loop_signals(const DictView &d, const WorkView &w, int precision) {
   const bool half = is_half(precision);
   if (w.gram_dom || w.v0 || w.gram_fly || w.refactor || w.flag_ties || precision == OMP_PREC_FP64) return 0;
-  if (w.S > 64 || w.tile_cfg != 1 || w.B > 256 * LOOP_WAVES) return 0;
+  if (w.S > 64 || (w.tile_cfg != 1 && !half) || w.B > 256 * (half ? 32 : LOOP_WAVES)) return 0;
   const int G = (int)((w.B + 255) / 256);
   if (d.Mp > 1024 || d.N > 2048) return 0;
-  if (half ? d.N > 1024 && d.N * d.Mp * 2 > (int64_t)768 << 10 : d.N * G > 4096) return 0;
-  if (solve_lds_per_wave(w) * (size_t)G > LOOP_STAGE_BYTES) return 0;
-  return loop_lds(d.Mp, d.Np, G, half) + sizeof(uint64_t) * LOOP_WAVES * LOOP_WAVES <= LDS_LIMIT ? G : 0;
+  if (half ? d.N * d.Mp * 2 > (int64_t)(G > LOOP_WAVES ? 384 : 512) << 10 : d.N * G > 4096) return 0;
+  if (solve_lds_per_wave(w) * (size_t)LOOP_WAVES * (half && G > LOOP_WAVES ? 2 : 1) > LOOP_STAGE_BYTES) return 0;
+  return loop_lds(d.Mp, d.Np, G, half) + sizeof(uint64_t) * 4 * LOOP_WAVES * LOOP_WAVES <= LDS_LIMIT ? G : 0;
 }
 
 hipError_t launch_solve_loop(const DictView &d, const WorkView &w0, int precision, hipStream_t st) {
@@ -2867,15 +2874,19 @@ hipError_t launch_solve_loop(const DictView &d, const WorkView &w0, int precisio
   SlotView none;
   memset(&none, 0, sizeof(none));
   const size_t lds = loop_lds(d.Mp, d.Np, G, half);
-  auto kern = precision == OMP_PREC_BF16   ? k_solve_loop<OpBF16, true, 1>
-              : precision == OMP_PREC_FP16 ? k_solve_loop<OpF16, true, 1>
-              : G == 1                     ? k_solve_loop<OpF32, false, 1>
-              : G == 2                     ? k_solve_loop<OpF32, false, 2>
-              : G <= 4                     ? k_solve_loop<OpF32, false, 4>
-                                           : k_solve_loop<OpF32, false, 8>;
+  const bool wide = half && G > LOOP_WAVES;
+  auto kern = precision == OMP_PREC_BF16   ? wide ? k_solve_loop<OpBF16, true, 1, 2 * LOOP_WAVES, 1>
+                                                  : k_solve_loop<OpBF16, true, 1, LOOP_WAVES, LOOP_BUFS>
+              : precision == OMP_PREC_FP16 ? wide ? k_solve_loop<OpF16, true, 1, 2 * LOOP_WAVES, 1>
+                                                  : k_solve_loop<OpF16, true, 1, LOOP_WAVES, LOOP_BUFS>
+              : G == 1                     ? k_solve_loop<OpF32, false, 1, LOOP_WAVES, LOOP_BUFS>
+              : G == 2                     ? k_solve_loop<OpF32, false, 2, LOOP_WAVES, LOOP_BUFS>
+              : G <= 4                     ? k_solve_loop<OpF32, false, 4, LOOP_WAVES, LOOP_BUFS>
+                                           : k_solve_loop<OpF32, false, 8, LOOP_WAVES, LOOP_BUFS>;
   hipError_t e = allow_lds(kern, lds);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(kern, dim3((unsigned)((w.B + G - 1) / G)), dim3(64 * LOOP_WAVES), lds, st, d, w, none, G);
+  hipLaunchKernelGGL(kern, dim3((unsigned)((w.B + G - 1) / G)), dim3(64 * LOOP_WAVES * (wide ? 2 : 1)), lds, st, d, w,
+                     none, G);
   return hipGetLastError();
 }
 

@@ -10,7 +10,8 @@ pytestmark = pytest.mark.gpu
 @pytest.mark.parametrize("M,N,B,S,eps", [(1, 3, 4, 1, 0.0), (16, 32, 1, 5, 0.0), (31, 64, 256, 31, 0.0),
                                          (65, 65, 257, 12, 0.3), (100, 300, 37, 12, 0.1), (200, 513, 513, 64, 0.0),
                                          (64, 250, 1500, 9, 0.2), (256, 1024, 771, 40, 0.0), (129, 512, 2048, 20, 0.05),
-                                         (1000, 1024, 300, 33, 0.0), (60, 2048, 100, 16, 0.0)])
+                                         (200, 1024, 300, 33, 0.0), (60, 2048, 100, 16, 0.0),
+                                         (64, 1000, 4100, 8, 0.0), (30, 2048, 2049, 25, 0.1), (300, 301, 7937, 11, 0.2)])
 def test_loop_equals_steps_bit_for_bit(M, N, B, S, eps, prec):
     torch = pytest.importorskip("torch")
     if not torch.cuda.is_available():
