@@ -1452,8 +1452,18 @@ stop:
   stop_signal<SLOTS>(w, sv, b, stopfl, k, rn, lane);
 }
 
+// Wavefronts per SIMD the solve is compiled for: what the compiler reaches without scratch
+// memory, or with 12 bytes of it in the 16-bit form. Vector instructions filled 60% of the
+// cycles at four; 256 x 1024, S = 32, us: FP32 Gram form, B = 5000 13.5 at four, 11.5 at
+// six, BF16, B = 10,000 36.6 at four, 33.3 at five; six (76 bytes of scratch) and, for
+// FP32, eight (36) lose, as do the slot scheduler's and the register-residual 16-bit
+// variants at five.
+template <int RPL, bool BF16, bool SLOTS, bool RR>
+constexpr int SOLVE_OCC = RPL > 1 || (BF16 && (RR || SLOTS)) ? 1 : BF16 || RR ? 5 : 6;
+
 template <int RPL, bool BF16, bool SLOTS, bool RR, bool RRF = false>
-__global__ __launch_bounds__(64 * SOLVE_WAVES) void k_solve(DictView d, WorkView w, SlotView sv) {
+__global__ __launch_bounds__(64 * SOLVE_WAVES)
+    __attribute__((amdgpu_waves_per_eu(SOLVE_OCC<RPL, BF16, SLOTS, RR>))) void k_solve(DictView d, WorkView w, SlotView sv) {
   extern __shared__ float smem[];
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
   const int64_t b = (int64_t)blockIdx.x * (blockDim.x >> 6) + wv;  // blocks of solve_waves(w) wavefronts
