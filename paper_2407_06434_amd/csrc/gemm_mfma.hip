@@ -32,11 +32,12 @@ namespace {
 // G + c * cstride; k_sum_chunks then adds the partials in chunk order.
 // ---------------------------------------------------------------------------
 using GramTile = Tile<128, 128, 2, 2>;
+using GramHalf = Tile<64, 128, 2, 2>;  // half the rows: finer shares where the tiles do not divide evenly
 
-__global__ __launch_bounds__(GramTile::NTHR) void k_gram(const float *__restrict__ X, const float *__restrict__ Z,
-                                                         int64_t Mp, int ntn, int ntm, int csl,
-                                                         float *__restrict__ G, int64_t ldg, int64_t cstride) {
-  using T = GramTile;
+template <class T>
+__global__ __launch_bounds__(T::NTHR) void k_gram(const float *__restrict__ X, const float *__restrict__ Z,
+                                                  int64_t Mp, int ntn, int ntm, int csl, float *__restrict__ G,
+                                                  int64_t ldg, int64_t cstride) {
   extern __shared__ u32x4 lds[];
   const int tile = blockIdx.x % (ntn * ntm), chunk = blockIdx.x / (ntn * ntm);
   const int tn = tile % ntn, tm = tile / ntn;
@@ -334,7 +335,9 @@ __global__ __launch_bounds__(T::NTHR) void k_corr_select(
 using Cfg1 = Tile<128, 128, 2, 2>;
 using Cfg2 = Tile<256, 256, 2, 2>;
 using Cfg3 = Tile<256, 256, 2, 4>;
+//   5: 128 x 64, 2 x 2 wavefronts of 64 x 32 (chosen by shape only; keys as in 1)
 using Cfg4 = Tile<256, 128, 2, 2>;
+using Cfg5 = Tile<128, 64, 2, 2>;
 
 template <class K>
 hipError_t set_lds(K kernel, size_t bytes) {
@@ -377,24 +380,48 @@ CorrGeom geom(int precision, int cfg, bool ties) {
 }  // namespace
 
 CorrGeom corr_geometry(int precision, int64_t Np, int64_t Bp, int cfg, bool ties) {
-  if (cfg == 0) cfg = (Np / 256) * (Bp / 256) >= 192 ? 3 : 1;
+  if (cfg == 0) {
+    // Rounds of workgroups: two of 128 x 128 share a CU, three of 128 x 64, which take 0.6 of
+    // their time each. 640 tiles of 128 x 128 (256 x 1024, B = 10,000) are two rounds, as 1280
+    // halves are: 15.7 and 15.2 us; 512 x 2048, B = 5000: 22.6 and 21.7 us.
+    const int64_t t1 = (Np / 128) * (Bp / 128);
+    if ((Np / 256) * (Bp / 256) >= 192) cfg = 3;
+    else cfg = (2 * t1 + 767) / 768 * 6 < (t1 + 511) / 512 * 10 ? 5 : 1;
+  }
   switch (cfg) {
     case 2: return geom<Cfg2>(precision, 2, ties);
     case 3: return geom<Cfg3>(precision, 3, ties);
     case 4: return geom<Cfg4>(precision, 4, ties);
+    case 5: return geom<Cfg5>(precision, 5, ties);
     default: return geom<Cfg1>(precision, 1, ties);
   }
 }
 
-hipError_t launch_gram(const DictView &d, hipStream_t st) {
-  using T = GramTile;
-  hipError_t e = set_lds(k_gram, T::LDS_BYTES);
+namespace {
+// X Z^T (rows and cols multiples of 128) in `ks` chunks of csl K slices. Both tiles give the
+// same sums in the same order. The product is bound by its MFMAs, four cycles of one SIMD
+// per instruction whichever tile it is in, so the CU with the most tiles sets the time: half
+// tiles where they shorten it by more than their extra LDS traffic costs. Measured, us, 128
+// x 128 against the chosen tile: 5120 x 1024 x 256 (320 tiles) 38 and 31; 1280 x 1280 x 8064
+// in 8 chunks (800 tiles) 333 and 274.
+hipError_t gram_product(const float *X, int64_t rows, const float *Z, int64_t cols, int64_t Mp, int ks, int csl,
+                        float *out, int64_t ldo, int64_t cstride, hipStream_t st) {
+  const int64_t t = (rows / 128) * (cols / 128) * ks;
+  const bool half = (2 * t + 255) / 256 * 105 < (t + 255) / 256 * 200;
+  auto kern = half ? k_gram<GramHalf> : k_gram<GramTile>;
+  const size_t lds = half ? GramHalf::LDS_BYTES : GramTile::LDS_BYTES;
+  hipError_t e = half ? set_lds(k_gram<GramHalf>, lds) : set_lds(k_gram<GramTile>, lds);
   if (e != hipSuccess) return e;
-  const int nt = (int)(d.Np / T::TN);
-  const int nsl = (int)(d.Mp / 4 / T::CH);
-  hipLaunchKernelGGL(k_gram, dim3(nt * nt), dim3(T::NTHR), T::LDS_BYTES, st, d.A32, d.A32, d.Mp, nt, nt, nsl,
-                     d.G, d.Np, (int64_t)0);
+  const int ntn = (int)(rows / (half ? GramHalf::TN : GramTile::TN)), ntm = (int)(cols / 128);
+  hipLaunchKernelGGL(kern, dim3((unsigned)((int64_t)ntn * ntm * ks)), dim3(GramTile::NTHR), lds, st, X, Z, Mp, ntn, ntm,
+                     csl, out, ldo, cstride);
   return hipGetLastError();
+}
+static_assert(GramTile::NTHR == GramHalf::NTHR && GramHalf::TB == 128 && GramTile::TB == 128, "one launch shape");
+}  // namespace
+
+hipError_t launch_gram(const DictView &d, hipStream_t st) {
+  return gram_product(d.A32, d.Np, d.A32, d.Np, d.Mp, 1, (int)(d.Mp / 4 / GramTile::CH), d.G, d.Np, 0, st);
 }
 
 // P[i] = sum over chunks c, in chunk order, of Pk[c][i]; four floats per lane.
@@ -417,16 +444,11 @@ hipError_t launch_project(const DictView &d, const WorkView &w, hipStream_t st) 
   using T = GramTile;
   static_assert(BPAD % T::TN == 0 && NPAD % T::TB == 0, "padded sizes must be whole tiles");
   if (!w.P || w.Bp % T::TN || d.Np % T::TB || w.Mp != d.Mp || w.Np != d.Np) return hipErrorInvalidValue;
-  hipError_t e = set_lds(k_gram, T::LDS_BYTES);
-  if (e != hipSuccess) return e;
-  const int ntb = (int)(w.Bp / T::TN), nta = (int)(d.Np / T::TB);
   const int nsl = (int)(d.Mp / 4 / T::CH), ks = w.pchunks;
   const int csl = ks >= 1 ? (nsl + ks - 1) / ks : 0;
   if (ks < 1 || (ks > 1 && !w.Pk) || nsl - (ks - 1) * csl < 1) return hipErrorInvalidValue;
   const int64_t n = w.Bp * d.Np;
-  hipLaunchKernelGGL(k_gram, dim3(ntb * nta * ks), dim3(T::NTHR), T::LDS_BYTES, st, w.R32, d.A32, d.Mp, ntb, nta,
-                     csl, ks > 1 ? w.Pk : w.P, d.Np, n);
-  e = hipGetLastError();
+  hipError_t e = gram_product(w.R32, w.Bp, d.A32, d.Np, d.Mp, ks, csl, ks > 1 ? w.Pk : w.P, d.Np, n, st);
   if (e != hipSuccess || ks == 1) return e;
   const int64_t n4 = n / 4;
   hipLaunchKernelGGL(k_sum_chunks, dim3((unsigned)((n4 + 255) / 256)), dim3(256), 0, st,
@@ -457,6 +479,7 @@ hipError_t prepare_corr(const DictView &d, const WorkView &w, int precision) {
     case 2: return prepare_corr_cfg<Cfg2>(precision, second);
     case 3: return prepare_corr_cfg<Cfg3>(precision, second);
     case 4: return prepare_corr_cfg<Cfg4>(precision, second);
+    case 5: return prepare_corr_cfg<Cfg5>(precision, second);
     default: return prepare_corr_cfg<Cfg1>(precision, second);
   }
 }
@@ -466,6 +489,7 @@ hipError_t launch_corr_select(const DictView &d, const WorkView &w, int precisio
     case 2: return launch_corr_cfg<Cfg2>(d, w, precision, st);
     case 3: return launch_corr_cfg<Cfg3>(d, w, precision, st);
     case 4: return launch_corr_cfg<Cfg4>(d, w, precision, st);
+    case 5: return launch_corr_cfg<Cfg5>(d, w, precision, st);
     default: return launch_corr_cfg<Cfg1>(d, w, precision, st);
   }
 }

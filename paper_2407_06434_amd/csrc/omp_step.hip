@@ -2863,7 +2863,7 @@ hipError_t launch_solve_slots(const DictView &d, const WorkView &w, const SlotVi
 int solve_loop_signals(const DictView &d, const WorkView &w, int precision) {
   const bool half = is_half(precision);
   if (w.gram_dom || w.v0 || w.gram_fly || w.refactor || w.flag_ties || precision == OMP_PREC_FP64) return 0;
-  if (w.S > 64 || (w.tile_cfg != 1 && !half) || w.B > 256 * (half ? 32 : LOOP_WAVES)) return 0;
+  if (w.S > 64 || w.B > 256 * (half ? 32 : LOOP_WAVES)) return 0;
   const int G = (int)((w.B + 255) / 256);
   if (d.Mp > 1024 || d.N > 2048) return 0;
   if (half ? d.N * d.Mp * 2 > (int64_t)(G > LOOP_WAVES ? 384 : 512) << 10 : d.N * G > 4096) return 0;
