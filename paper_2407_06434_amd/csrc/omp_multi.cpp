@@ -376,6 +376,22 @@ int validate(const omp_problem_t *probs, int nprob, const omp_multi_opts_t *opts
   return OMP_OK;
 }
 
+// The caller's problems with the default slots filled in: 8192, or the former 4096 where
+// the workspace holds only those.
+int with_default_slots(const omp_problem_t *probs, int nprob, const omp_multi_opts_t *opts, omp_problem_t *out) {
+  if (!probs || !opts || nprob < 1 || nprob > OMP_MAX_PROBLEMS) return OMP_EINVAL;
+  if (opts->precision != OMP_PREC_FP32 && !is_half(opts->precision)) return OMP_EINVAL;
+  for (int p = 0; p < nprob; ++p) {
+    const int rc = check_problem(probs[p], opts->precision);
+    if (rc != OMP_OK) return rc;
+    out[p] = probs[p];
+  }
+  if (opts->workspace_bytes < total_bytes(probs, nprob, opts->precision))
+    for (int p = 0; p < nprob; ++p)
+      if (out[p].slots == 0) out[p].slots = 4096;
+  return OMP_OK;
+}
+
 }  // namespace
 
 hipError_t graph_launch_cached(const std::string &key, const std::function<hipError_t(hipStream_t)> &body,
@@ -404,8 +420,10 @@ size_t omp_multi_workspace_size(const omp_problem_t *probs, int32_t nprob, const
   return total_bytes(probs, nprob, opts->precision);
 }
 
-int omp_solve_multi(const omp_problem_t *probs, int32_t nprob, const omp_multi_opts_t *opts, void *stream) {
-  int rc = validate(probs, nprob, opts);
+int omp_solve_multi(const omp_problem_t *caller_probs, int32_t nprob, const omp_multi_opts_t *opts, void *stream) {
+  omp_problem_t probs[OMP_MAX_PROBLEMS];
+  int rc = with_default_slots(caller_probs, nprob, opts, probs);
+  if (rc == OMP_OK) rc = validate(probs, nprob, opts);
   if (rc != OMP_OK) return rc;
   bool any = false;
   for (int p = 0; p < nprob; ++p) any |= probs[p].B > 0;
@@ -421,7 +439,9 @@ int omp_solve_multi(const omp_problem_t *probs, int32_t nprob, const omp_multi_o
 }
 
 int omp_tune(omp_problem_t *probs, int32_t nprob, const omp_multi_opts_t *opts, int64_t sample, void *stream) {
-  int rc = validate(probs, nprob, opts);
+  omp_problem_t checked[OMP_MAX_PROBLEMS];
+  int rc = with_default_slots(probs, nprob, opts, checked);
+  if (rc == OMP_OK) rc = validate(checked, nprob, opts);
   if (rc != OMP_OK) return rc;
   if (sample < 0) return OMP_EINVAL;
   rc = check_device();

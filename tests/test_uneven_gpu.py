@@ -154,3 +154,25 @@ def test_slots_with_large_support():
     for prec in ("fp32", "bf16"):
         outs = omp.solve_multi(_problems([w], prec, dense=True, slots=256), precision=prec)
         _same(_to_np(outs[0]), _plain(w, prec), keys=("support", "coef", "status", "rnorm", "X"))
+
+
+def test_default_slots_in_a_workspace_of_the_former_default():
+    """A problem with slots = 0 in a workspace that holds 4096 slots, the default before it
+    was 8192, runs with these and gives the same results."""
+    import ctypes
+    torch = _torch()
+    from paper_2407_06434_amd import omp
+    g = torch.Generator(device="cuda").manual_seed(5)
+    A = torch.randn((300, 100), generator=g, device="cuda")
+    Y = torch.randn((5000, 100), generator=g, device="cuda")
+    d = omp.Dictionary(A, "bf16")
+    print("case default slots B=5000", flush=True)
+    want = [t.clone() for t in omp.solve_multi([omp.Problem(d, Y, 9)], "bf16")[0][1:]]
+    small = omp.Problem(d, Y, 9, slots=4096)
+    lib, arr, o, dev, ws = omp._multi_call([small], "bf16", 0, None)
+    arr[0].slots = 0
+    assert lib.omp_multi_workspace_size(arr, 1, ctypes.byref(o)) > ws.numel()
+    rc = lib.omp_solve_multi(arr, 1, ctypes.byref(o), None)
+    torch.cuda.synchronize()
+    assert rc == omp.OMP_OK
+    assert all(torch.equal(a, b) for a, b in zip(want, small.out[1:]))
