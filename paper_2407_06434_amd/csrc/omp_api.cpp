@@ -85,16 +85,17 @@ WorkLayout work_layout(int64_t M, int64_t N, int64_t B, int S, int precision, in
   const size_t Bp = (size_t)L.Bp, Sz = (size_t)S;
   Carve c;
   L.Yp = c.take<float>(Bp * L.Mp);
-  L.R32 = gram_dom ? L.Yp : c.take<float>(Bp * L.Mp);  // Gram-domain form: y itself, there is no residual
+  L.R32 = c.take<float>(Bp * L.Mp);
   L.R16 = is_half(precision) ? c.take<uint16_t>(Bp * L.Mp) : 0;
   L.rscale = precision == OMP_PREC_FP16 ? c.take<float>(Bp) : 0;
   L.rscale_next = precision == OMP_PREC_FP16 ? c.take<float>(Bp) : 0;
-  // (the Gram-domain select writes one key per signal and atom slice or panel, two with
-  // near-tie flagging; v0 two keys, the FP64 form two (score, index) pairs of doubles)
+  // (the Gram-domain select writes one key per signal and atom slice, two with near-tie
+  // flagging; v0 two keys, the FP64 form two (score, index) pairs of doubles)
   L.gpanel = gram_dom && gram_panels(B, L.Mp, L.Np, ties) ? 1 : 0;
   L.gkeys = L.gpanel ? (int)(L.Np / GPANEL) : GSLICE;
   L.part = c.take<uint64_t>(Bp * (size_t)std::max<int64_t>((int64_t)L.ntile * L.g.keys_per_tile,
-                                                            gram_dom ? L.gkeys * (ties ? 2 : 1) : 4));
+                                                            gram_dom ? GSLICE * (ties ? 2 : 1) : 4));
+  if (L.gpanel) L.part = L.R32;  // a key per panel: over y's copy, which only the projection reads
   L.mask = c.take<uint32_t>(Bp * (L.Np / 32));
   L.k = c.take<int32_t>(Bp);
   L.flags = c.take<int32_t>(Bp);
@@ -399,6 +400,8 @@ int omp_dict_init(omp_dict_t *dict, const float *A, int64_t M, int64_t N, int64_
 // dictionary at most four times wider than long (4M >= N), tall ones included,
 // except dictionaries under 1 MiB in FP32 in batches of more than 4096 signals,
 // where the residual-vector form (its residual formed in the solve) is faster.
+// (Measured before the select kept panels of G in LDS; with them this form is faster there
+// too, but the two forms round differently, so the line stays and no call changes its form.)
 static bool gram_domain_form(int32_t mode, int prec, int64_t M, int64_t N, int64_t B) {
   if (mode == 1) return true;
   if (mode != 2 || prec != OMP_PREC_FP32) return false;

@@ -129,8 +129,8 @@ constexpr int GSLICE = 8;
 // and 94 at B = 512, 485 and 223 at B = 10,000; 256 x 1024, S = 32: 467 and 392 at B = 512,
 // 2876 and 1660 at B = 10,000. Panels of 16 columns for wider dictionaries lose (512 x
 // 2048, S = 32, B = 5000: 1857 against 2223), as every panel walks over all signals.
-// A panel gives a key per signal, and the keys must fit in the space of the residual copy
-// that this form does not keep, so that no workspace grows.
+// A panel gives a key per signal, and the keys must fit over the copy of y that only the
+// projection reads (R32), so that no workspace grows.
 constexpr int GPANEL = 32;
 inline bool gram_panels(int64_t B, int64_t Mp, int64_t Np, bool ties) {
   return Np <= 1024 && B >= 512 && Np / GPANEL * 8 * (ties ? 2 : 1) <= 4 * Mp;
