@@ -2461,7 +2461,8 @@ __global__ __launch_bounds__(V0_THREADS) void k_v0_solve64(DictView d, WorkView 
 template <int SM, int NTMAX>
 __global__ __launch_bounds__(NTMAX) void k_v0_reg64(DictView d, WorkView w) {
   extern __shared__ double F[];  // packed by columns: column k at k (k + 1) / 2
-  __shared__ double zs[SM], us[SM], xs[SM], cstar, part[16];
+  static_assert(NPAD >= V0_THREADS, "a workgroup has the threads that sum the residual");
+  __shared__ double zs[SM], us[SM], xs[SM], cstar, part[V0_THREADS / 64];
   __shared__ uint64_t rkey[2][16];
   __shared__ int rn_[2][16], ss[SM];
   const int64_t b = blockIdx.x, Np = d.Np;
@@ -2518,7 +2519,9 @@ __global__ __launch_bounds__(NTMAX) void k_v0_reg64(DictView d, WorkView w) {
     }
     __syncthreads();
     const double zl = lane < k ? zs[lane < SM ? lane : 0] : 0.0;
-    const double d2 = nu2 - wave_sum(zl * zl);
+    // (an explicit FMA with zero, v0_step64's only term: the bare product would be contracted
+    // into wave_sum's first addition, and every later value would differ in its last bits)
+    const double d2 = nu2 - wave_sum(fma(zl, zl, 0.0));
     if (!(d2 > DEP_TOL2 * nu2)) {  // dependent atom: stop without appending
       fl |= FLAG_DONE | OMP_SIG_DEPENDENT;
       break;
@@ -2560,18 +2563,23 @@ __global__ __launch_bounds__(NTMAX) void k_v0_reg64(DictView d, WorkView w) {
         xs[i] = acc;
       }
       __syncthreads();
-      const float *yb = w.Yp + b * w.Mp;
-      double acc = 0.0;
-      for (int64_t m = tid; m < d.M; m += Np) {
-        double rm = (double)yb[m];
-        for (int j = 0; j < K; ++j) rm -= xs[j] * (double)d.A32[(int64_t)ss[j] * d.Mp + m];
-        acc += rm * rm;
+      // over the first V0_THREADS threads, as v0_step64 sums it: at the noise floor another
+      // order would give other bits of ||r||, and so other stops near eps
+      if (tid < V0_THREADS) {
+        const float *yb = w.Yp + b * w.Mp;
+        double acc = 0.0;
+        for (int64_t m = tid; m < d.M; m += V0_THREADS) {
+          double rm = (double)yb[m];
+          for (int j = 0; j < K; ++j) rm -= xs[j] * (double)d.A32[(int64_t)ss[j] * d.Mp + m];
+          acc += rm * rm;
+        }
+        acc = wave_sum(acc);
+        if (lane == 0) part[wv] = acc;
       }
-      acc = wave_sum(acc);
-      if (lane == 0) part[wv] = acc;
       __syncthreads();
       r2 = 0.0;
-      for (int i = 0; i < nw; ++i) r2 += part[i];
+#pragma unroll
+      for (int i = 0; i < V0_THREADS / 64; ++i) r2 += part[i];
     }
     if (K >= Sb) {
       fl |= FLAG_DONE;

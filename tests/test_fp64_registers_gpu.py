@@ -37,3 +37,25 @@ def test_registers_equal_memory_bit_for_bit(M, N, B, S, eps, ties):
         assert torch.equal(a[1:], b[1:])
     assert torch.equal(whole.support[0, :2].sort().values, parts.support[0, :2].sort().values)
     assert torch.allclose(whole.rnorm[1:], parts.rnorm[1:], rtol=1e-6, atol=0.0)
+
+
+@pytest.mark.parametrize("M,N,B,S", [(16, 30, 37, 16), (30, 600, 50, 30), (64, 256, 40, 60), (100, 900, 33, 32),
+                                     (300, 500, 20, 64)])
+def test_residual_norms_bit_for_bit(M, N, B, S):
+    """Both paths give the same norms for every signal, also where they are rounding noise
+    (S = M, or signals that 5 atoms explain: there a stop near eps hangs on the last bits)."""
+    torch = pytest.importorskip("torch")
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2407_06434_amd import omp
+    g = np.random.default_rng(M + N)
+    A = (g.normal(size=(N, M)) / np.sqrt(M)).astype(np.float32)
+    Y = g.normal(size=(B, M)).astype(np.float32)
+    Y[: B // 3] = A[np.argsort(g.random((B // 3, N)), axis=1)[:, :5]].sum(axis=1)
+    At, Yt = torch.from_numpy(A).cuda(), torch.from_numpy(Y).cuda()
+    d = omp.Dictionary(At, "fp64")
+    print(f"case fp64 norms M={M} N={N} B={B} S={S}", flush=True)
+    for eps in (0.0, 1e-7, 0.3):
+        whole, parts = (omp.solve(At, Yt, S, eps, precision="fp64", dictionary=d, timing=t) for t in (None, {}))
+        for k in ("support", "status", "coef", "rnorm", "X"):
+            assert torch.equal(getattr(whole, k), getattr(parts, k)), (eps, k)
