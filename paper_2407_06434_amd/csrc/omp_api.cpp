@@ -77,7 +77,7 @@ WorkLayout work_layout(int64_t M, int64_t N, int64_t B, int S, int precision, in
   L.Mp = round_up(M, KPAD);
   L.Np = round_up(N, NPAD);
   L.Bp = round_up(B > 0 ? B : 1, BPAD);
-  L.g = corr_geometry(precision, L.Np, L.Bp, cfg, ties);
+  L.g = corr_geometry(precision, L.Mp, L.Np, L.Bp, cfg, ties);
   L.ntile = (int)(L.Np / L.g.tile_atoms);
   // Slice the residual over the XCDs when the FP32 dictionary outgrows one L2.
   L.nslice = (L.Np * L.Mp * 4 > (int64_t)2 << 20) ? NSLICE_MAX : 1;

@@ -299,15 +299,15 @@ constexpr int NKEEP = 3;
 //         Key slot in the tile: ((wn * subs_per_half + ig) * 2 + h) * NKEEP + {0..NKEEP-1};
 //         atom: t*tile_atoms + wn*wave_atoms + 32 (ig*sub_frags + i') + 8 g + 4 h + e.
 struct CorrGeom {
-  int cfg;  // tile configuration 1..4 (see the correlation kernels)
+  int cfg;  // tile configuration 1..5 (see the correlation kernels)
   int tile_atoms, tile_signals;
   int keys_per_tile;
   int wave_atoms;
   int sub_frags;
   int subs_per_half;
 };
-// cfg 0 picks by shape: 256 x 256 tiles when that still gives about one tile per CU.
+// cfg 0 picks by shape, 5 (128 x 64) among others; a caller names 1..MAX_TILE_CFG.
 // `ties`: the FP32 epilogue writes two keys per (signal, tile), best and second best.
-CorrGeom corr_geometry(int precision, int64_t Np, int64_t Bp, int cfg, bool ties = false);
+CorrGeom corr_geometry(int precision, int64_t Mp, int64_t Np, int64_t Bp, int cfg, bool ties = false);
 
 }  // namespace bomp
