@@ -2868,12 +2868,19 @@ hipError_t launch_solve_slots(const DictView &d, const WorkView &w, const SlotVi
 // 620 and 520, B = 4000 830 and 888; 512 x 1024: B = 1500 804 and 816; 256 x 1500: B = 500
 // 624 and 622; 128 x 1500, S = 16: B = 5000 572 and 447. Hence up to 512 KiB of 16-bit
 // atoms for G <= 8, 384 KiB beyond.
+// Every workgroup reads all of A at each step, so A must fit an XCD's L2 (4 MiB in FP32, the
+// size up to which the steps form the residual in the solve, too): FP32, S = 16, steps
+// against one launch: 1024 x 2048 B = 16 1310 and 1390, B = 512 1402 and 1474; 1000 x 1000 B =
+// 512 2095 and 1279 (S = 24). Wide dictionaries lose where the steps spread the atoms over
+// more CUs than there are signals, or two signals share a CU: 512 x 2000, FP32, B = 400
+// 785 and 771, B = 512 794 and 808; 128 x 2000, BF16, B = 4 260 and 269, B = 64 278 and 264.
 int solve_loop_signals(const DictView &d, const WorkView &w, int precision) {
   const bool half = is_half(precision);
   if (w.gram_dom || w.v0 || w.gram_fly || w.refactor || w.flag_ties || precision == OMP_PREC_FP64) return 0;
   if (w.S > 64 || w.B > 256 * (half ? 32 : LOOP_WAVES)) return 0;
   const int G = (int)((w.B + 255) / 256);
-  if (d.Mp > 1024 || d.N > 2048) return 0;
+  if (d.Mp > 1024 || d.N > 2048 || d.Mp * d.Np * 4 > (int64_t)4 << 20) return 0;
+  if (d.N > 1536 && (half ? d.Mp > 64 && w.B < 16 : d.Mp >= 512 && G > 1)) return 0;
   if (half ? d.N * d.Mp * 2 > (int64_t)(G > LOOP_WAVES ? 384 : 512) << 10 : d.N * G > 4096) return 0;
   if (solve_lds_per_wave(w) * (size_t)LOOP_WAVES * (half && G > LOOP_WAVES ? 2 : 1) > LOOP_STAGE_BYTES) return 0;
   return loop_lds(d.Mp, d.Np, G, half) + sizeof(uint64_t) * 4 * LOOP_WAVES * LOOP_WAVES <= LDS_LIMIT ? G : 0;

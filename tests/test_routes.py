@@ -63,3 +63,19 @@ def test_half_tiles_only_where_they_relieve_the_fullest_cu(routes):
             assert cfg == (5 if most_half < 2 * most_whole else 1), (p, M, N, B, t)
     assert [c for c, _ in routes([("bf16", 1024, 1024, 11000, 12), ("bf16", 2500, 2304, 5120, 12),
                                   ("bf16", 256, 1024, 9984, 12)])] == [1, 1, 5]
+
+
+def test_one_launch_solve_where_it_is_the_faster_one(routes):
+    """The one-launch solve has every workgroup read the whole dictionary at each step: not
+    beyond 4 MiB in FP32 (up to 7% slower than the steps at 1024 x 2048), nor over wide
+    dictionaries with fewer signals than CUs would share their atoms."""
+    yes = [("fp32", 1000, 1000, 1, 24), ("fp32", 1000, 1000, 1024, 24), ("fp32", 512, 2048, 256, 24),
+           ("fp32", 256, 2048, 512, 24), ("fp32", 64, 256, 100, 8), ("fp32", 1024, 200, 1500, 24),
+           ("bf16", 256, 1000, 1, 20), ("bf16", 64, 2000, 1, 16), ("fp16", 128, 2000, 64, 20), ("bf16", 60, 100, 8192, 20)]
+    no = [("fp32", 1024, 2048, 1, 24), ("fp32", 1024, 2048, 512, 24), ("fp32", 900, 1900, 256, 24),
+          ("fp32", 512, 2000, 300, 16), ("bf16", 128, 2000, 1, 20), ("fp16", 128, 2000, 15, 16),
+          ("fp32", 256, 1024, 2049, 24), ("bf16", 1000, 500, 40, 20), ("fp64", 64, 256, 100, 8)]
+    got = [g for _, g in routes(yes + no)]
+    for case, g in zip(yes + no, got):
+        assert (g > 0) == (case in yes), (case, g)
+        assert g in (0, -(-case[3] // 256)), (case, g)
