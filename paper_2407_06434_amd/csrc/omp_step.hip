@@ -1023,11 +1023,12 @@ __device__ __attribute__((always_inline)) inline void solve_step(const DictView 
         if (64 * j >= nkeys) break;  // wave-uniform: no load and no work for groups without keys
         const int t = 64 * j + lane;
         kv[j] = keys[t < nkeys ? t : 0];
-        if (64 * j + 64 > nkeys) kv[j] = t < nkeys ? kv[j] : 0x80000000u;
       }
+      // (looked at only here: a use beside the load would wait for each group in turn)
 #pragma unroll
       for (int j = 0; j < KREG; ++j) {
         if (64 * j >= nkeys) break;
+        if (64 * j + 64 > nkeys) kv[j] = 64 * j + lane < nkeys ? kv[j] : 0x80000000u;
         hmax = max(hmax, key_valid(kv[j]) ? (kv[j] & ~31u) | 1u : 0u);
       }
     } else {
