@@ -50,13 +50,42 @@ struct Plan {
   float *coef;
 };
 
+// Whether a problem does better with 8192 slots (two turns of the solve on the chip) than
+// with 4096. It does where an iteration then costs little more: the batch needs fewer
+// iterations, and the last signals' iterations, which run nearly empty, weigh less. It does
+// not where the product sets the iteration's time, as those last iterations then take twice
+// as long: FP32 beyond 192 Ki dictionary entries (dictionaries of one 256-atom block aside,
+// whose product is small), and more than 2048 atoms in any precision; nor where wide
+// dictionaries meet batches that would fill the slots just once. Signals that end at 1 .. S
+// (u) or all at S (f), 4096 against 8192 slots, ms:
+//   FP32  64 x 256, S = 32, B = 20,000 u    2.80  2.05     128 x 768, S = 32, B = 10,000 u    2.21  1.93
+//         200 x 768, S = 32, B = 6500 u     1.94  1.78     1000 x 100, S = 32, B = 10,000 u   3.93  2.89
+//         256 x 1024, S = 32, B = 10,000 u  2.49  2.57     512 x 2048, S = 32, B = 10,000 u   5.80  6.42
+//         1024 x 4096, S = 32, B = 5000 u   11.4  17.2     512 x 4096, S = 32, B = 20,000 f   26.1  29.4
+//         64 x 2048, S = 8, B = 6500 u      0.647 0.666    64 x 2048, S = 8, B = 10,000 u     0.868 0.843
+//   BF16  256 x 1024, S = 32, B = 10,000 f  3.95  3.38     512 x 2048, S = 32, B = 6500 f     3.49  2.60
+//         1024 x 2048, S = 8, B = 20,000 u  2.79  2.30     512 x 4096, S = 32, B = 5000 u     2.39  2.88
+//         256 x 2048, S = 8, B = 5000 u     0.531 0.581    256 x 2048, S = 32, B = 6500 u     1.73  1.59
+//   FP16  1024 x 2500, S = 32, B = 10,000 u 4.74  5.17     1024 x 4096, S = 32, B = 10,000 u  5.10  5.68
+bool wants_8192_slots(const omp_problem_t &p) {
+  const int64_t Mp = round_up(p.dict->M, KPAD), Np = round_up(p.dict->N, NPAD);
+  const bool half = is_half(p.dict->precision);
+  if (Np > 2048 || (!half && Np > 256 && Mp * Np > 192 << 10)) return false;
+  return Np < 1024 || p.B >= (half && Mp > 64 ? 6144 : 8192);
+}
+
+// Writes the slots of the problems that name none into `probs`: 8192, or 4096 where one of
+// them does better with these (the problems' iterations run side by side, so the others'
+// additional slots would only slow that one down) or `most` says so.
+void fill_slots(omp_problem_t *probs, int nprob, int most) {
+  for (int p = 0; p < nprob; ++p)
+    if (probs[p].slots == 0 && probs[p].B > 0 && !wants_8192_slots(probs[p])) most = 4096;
+  for (int p = 0; p < nprob; ++p)
+    if (probs[p].slots == 0) probs[p].slots = most;
+}
+
 int64_t plan_slots(const omp_problem_t &p) {
-  // Default: 8192 slots (two turns of the solve on the chip). An iteration costs little more than
-  // with half as many, the batch needs fewer of them, and the last signals' iterations, which
-  // run nearly empty, weigh less. Slots, ms: 2 x 10,000 signals of 128 x 512 and 512 x 2048, BF16,
-  // 2048: 9.37, 4096: 7.50, 8192: 7.28; 800 + 6000 signals in FP32, 4096: 3.82, 8192: 3.20; 9000
-  // + 2000 at S = 16 in BF16, 4096: 1.32, 8192: 1.05.
-  const int64_t want = p.slots > 0 ? p.slots : 8192;
+  const int64_t want = p.slots > 0 ? p.slots : 4096;  // (fill_slots has filled it in but for checks)
   return round_up(std::max<int64_t>(1, std::min<int64_t>(want, p.B)), BPAD);
 }
 
@@ -376,19 +405,20 @@ int validate(const omp_problem_t *probs, int nprob, const omp_multi_opts_t *opts
   return OMP_OK;
 }
 
-// The caller's problems with the default slots filled in: 8192, or the former 4096 where
-// the workspace holds only those.
-int with_default_slots(const omp_problem_t *probs, int nprob, const omp_multi_opts_t *opts, omp_problem_t *out) {
+// The caller's problems, checked and with their slots; 4096 by default where the workspace
+// holds no more (4096 was every problem's default before).
+int with_slots(const omp_problem_t *probs, int nprob, const omp_multi_opts_t *opts, omp_problem_t *out) {
   if (!probs || !opts || nprob < 1 || nprob > OMP_MAX_PROBLEMS) return OMP_EINVAL;
   if (opts->precision != OMP_PREC_FP32 && !is_half(opts->precision)) return OMP_EINVAL;
   for (int p = 0; p < nprob; ++p) {
     const int rc = check_problem(probs[p], opts->precision);
     if (rc != OMP_OK) return rc;
-    out[p] = probs[p];
   }
-  if (opts->workspace_bytes < total_bytes(probs, nprob, opts->precision))
-    for (int p = 0; p < nprob; ++p)
-      if (out[p].slots == 0) out[p].slots = 4096;
+  for (int most : {8192, 4096}) {
+    std::copy(probs, probs + nprob, out);
+    fill_slots(out, nprob, most);
+    if (opts->workspace_bytes >= total_bytes(out, nprob, opts->precision)) break;
+  }
   return OMP_OK;
 }
 
@@ -415,14 +445,18 @@ extern "C" {
 size_t omp_multi_workspace_size(const omp_problem_t *probs, int32_t nprob, const omp_multi_opts_t *opts) {
   if (!probs || !opts || nprob < 1 || nprob > OMP_MAX_PROBLEMS) return 0;
   if (opts->precision != OMP_PREC_FP32 && !is_half(opts->precision)) return 0;
-  for (int p = 0; p < nprob; ++p)
+  omp_problem_t filled[OMP_MAX_PROBLEMS];
+  for (int p = 0; p < nprob; ++p) {
     if (check_problem(probs[p], opts->precision) != OMP_OK) return 0;
-  return total_bytes(probs, nprob, opts->precision);
+    filled[p] = probs[p];
+  }
+  fill_slots(filled, nprob, 8192);
+  return total_bytes(filled, nprob, opts->precision);
 }
 
 int omp_solve_multi(const omp_problem_t *caller_probs, int32_t nprob, const omp_multi_opts_t *opts, void *stream) {
   omp_problem_t probs[OMP_MAX_PROBLEMS];
-  int rc = with_default_slots(caller_probs, nprob, opts, probs);
+  int rc = with_slots(caller_probs, nprob, opts, probs);
   if (rc == OMP_OK) rc = validate(probs, nprob, opts);
   if (rc != OMP_OK) return rc;
   bool any = false;
@@ -440,7 +474,7 @@ int omp_solve_multi(const omp_problem_t *caller_probs, int32_t nprob, const omp_
 
 int omp_tune(omp_problem_t *probs, int32_t nprob, const omp_multi_opts_t *opts, int64_t sample, void *stream) {
   omp_problem_t checked[OMP_MAX_PROBLEMS];
-  int rc = with_default_slots(probs, nprob, opts, checked);
+  int rc = with_slots(probs, nprob, opts, checked);
   if (rc == OMP_OK) rc = validate(checked, nprob, opts);
   if (rc != OMP_OK) return rc;
   if (sample < 0) return OMP_EINVAL;

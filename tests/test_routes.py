@@ -1,5 +1,6 @@
 """Which kernels a call is sent to, where a rule by sizes decides it: the library's own host
 functions, called from a small C++ program built here (CPU only, nothing is launched)."""
+import ctypes
 import os
 import subprocess
 
@@ -79,3 +80,38 @@ def test_one_launch_solve_where_it_is_the_faster_one(routes):
     for case, g in zip(yes + no, got):
         assert (g > 0) == (case in yes), (case, g)
         assert g in (0, -(-case[3] // 256)), (case, g)
+
+
+def test_default_slots_by_the_work_of_an_iteration():
+    """Problems that name no slots get 8192 only where an iteration over them costs little
+    more than over 4096: an FP32 product over 1024 x 4096 made that default up to half as
+    slow again. Read off the workspace the problems ask for."""
+    from paper_2407_06434_amd import omp
+    lib = omp.load()
+    o = omp.OmpMultiOptsStruct()
+
+    def size(prec, shapes, slots):
+        arr = (omp.OmpProblemStruct * len(shapes))()
+        keep = []
+        for p, (M, N, B) in zip(arr, shapes):
+            d = omp.OmpDictStruct(0x4F4D5044, PREC[prec], M, N, 0, 0, 1 << 20, 1 << 20, 1 << 40)
+            keep.append(d)
+            p.dict = ctypes.pointer(d)
+            p.Y = p.support_out = 1 << 20
+            p.B, p.ldy, p.S, p.slots = B, M, 16, slots
+        o.precision = PREC[prec]
+        return lib.omp_multi_workspace_size(arr, len(shapes), ctypes.byref(o))
+
+    for prec, M, N, B, slots in (
+            ("fp32", 64, 256, 5000, 8192), ("fp32", 128, 768, 20000, 8192), ("fp32", 200, 768, 20000, 8192),
+            ("fp32", 1000, 100, 20000, 8192), ("fp32", 256, 1024, 20000, 4096), ("fp32", 512, 2048, 20000, 4096),
+            ("fp32", 1024, 4096, 5000, 4096), ("fp32", 32, 4096, 20000, 4096), ("fp32", 64, 2048, 6500, 4096),
+            ("bf16", 256, 1024, 20000, 8192), ("bf16", 512, 2048, 10000, 8192), ("fp16", 1024, 2048, 6500, 8192),
+            ("bf16", 256, 2048, 5000, 4096), ("bf16", 512, 4096, 20000, 4096), ("fp16", 1024, 2500, 20000, 4096)):
+        one = [(M, N, B)]
+        assert size(prec, one, 4096) < size(prec, one, 8192)
+        assert size(prec, one, 0) == size(prec, one, slots), (prec, M, N, B)
+    # problems run side by side: one that does better with 4096 holds the others to it
+    for prec, slots in (("fp32", 4096), ("bf16", 8192)):
+        two = [(128, 512, 10000), (512, 2048, 10000)]
+        assert size(prec, two, 0) == size(prec, two, slots), prec
