@@ -226,6 +226,10 @@ constexpr size_t WS_ALIGN = 256;
 hipError_t graph_launch_cached(const std::string &key, const std::function<hipError_t(hipStream_t)> &body,
                                hipStream_t st);
 
+// Fills in the schedule of problems that omp_solve_multi runs side by side, where they leave
+// it to the library: slots (at most `most` by default) and tile configurations.
+void fill_schedule(struct omp_problem *probs, int nprob, int most);
+
 // ---- launchers (all enqueue on `st`, return the launch status) -------------
 
 // Atom norms, padded FP32 copy and (optionally) BF16 copy of A.

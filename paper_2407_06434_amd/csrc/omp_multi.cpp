@@ -74,18 +74,8 @@ bool wants_8192_slots(const omp_problem_t &p) {
   return Np < 1024 || p.B >= (half && Mp > 64 ? 6144 : 8192);
 }
 
-// Writes the slots of the problems that name none into `probs`: 8192, or 4096 where one of
-// them does better with these (the problems' iterations run side by side, so the others'
-// additional slots would only slow that one down) or `most` says so.
-void fill_slots(omp_problem_t *probs, int nprob, int most) {
-  for (int p = 0; p < nprob; ++p)
-    if (probs[p].slots == 0 && probs[p].B > 0 && !wants_8192_slots(probs[p])) most = 4096;
-  for (int p = 0; p < nprob; ++p)
-    if (probs[p].slots == 0) probs[p].slots = most;
-}
-
 int64_t plan_slots(const omp_problem_t &p) {
-  const int64_t want = p.slots > 0 ? p.slots : 4096;  // (fill_slots has filled it in but for checks)
+  const int64_t want = p.slots > 0 ? p.slots : 4096;  // (fill_schedule has filled it in but for checks)
   return round_up(std::max<int64_t>(1, std::min<int64_t>(want, p.B)), BPAD);
 }
 
@@ -405,9 +395,9 @@ int validate(const omp_problem_t *probs, int nprob, const omp_multi_opts_t *opts
   return OMP_OK;
 }
 
-// The caller's problems, checked and with their slots; 4096 by default where the workspace
+// The caller's problems, checked and with their schedule; 4096 by default where the workspace
 // holds no more (4096 was every problem's default before).
-int with_slots(const omp_problem_t *probs, int nprob, const omp_multi_opts_t *opts, omp_problem_t *out) {
+int with_schedule(const omp_problem_t *probs, int nprob, const omp_multi_opts_t *opts, omp_problem_t *out) {
   if (!probs || !opts || nprob < 1 || nprob > OMP_MAX_PROBLEMS) return OMP_EINVAL;
   if (opts->precision != OMP_PREC_FP32 && !is_half(opts->precision)) return OMP_EINVAL;
   for (int p = 0; p < nprob; ++p) {
@@ -416,13 +406,40 @@ int with_slots(const omp_problem_t *probs, int nprob, const omp_multi_opts_t *op
   }
   for (int most : {8192, 4096}) {
     std::copy(probs, probs + nprob, out);
-    fill_slots(out, nprob, most);
+    fill_schedule(out, nprob, most);
     if (opts->workspace_bytes >= total_bytes(out, nprob, opts->precision)) break;
   }
   return OMP_OK;
 }
 
 }  // namespace
+
+// The problems' own choices stay. Slots: 8192, or 4096 where one of the problems does better
+// with these (their iterations run side by side, so the others' additional slots would only
+// slow that one down) or `most` says so. Tiles: FP32 problems that would run on 128 x 64 tiles
+// beside others keep 128 x 128 when all products together are more than two tiles a CU. A
+// half tile (48 KiB of LDS) on a CU leaves room for one whole tile (64 KiB) where there was
+// room for two, and what the halves gain on an idle chip is lost: 10,000 signals each over
+// 128 x 512 and 512 x 2048 (128 + 512 tiles), halves 7.55 ms, whole tiles 6.99; over 64 x 256
+// and 256 x 1024 (64 + 256 tiles) 3.12 and 3.40.
+void fill_schedule(omp_problem *probs, int nprob, int most) {
+  int active = 0;
+  for (int p = 0; p < nprob; ++p) {
+    active += probs[p].B > 0 ? 1 : 0;
+    if (probs[p].slots == 0 && probs[p].B > 0 && !wants_8192_slots(probs[p])) most = 4096;
+  }
+  int64_t tiles = 0;
+  for (int p = 0; p < nprob; ++p) {
+    if (probs[p].slots == 0) probs[p].slots = most;
+    if (probs[p].B > 0) tiles += plan_slots(probs[p]) / 128 * (round_up(probs[p].dict->N, NPAD) / 128);
+  }
+  for (int p = 0; p < nprob; ++p) {
+    const omp_dict_t &d = *probs[p].dict;
+    if (probs[p].tile_config != 0 || probs[p].B == 0 || active < 2 || tiles <= 512 || is_half(d.precision)) continue;
+    const int64_t Mp = round_up(d.M, KPAD), Np = round_up(d.N, NPAD);
+    if (corr_geometry(d.precision, Mp, Np, plan_slots(probs[p]), 0).cfg == 5) probs[p].tile_config = 1;
+  }
+}
 
 hipError_t graph_launch_cached(const std::string &key, const std::function<hipError_t(hipStream_t)> &body,
                                hipStream_t st) {
@@ -450,13 +467,13 @@ size_t omp_multi_workspace_size(const omp_problem_t *probs, int32_t nprob, const
     if (check_problem(probs[p], opts->precision) != OMP_OK) return 0;
     filled[p] = probs[p];
   }
-  fill_slots(filled, nprob, 8192);
+  fill_schedule(filled, nprob, 8192);
   return total_bytes(filled, nprob, opts->precision);
 }
 
 int omp_solve_multi(const omp_problem_t *caller_probs, int32_t nprob, const omp_multi_opts_t *opts, void *stream) {
   omp_problem_t probs[OMP_MAX_PROBLEMS];
-  int rc = with_slots(caller_probs, nprob, opts, probs);
+  int rc = with_schedule(caller_probs, nprob, opts, probs);
   if (rc == OMP_OK) rc = validate(probs, nprob, opts);
   if (rc != OMP_OK) return rc;
   bool any = false;
@@ -474,7 +491,7 @@ int omp_solve_multi(const omp_problem_t *caller_probs, int32_t nprob, const omp_
 
 int omp_tune(omp_problem_t *probs, int32_t nprob, const omp_multi_opts_t *opts, int64_t sample, void *stream) {
   omp_problem_t checked[OMP_MAX_PROBLEMS];
-  int rc = with_slots(probs, nprob, opts, checked);
+  int rc = with_schedule(probs, nprob, opts, checked);
   if (rc == OMP_OK) rc = validate(checked, nprob, opts);
   if (rc != OMP_OK) return rc;
   if (sample < 0) return OMP_EINVAL;

@@ -10,12 +10,28 @@ ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 PREC = {"fp32": 0, "bf16": 1, "fp64": 2, "fp16": 3}
 
 PROBE = r"""
+#include "batched_omp.h"
 #include "omp_internal.h"
 #include <cstdio>
 using namespace bomp;
-int main() {
+int main(int argc, char **) {
   long M, N, B;
   int S, prec;
+  if (argc > 1) {  // problems side by side
+    omp_problem_t p[OMP_MAX_PROBLEMS] = {};
+    omp_dict_t d[OMP_MAX_PROBLEMS] = {};
+    int n = 0;
+    for (; std::scanf("%d %ld %ld %ld %d", &prec, &M, &N, &B, &S) == 5; ++n) {
+      d[n].precision = prec;
+      d[n].M = M;
+      d[n].N = N;
+      p[n].dict = &d[n];
+      p[n].B = B;
+    }
+    fill_schedule(p, n, 8192);
+    for (int i = 0; i < n; ++i) std::printf("%d %d\n", p[i].tile_config, p[i].slots);
+    return 0;
+  }
   char *mem = reinterpret_cast<char *>(1 << 20);  // addresses only, nothing is read
   while (std::scanf("%d %ld %ld %ld %d", &prec, &M, &N, &B, &S) == 5) {
     const WorkView w = work_view(mem, M, N, B, S, prec, 0);
@@ -28,19 +44,20 @@ int main() {
 @pytest.fixture(scope="module")
 def routes(tmp_path_factory):
     """Function from [(precision, M, N, B, S)] to [(tile configuration chosen by shape,
-    signals per workgroup of the one-launch solve or 0)]."""
+    signals per workgroup of the one-launch solve or 0)], and with `multi` to the (tile
+    configuration or 0 for that choice, slots) of these problems run side by side."""
     pkg = os.path.join(ROOT, "paper_2407_06434_amd")
     d = tmp_path_factory.mktemp("routes")
     (d / "probe.cpp").write_text(PROBE)
     rocm = os.environ.get("ROCM_PATH", "/opt/rocm")
     lib = os.path.join(pkg, "libbatched_omp.so")
     subprocess.run(["g++", "-std=c++17", "-D__HIP_PLATFORM_AMD__", "-I", os.path.join(rocm, "include"), "-I",
-                    os.path.join(pkg, "csrc"), str(d / "probe.cpp"), lib, "-L", os.path.join(rocm, "lib"), "-lamdhip64",
+                    os.path.join(pkg, "csrc"), "-I", os.path.join(ROOT, "include"), str(d / "probe.cpp"), lib, "-L", os.path.join(rocm, "lib"), "-lamdhip64",
                     f"-Wl,-rpath,{pkg}:{os.path.join(rocm, 'lib')}", "-o", str(d / "probe")], check=True)
 
-    def ask(cases):
+    def ask(cases, multi=False):
         text = "".join(f"{PREC[p]} {M} {N} {B} {S}\n" for p, M, N, B, S in cases)
-        out = subprocess.run([str(d / "probe")], input=text, capture_output=True, text=True, check=True).stdout
+        out = subprocess.run([str(d / "probe")] + ["multi"] * multi, input=text, capture_output=True, text=True, check=True).stdout
         return [tuple(map(int, line.split())) for line in out.splitlines()]
 
     return ask
@@ -115,3 +132,14 @@ def test_default_slots_by_the_work_of_an_iteration():
     for prec, slots in (("fp32", 4096), ("bf16", 8192)):
         two = [(128, 512, 10000), (512, 2048, 10000)]
         assert size(prec, two, 0) == size(prec, two, slots), prec
+
+
+def test_half_tiles_beside_other_problems(routes):
+    """FP32 problems side by side whose products are more than two 128 x 128 tiles a CU keep
+    whole tiles, also where one of them alone would run on halves (8% slower then)."""
+    pair = [("fp32", 128, 512, 10000, 32), ("fp32", 512, 2048, 10000, 32)]
+    assert routes(pair, multi=True) == [(1, 4096), (0, 4096)]
+    assert routes(pair[:1], multi=True) == [(0, 8192)]
+    assert routes([("fp32", 64, 256, 10000, 16), ("fp32", 256, 1024, 10000, 32)], multi=True) == [(0, 4096)] * 2
+    assert routes(pair[:1] + [("fp32", 512, 2048, 0, 32)], multi=True) == [(0, 8192)] * 2
+    assert routes([("bf16", *c[1:]) for c in pair], multi=True) == [(0, 8192)] * 2
