@@ -119,8 +119,9 @@ int omp_dict_init(omp_dict_t *dict, const float *A, int64_t M, int64_t N, int64_
 typedef struct omp_opts {
   int32_t precision;            /* OMP_PREC_FP32 (default) or OMP_PREC_BF16 */
   int32_t tile_config;          /* correlation tiles (atoms x signals): 0 = chosen by shape
-                                   (default), 1 = 128x128, 2 = 256x256 (4 wavefronts),
-                                   3 = 256x256 (8 wavefronts), 4 = 256x128 */
+                                   (default), 1 = 128x128 (as 128x64 where that leaves fewer
+                                   CUs idle), 2 = 256x256 (4 wavefronts), 3 = 256x256
+                                   (8 wavefronts), 4 = 256x128 */
   const int32_t *S_per_signal;  /* device [B], optional: per-signal S_b in 0..S */
   const float *eps_per_signal;  /* device [B], optional: per-signal eps_b (replaces eps) */
   int32_t *status_out;          /* device [B], optional: (k_b << 8) | OMP_SIG_* bits */
@@ -292,7 +293,9 @@ typedef struct omp_problem {
   float *rnorm_out;             /* device [B], optional */
   /* schedule (0 = chosen by shape; omp_tune writes its choices here) */
   int32_t tile_config;          /* as omp_opts_t.tile_config */
-  int32_t slots;                /* signals in flight: a multiple of 256 (rounded up), capped at B */
+  int32_t slots;                /* signals in flight: a multiple of 256 (rounded up), capped at B;
+                                   0 = 8192, or 4096 where the product is what takes the time
+                                   of an iteration, in any of the problems solved together */
   int32_t residual_lanes;       /* lanes per signal in the residual kernel: 1, 2, 4, ..., 64 */
 } omp_problem_t;
 
@@ -325,12 +328,17 @@ int omp_solve_multi(const omp_problem_t *probs, int32_t nprob, const omp_multi_o
 
 /* Schedule autotuner: for each problem, times omp_solve_multi on its first
  * `sample` signals (0 = min(B, 8192)) over the candidate tile configurations
- * (1, 3, 4), slot counts (1024 .. 8192) and residual lane counts (by shape and
- * half of it), and writes the fastest choice into probs[p].tile_config, .slots
- * and .residual_lanes. The workspace must hold the largest candidate: size it
- * with omp_multi_workspace_size on problems whose slots field is 8192 (or B).
- * Overwrites the problems' output arrays (sample rows). Waits like
- * omp_solve_multi. */
+ * (1, 3, 4), slot counts (powers of two from 1024) and residual lane counts (by
+ * shape and half of it), and writes the fastest choice (changes from the
+ * untuned schedule by at least 2% each) into probs[p].tile_config, .slots and
+ * .residual_lanes. The slots field on entry
+ * (0 = 8192) is the largest count it may choose. More slots than a problem gets
+ * untuned are tried only where the sample fills them twice or is the whole
+ * batch; where the sample is too small for the untuned count and the largest
+ * count tried was the fastest, the untuned count is chosen. The workspace must
+ * hold the largest candidate: size it with omp_multi_workspace_size on problems
+ * whose slots field is 8192 (or B). Overwrites the problems' output arrays
+ * (sample rows). Waits like omp_solve_multi. */
 int omp_tune(omp_problem_t *probs, int32_t nprob, const omp_multi_opts_t *opts, int64_t sample, void *stream);
 
 /* ---- learned support proposal -------------------------------------------

@@ -380,20 +380,20 @@ CorrGeom geom(int precision, int cfg, bool ties) {
 }  // namespace
 
 CorrGeom corr_geometry(int precision, int64_t Mp, int64_t Np, int64_t Bp, int cfg, bool ties) {
-  if (cfg == 0) {
-    // 256 x 256 tiles when they still give about one per CU. Else 128 x 128 (t of them), or
-    // 128 x 64 where the CU with the most tiles then has less to do (a half tile takes 0.55 of
-    // a whole one's time): 512 < t <= 640 and 256 < t <= 384, also t <= 128, where half the
-    // CUs would stay idle; for 128 < t <= 256 two halves on a CU hide each other's latencies,
-    // except in FP32 on long signals, where the whole tile's MFMAs do. Measured, us, 128 x 128
-    // against 128 x 64: t = 624, M = 256 18.8 and 17.7 in BF16, 48.7 and 45.1 in FP32; t = 320,
-    // M = 1024, FP32 139 and 111; t = 128, M = 1024, FP32 74.9 and 45.5, BF16 11.6 and 10.3; t =
-    // 256, FP32, M = 256 24.8 and 23.6, M = 2500 172.5 and 174.7; and where halves lose, t =
-    // 720, M = 2500, BF16 75.5 and 88.8, t = 688, M = 1024 37.2 and 39.5 in BF16, 204 and 211
-    // in FP32.
+  // 256 x 256 tiles when they still give about one per CU
+  if (cfg == 0) cfg = (Np / 256) * (Bp / 256) >= 192 ? 3 : 1;
+  if (cfg == 1) {
+    // 128 x 128 (t of them), or 128 x 64 where the CU with the most tiles then has less to do
+    // (a half tile takes 0.55 of a whole one's time): t <= 128, where half the CUs would stay
+    // idle, 256 < t <= 384 and 512 < t <= 640. For 128 < t <= 256 two halves on a CU hide each
+    // other's latencies, except in FP32 on long signals, where the whole tile's MFMAs do.
+    // Measured, us, 128 x 128 against 128 x 64: t = 624, M = 256 18.8 and 17.7 in BF16, 48.7 and
+    // 45.1 in FP32; t = 320, M = 1024, FP32 139 and 111; t = 128, M = 1024, FP32 74.9 and 45.5,
+    // BF16 11.6 and 10.3; t = 256, FP32, M = 256 24.8 and 23.6, M = 2500 172.5 and 174.7; and
+    // where halves lose, t = 720, M = 2500, BF16 75.5 and 88.8, t = 688, M = 1024 37.2 and 39.5
+    // in BF16, 204 and 211 in FP32.
     const int64_t t = (Np / 128) * (Bp / 128), halves = (2 * t + 255) / 256, whole = (t + 255) / 256;
-    if ((Np / 256) * (Bp / 256) >= 192) cfg = 3;
-    else if (t > 128 && t <= 256) cfg = is_half(precision) || Mp <= 1024 ? 5 : 1;
+    if (t > 128 && t <= 256) cfg = is_half(precision) || Mp <= 1024 ? 5 : 1;
     else cfg = halves < 2 * whole ? 5 : 1;
   }
   switch (cfg) {

@@ -38,8 +38,9 @@ constexpr int NSLICE_MAX = 8;
 
 constexpr uint32_t DICT_MAGIC = 0x4f4d5044u;  // "OMPD"
 
-// Correlation tile configurations 1..MAX_TILE_CFG (0 = chosen by shape).
+// Correlation tile configurations a caller names: 1..MAX_TILE_CFG (0 = chosen by shape).
 constexpr int MAX_TILE_CFG = 4;
+constexpr int TILE_WHOLE = 6;  // internal: 1 without its halves
 
 inline int64_t round_up(int64_t x, int64_t m) { return (x + m - 1) / m * m; }
 
@@ -310,7 +311,7 @@ struct CorrGeom {
   int sub_frags;
   int subs_per_half;
 };
-// cfg 0 picks by shape, 5 (128 x 64) among others; a caller names 1..MAX_TILE_CFG.
+// cfg 0 picks by shape; 1 picks between 128 x 128 (1) and its halves (5), TILE_WHOLE takes 1.
 // `ties`: the FP32 epilogue writes two keys per (signal, tile), best and second best.
 CorrGeom corr_geometry(int precision, int64_t Mp, int64_t Np, int64_t Bp, int cfg, bool ties = false);
 

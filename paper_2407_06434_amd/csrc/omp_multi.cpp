@@ -382,7 +382,9 @@ int solve_multi_locked(const omp_problem_t *probs, int nprob, const omp_multi_op
   return OMP_OK;
 }
 
-int validate(const omp_problem_t *probs, int nprob, const omp_multi_opts_t *opts) {
+// Checks a call; `out` receives the caller's problems with their schedule, 4096 slots by
+// default where the workspace holds no more (4096 was every problem's default before).
+int with_schedule(const omp_problem_t *probs, int nprob, const omp_multi_opts_t *opts, omp_problem_t *out) {
   if (!probs || !opts || nprob < 1 || nprob > OMP_MAX_PROBLEMS) return OMP_EINVAL;
   if (opts->precision != OMP_PREC_FP32 && !is_half(opts->precision)) return OMP_EINVAL;
   if (opts->iters_per_graph < 0 || opts->iters_per_graph > MAX_CHUNK) return OMP_EINVAL;
@@ -390,25 +392,14 @@ int validate(const omp_problem_t *probs, int nprob, const omp_multi_opts_t *opts
     const int rc = check_problem(probs[p], opts->precision);
     if (rc != OMP_OK) return rc;
   }
-  const size_t need = total_bytes(probs, nprob, opts->precision);
-  if (!opts->workspace || opts->workspace_bytes < need || !aligned(opts->workspace, WS_ALIGN)) return OMP_EWORKSPACE;
-  return OMP_OK;
-}
-
-// The caller's problems, checked and with their schedule; 4096 by default where the workspace
-// holds no more (4096 was every problem's default before).
-int with_schedule(const omp_problem_t *probs, int nprob, const omp_multi_opts_t *opts, omp_problem_t *out) {
-  if (!probs || !opts || nprob < 1 || nprob > OMP_MAX_PROBLEMS) return OMP_EINVAL;
-  if (opts->precision != OMP_PREC_FP32 && !is_half(opts->precision)) return OMP_EINVAL;
-  for (int p = 0; p < nprob; ++p) {
-    const int rc = check_problem(probs[p], opts->precision);
-    if (rc != OMP_OK) return rc;
-  }
+  size_t need = 0;
   for (int most : {8192, 4096}) {
     std::copy(probs, probs + nprob, out);
     fill_schedule(out, nprob, most);
-    if (opts->workspace_bytes >= total_bytes(out, nprob, opts->precision)) break;
+    need = total_bytes(out, nprob, opts->precision);
+    if (opts->workspace_bytes >= need) break;
   }
+  if (!opts->workspace || opts->workspace_bytes < need || !aligned(opts->workspace, WS_ALIGN)) return OMP_EWORKSPACE;
   return OMP_OK;
 }
 
@@ -435,9 +426,10 @@ void fill_schedule(omp_problem *probs, int nprob, int most) {
   }
   for (int p = 0; p < nprob; ++p) {
     const omp_dict_t &d = *probs[p].dict;
-    if (probs[p].tile_config != 0 || probs[p].B == 0 || active < 2 || tiles <= 512 || is_half(d.precision)) continue;
+    if (probs[p].tile_config > 1 || probs[p].B == 0 || active < 2 || tiles <= 512 || is_half(d.precision)) continue;
     const int64_t Mp = round_up(d.M, KPAD), Np = round_up(d.N, NPAD);
-    if (corr_geometry(d.precision, Mp, Np, plan_slots(probs[p]), 0).cfg == 5) probs[p].tile_config = 1;
+    if (corr_geometry(d.precision, Mp, Np, plan_slots(probs[p]), probs[p].tile_config).cfg == 5)
+      probs[p].tile_config = TILE_WHOLE;
   }
 }
 
@@ -474,7 +466,6 @@ size_t omp_multi_workspace_size(const omp_problem_t *probs, int32_t nprob, const
 int omp_solve_multi(const omp_problem_t *caller_probs, int32_t nprob, const omp_multi_opts_t *opts, void *stream) {
   omp_problem_t probs[OMP_MAX_PROBLEMS];
   int rc = with_schedule(caller_probs, nprob, opts, probs);
-  if (rc == OMP_OK) rc = validate(probs, nprob, opts);
   if (rc != OMP_OK) return rc;
   bool any = false;
   for (int p = 0; p < nprob; ++p) any |= probs[p].B > 0;
@@ -490,55 +481,82 @@ int omp_solve_multi(const omp_problem_t *caller_probs, int32_t nprob, const omp_
 }
 
 int omp_tune(omp_problem_t *probs, int32_t nprob, const omp_multi_opts_t *opts, int64_t sample, void *stream) {
-  omp_problem_t checked[OMP_MAX_PROBLEMS];
-  int rc = with_schedule(probs, nprob, opts, checked);
-  if (rc == OMP_OK) rc = validate(checked, nprob, opts);
+  omp_problem_t untuned[OMP_MAX_PROBLEMS];
+  int rc = with_schedule(probs, nprob, opts, untuned);
   if (rc != OMP_OK) return rc;
   if (sample < 0) return OMP_EINVAL;
   rc = check_device();
   if (rc != OMP_OK) return rc;
+  // the slots omp_solve_multi would take by itself
+  for (int p = 0; p < nprob; ++p) {
+    untuned[p] = probs[p];
+    untuned[p].slots = 0;
+  }
+  fill_schedule(untuned, nprob, 8192);
   std::lock_guard<std::mutex> lock(g_mu);
   for (int p = 0; p < nprob; ++p) {
     omp_problem_t &pr = probs[p];
     if (pr.B == 0) continue;
     omp_problem_t trial = pr;
     trial.B = std::min<int64_t>(pr.B, sample > 0 ? sample : 8192);
-    const int64_t max_slots =
-        round_up(std::max<int64_t>(1, std::min<int64_t>(pr.slots > 0 ? pr.slots : 8192, trial.B)), BPAD);
+    // Most slots the caller allows, and most that are tried. A sample that fills the slots
+    // less than twice says too much for them: it has fewer nearly empty last iterations than
+    // the batch will have, so beyond the untuned count they are tried on two fillings or on
+    // the whole batch only.
+    const int64_t allowed = std::min<int64_t>(pr.slots > 0 ? pr.slots : 8192, pr.B);
+    const int64_t def = std::min<int64_t>(untuned[p].slots, allowed);
+    const int64_t fair = trial.B == pr.B ? trial.B : std::max<int64_t>(def, trial.B / 2);
+    const int64_t max_slots = round_up(std::max<int64_t>(1, std::min({allowed, trial.B, fair})), BPAD);
     omp_multi_opts_t o = *opts;
     float ms = 0.f;
     int32_t iters = 0;
     o.elapsed_ms = &ms;
     o.iterations = &iters;
-    // Times one candidate (second run: the first captures its graph); +inf if
-    // it does not fit the workspace.
+    // Times one candidate (the best of three runs after the first, which captures its
+    // graph); +inf if it does not fit the workspace.
     auto time_one = [&](const omp_problem_t &cand, float *out) -> int {
       *out = INFINITY;
       if (total_bytes(&cand, 1, o.precision) > o.workspace_bytes) return OMP_OK;
-      for (int rep = 0; rep < 2; ++rep) {
+      for (int rep = 0; rep < 4; ++rep) {
         const int r = solve_multi_locked(&cand, 1, &o, stream);
         if (r != OMP_OK) return r;
+        if (rep > 0) *out = std::min(*out, ms);
       }
-      *out = ms;
       return OMP_OK;
     };
-    // Coordinate search: tile configuration, then slots, then residual lanes.
+    // The configuration a caller names for the tiles chosen by shape
+    auto shape_tile = [&](int64_t slots) {
+      const int64_t Mp = round_up(pr.dict->M, KPAD), Np = round_up(pr.dict->N, NPAD);
+      const int cfg = corr_geometry(o.precision, Mp, Np, round_up(slots, BPAD), 0).cfg;
+      return cfg == 5 ? 1 : cfg;
+    };
+    // Coordinate search from the untuned schedule: tile configuration, then slots, then
+    // residual lanes. A change has to gain 2% on the sample: less does not carry over to the
+    // batch, nor to the other problems beside it.
     omp_problem_t best = trial;
-    best.slots = (int32_t)std::min<int64_t>(max_slots, 4096);
+    best.slots = (int32_t)std::min<int64_t>(max_slots, round_up(def, BPAD));
+    best.tile_config = shape_tile(best.slots);
     float best_ms = INFINITY;
+    if ((rc = time_one(best, &best_ms)) != OMP_OK) return rc;
+    auto consider = [&](const omp_problem_t &c) -> int {
+      float t;
+      const int r = time_one(c, &t);
+      if (r == OMP_OK && t < (std::isfinite(best_ms) ? 0.98f * best_ms : INFINITY)) best_ms = t, best = c;
+      return r;
+    };
+    const int shape = best.tile_config;
     for (int cfg : {1, 3, 4}) {
+      if (cfg == shape) continue;
       omp_problem_t c = best;
       c.tile_config = cfg;
-      float t;
-      if ((rc = time_one(c, &t)) != OMP_OK) return rc;
-      if (t < best_ms) best_ms = t, best = c;
+      if ((rc = consider(c)) != OMP_OK) return rc;
     }
+    const int start = best.slots;
     for (int64_t sl = 1024; sl <= max_slots; sl *= 2) {
+      if (sl == start) continue;
       omp_problem_t c = best;
       c.slots = (int32_t)sl;
-      float t;
-      if ((rc = time_one(c, &t)) != OMP_OK) return rc;
-      if (t < best_ms) best_ms = t, best = c;
+      if ((rc = consider(c)) != OMP_OK) return rc;
     }
     {
       const int64_t Mp = round_up(pr.dict->M, KPAD);
@@ -548,12 +566,18 @@ int omp_tune(omp_problem_t *probs, int32_t nprob, const omp_multi_opts_t *opts, 
       for (int l : {lp, std::max(1, lp / 2), std::max(1, lp / 4)}) {
         omp_problem_t c = best;
         c.residual_lanes = l;
-        float t;
-        if ((rc = time_one(c, &t)) != OMP_OK) return rc;
-        if (t < best_ms) best_ms = t, best = c;
+        if ((rc = consider(c)) != OMP_OK) return rc;
       }
     }
     if (!std::isfinite(best_ms)) return OMP_EWORKSPACE;
+    // where more slots were better up to the sample's size, the untuned count, which the sample
+    // could not fill
+    if (best.slots * 2 > max_slots && best.slots < def) {
+      omp_problem_t c = pr;
+      c.slots = (int32_t)round_up(def, BPAD);
+      c.tile_config = shape_tile(c.slots);
+      if (total_bytes(&c, 1, o.precision) <= o.workspace_bytes) best.slots = c.slots, best.tile_config = c.tile_config;
+    }
     pr.tile_config = best.tile_config;
     pr.slots = best.slots;
     pr.residual_lanes = best.residual_lanes;

@@ -35,7 +35,8 @@ int main(int argc, char **) {
   char *mem = reinterpret_cast<char *>(1 << 20);  // addresses only, nothing is read
   while (std::scanf("%d %ld %ld %ld %d", &prec, &M, &N, &B, &S) == 5) {
     const WorkView w = work_view(mem, M, N, B, S, prec, 0);
-    std::printf("%d %d\n", w.tile_cfg, solve_loop_signals(dict_view(mem, M, N, prec), w, prec));
+    std::printf("%d %d %d\n", w.tile_cfg, solve_loop_signals(dict_view(mem, M, N, prec), w, prec),
+                work_view(mem, M, N, B, S, prec, 1).tile_cfg);
   }
 }
 """
@@ -44,8 +45,9 @@ int main(int argc, char **) {
 @pytest.fixture(scope="module")
 def routes(tmp_path_factory):
     """Function from [(precision, M, N, B, S)] to [(tile configuration chosen by shape,
-    signals per workgroup of the one-launch solve or 0)], and with `multi` to the (tile
-    configuration or 0 for that choice, slots) of these problems run side by side."""
+    signals per workgroup of the one-launch solve or 0, tile that configuration 1 stands
+    for)], and with `multi` to the (tile configuration or 0 for the choice by shape, slots) of
+    these problems run side by side."""
     pkg = os.path.join(ROOT, "paper_2407_06434_amd")
     d = tmp_path_factory.mktemp("routes")
     (d / "probe.cpp").write_text(PROBE)
@@ -69,17 +71,18 @@ def test_half_tiles_only_where_they_relieve_the_fullest_cu(routes):
     up = lambda x: (x + 255) // 256 * 2  # 128-wide tiles of the padded size
     cases = [(p, M, N, B, 12) for p in ("fp32", "bf16", "fp16") for M in (64, 3000) for N in (200, 500, 1024, 2304, 4864)
              for B in range(256, 25000, 509)]
-    for (p, M, N, B, _), (cfg, _) in zip(cases, routes(cases)):
+    for (p, M, N, B, _), (cfg, _, one) in zip(cases, routes(cases)):
         t = up(N) * up(B)
         if t // 4 >= 192:
             assert cfg == 3, (p, M, N, B)
             continue
+        assert one == cfg  # what a schedule that names configuration 1 (the tuner's) gets
         most_whole, most_half = -(-t // 256), -(-2 * t // 256)
         if 128 < t <= 256:
             assert cfg == (1 if p == "fp32" and M == 3000 else 5), (p, M, N, B)
         else:
             assert cfg == (5 if most_half < 2 * most_whole else 1), (p, M, N, B, t)
-    assert [c for c, _ in routes([("bf16", 1024, 1024, 11000, 12), ("bf16", 2500, 2304, 5120, 12),
+    assert [r[0] for r in routes([("bf16", 1024, 1024, 11000, 12), ("bf16", 2500, 2304, 5120, 12),
                                   ("bf16", 256, 1024, 9984, 12)])] == [1, 1, 5]
 
 
@@ -93,7 +96,7 @@ def test_one_launch_solve_where_it_is_the_faster_one(routes):
     no = [("fp32", 1024, 2048, 1, 24), ("fp32", 1024, 2048, 512, 24), ("fp32", 900, 1900, 256, 24),
           ("fp32", 512, 2000, 300, 16), ("bf16", 128, 2000, 1, 20), ("fp16", 128, 2000, 15, 16),
           ("fp32", 256, 1024, 2049, 24), ("bf16", 1000, 500, 40, 20), ("fp64", 64, 256, 100, 8)]
-    got = [g for _, g in routes(yes + no)]
+    got = [r[1] for r in routes(yes + no)]
     for case, g in zip(yes + no, got):
         assert (g > 0) == (case in yes), (case, g)
         assert g in (0, -(-case[3] // 256)), (case, g)
@@ -138,7 +141,7 @@ def test_half_tiles_beside_other_problems(routes):
     """FP32 problems side by side whose products are more than two 128 x 128 tiles a CU keep
     whole tiles, also where one of them alone would run on halves (8% slower then)."""
     pair = [("fp32", 128, 512, 10000, 32), ("fp32", 512, 2048, 10000, 32)]
-    assert routes(pair, multi=True) == [(1, 4096), (0, 4096)]
+    assert routes(pair, multi=True) == [(6, 4096), (0, 4096)]  # 6: whole 128 x 128 tiles
     assert routes(pair[:1], multi=True) == [(0, 8192)]
     assert routes([("fp32", 64, 256, 10000, 16), ("fp32", 256, 1024, 10000, 32)], multi=True) == [(0, 4096)] * 2
     assert routes(pair[:1] + [("fp32", 512, 2048, 0, 32)], multi=True) == [(0, 8192)] * 2

@@ -176,3 +176,23 @@ def test_default_slots_in_a_workspace_of_the_former_default():
     torch.cuda.synchronize()
     assert rc == omp.OMP_OK
     assert all(torch.equal(a, b) for a, b in zip(want, small.out[1:]))
+
+
+def test_tuned_slots_are_no_worse_than_the_untuned_ones():
+    """A sample smaller than the slots a problem gets untuned says nothing against them, and
+    one that fills more slots just once nothing for these: the tuner chose 4096 where 8192 is
+    faster and the reverse."""
+    torch = _torch()
+    from paper_2407_06434_amd import omp
+    for prec, M, N, S, sample, want in (("bf16", 64, 256, 24, 4096, 8192), ("fp32", 256, 1024, 16, 0, 4096)):
+        g = torch.Generator(device="cuda").manual_seed(M)
+        d = omp.Dictionary(torch.randn((N, M), generator=g, device="cuda"), prec)
+        p = omp.Problem(d, torch.randn((9000, M), generator=g, device="cuda"), S)
+        print(f"case tuned slots {prec} {M}x{N}", flush=True)
+        (cfg, slots, _), = omp.tune([p], prec, sample=sample)
+        assert slots == want and cfg in (1, 3, 4), (prec, cfg, slots)
+        p.slots, p.tile_config = 0, cfg
+        lib, arr, o, _, _ = omp._multi_call([p], prec, 0, None)
+        untuned = o.workspace_bytes
+        p.slots = slots
+        assert omp._multi_call([p], prec, 0, None)[2].workspace_bytes == untuned
