@@ -73,9 +73,8 @@ struct NetWork {
   int64_t Bp;
   uint16_t *F, *H1, *H2, *dZ, *dH2, *dH1;
   uint16_t *FT, *H1T, *H2T, *dZT, *dH2T, *dH1T;
-  float *Z;
+  float *Z;         // scores; while training (which keeps none) the loss partials
   uint32_t *labels;
-  float *loss_part;
   float *gW[3], *gb[3];
   uint16_t *Y16;
   float *yinv;
@@ -102,7 +101,6 @@ NetWork net_layout(int64_t ni, int64_t nh, int64_t no, int64_t M, int64_t B, cha
   w.dH1T = c.take<uint16_t>(Bp * nh);
   w.Z = c.take<float>(Bp * no);
   w.labels = c.take<uint32_t>(Bp * (no / 32));
-  w.loss_part = c.take<float>(gemm_blocks(Bp, no, 1));
   for (int l = 0; l < 3; ++l) {
     int64_t in, out;
     layer_dims(ni, nh, no, l, &in, &out);
@@ -161,7 +159,7 @@ hipError_t forward(const Net &n, const NetWork &w, int64_t B, bool train, hipStr
   e.ldl = n.no / 32;
   e.mvalid = B;
   e.scale = 1.f / (float)B;
-  e.loss_part = w.loss_part;
+  e.loss_part = w.Z;
   return launch_gemm_bf16(EPI_BCE, w.H2, n.nh, n.L[2].W16, n.nh, Bp, n.no, n.nh, 1, e, st);
 }
 
@@ -358,7 +356,7 @@ int omp_mlp_grad(const omp_mlp_t *mlp, const uint16_t *F, const int32_t *support
     g.n[3 + l] = n.L[l].n_out;
     g.parts[3 + l] = groups;
   }
-  hipError_t e = launch_grad_sums(g, w.loss_part, gemm_blocks(w.Bp, n.no, 1), 1.f / (float)B, loss_out, st);
+  hipError_t e = launch_grad_sums(g, w.Z, gemm_blocks(w.Bp, n.no, 1), 1.f / (float)B, loss_out, st);
   if (e != hipSuccess) return device_error(e);
   return OMP_OK;
 }
@@ -377,7 +375,7 @@ int omp_mlp_train_step(omp_mlp_t *mlp, const uint16_t *F, const int32_t *support
   const float c2 = (float)(1.0 / (1.0 - std::pow((double)ADAM_B2, (double)t)));
   SumBatch none;
   std::memset(&none, 0, sizeof(none));
-  hipError_t e = launch_grad_sums(none, w.loss_part, gemm_blocks(w.Bp, n.no, 1), 1.f / (float)B, loss_out, st);
+  hipError_t e = launch_grad_sums(none, w.Z, gemm_blocks(w.Bp, n.no, 1), 1.f / (float)B, loss_out, st);
   for (int l = 0; l < 3 && e == hipSuccess; ++l) {
     e = launch_adam_w(n.L[l], w.gW[l], splits, lr, ADAM_B1, ADAM_B2, ADAM_EPS, c1, c2, 1, st);
     if (e == hipSuccess) e = launch_adam_b(n.L[l], w.gb[l], groups, lr, ADAM_B1, ADAM_B2, ADAM_EPS, c1, c2, st);

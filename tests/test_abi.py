@@ -436,3 +436,23 @@ def test_noalloc_limits_checked_on_the_host(lib):
     rc = lib.omp_solve_noalloc(FAKE, 64, 256, 64, FAKE, 10, 64, 8, 0.0, None, FAKE, ctypes.byref(o), None)
     assert rc == omp.OMP_EINVAL
     assert lib.omp_solve_noalloc(FAKE, 64, 256, 64, FAKE, 10, 64, 8, 0.0, None, FAKE, None, None) == omp.OMP_EINVAL
+
+
+def test_network_workspace_stays_within_its_former_size(lib):
+    """A workspace of the size the network calls needed when their products ran on 128 x 128
+    tiles (one loss partial per tile) is still enough, whatever tiles they run on now."""
+    from paper_2407_06434_amd import omp
+    al = lambda x: (x + 255) // 256 * 256
+    for ni, nh, no in ((256, 256, 256), (512, 512, 512), (1024, 1024, 1024), (256, 1024, 256), (2048, 512, 4096)):
+        net = omp.OmpMlpStruct()
+        net.magic, net.n_in, net.n_hidden, net.n_out, net.mem, net.bytes = 0x4F4D4C50, ni, nh, no, 1 << 20, 1 << 40
+        for B in (1, 256, 700, 1024, 2049, 4096, 16384):
+            for M in (0, 100, 1000):
+                Bp, Mp = (B + 255) // 256 * 256, max(64, (M + 63) // 64 * 64)
+                parts = [2 * Bp * x for x in (ni, nh, nh, no, nh, nh)] * 2 + [4 * Bp * no, Bp * no // 8,
+                                                                            4 * (Bp // 128) * (no // 128)]
+                for a, b in ((ni, nh), (nh, nh), (nh, no)):
+                    parts += [16 * a * b, 64 * b]
+                parts += [2 * Bp * Mp, 4 * Bp]
+                former = sum(al(p) for p in parts)
+                assert 0 < lib.omp_mlp_workspace_size(ctypes.byref(net), M, B) <= former, (ni, nh, no, B, M)
