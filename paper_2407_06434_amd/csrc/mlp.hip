@@ -453,7 +453,7 @@ __global__ __launch_bounds__(64 * LS_WAVES) __attribute__((amdgpu_waves_per_eu(2
   if (b >= B) return;
   constexpr int LD = SMAX + 1;
   float *Ls = lsm + (size_t)wv * SMAX * LD;
-  const int pi = lane < S ? P[b * S + lane] : 0;
+  const int pi = P[b * S + (lane < S ? lane : 0)];  // (past S the first atom again, times zero)
   const double nu2i = d.nu2[pi];
   // row i of the Gram block's lower triangle (symmetric: column p_i of row p_j); zero
   // elsewhere. Each entry is a cache line of its own, so the upper one is not read.
@@ -480,7 +480,7 @@ __global__ __launch_bounds__(64 * LS_WAVES) __attribute__((amdgpu_waves_per_eu(2
       if (j0 == 0) finite &= (isfinite(v.x) && isfinite(v.y) && isfinite(v.z) && isfinite(v.w)) ? 1 : 0;
       float4 a[8];
 #pragma unroll
-      for (int u = 0; u < 8; ++u) {  // (past S: atom 0's sum, which no lane takes)
+      for (int u = 0; u < 8; ++u) {  // (past S: the first atom's sum again, dropped below)
         const char *row = reinterpret_cast<const char *>(A4 + (int64_t)__builtin_amdgcn_readlane(pi, j0 + u) * nc4);
         a[u] = *reinterpret_cast<const float4 *>(row + 16u * c);
       }
@@ -540,7 +540,7 @@ __global__ __launch_bounds__(64 * LS_WAVES) __attribute__((amdgpu_waves_per_eu(2
   double rn = 0.0;
   if (!dependent) {
     // forward solve L u = beta: u_j = (beta_j - sum_k L[j][k] u_k) / L[j][j]
-    float t = (float)bj;
+    float t = lane < S ? (float)bj : 0.f;
 #pragma unroll
     for (int j = 0; j < SMAX; ++j)
       if (j < S) t = fmaf(-L[j], readlane(t, j) * readlane(rdj, j), t);
@@ -564,7 +564,7 @@ __global__ __launch_bounds__(64 * LS_WAVES) __attribute__((amdgpu_waves_per_eu(2
         float4 a[4];
         float xj[4];
 #pragma unroll
-        for (int u = 0; u < 4; ++u) {  // (past S: atom 0 times zero)
+        for (int u = 0; u < 4; ++u) {  // (past S: the first atom times zero)
           const char *row = reinterpret_cast<const char *>(A4 + (int64_t)__builtin_amdgcn_readlane(pi, j0 + u) * nc4);
           xj[u] = -readlane(x, j0 + u);
           a[u] = *reinterpret_cast<const float4 *>(row + 16u * c);

@@ -76,3 +76,29 @@ def test_gradients_at_ragged_batches(ni, nh, no, B):
         e = got[k].cpu().numpy().astype(np.float64) - want[k]
         assert np.abs(e).max() <= 1e-2 * np.abs(want[k]).max(), k
         assert np.linalg.norm(e) <= 2e-3 * np.linalg.norm(want[k]), k
+
+
+@pytest.mark.parametrize("value", [float("inf"), float("nan"), 3e38])
+@pytest.mark.parametrize("S", [1, 5, 6, 17, 35])
+def test_check_reads_the_proposed_atoms_only(S, value):
+    """Atom 0 is not finite (or overflows FP32 in a product) and not proposed: whether a
+    proposal explains its signal does not depend on it, however S divides into the rounds
+    that the check reads atoms in. Every signal is its proposal's combination."""
+    torch = _torch()
+    from paper_2407_06434_amd import omp, workloads
+    M, N, B = 130, 256, 21
+    g = np.random.default_rng(S)
+    A = (g.normal(size=(N, M)) / np.sqrt(M)).astype(np.float32)
+    A[0] = value
+    P = np.sort(1 + g.choice(N - 1, S, replace=False))
+    p = workloads.mlp_init_params(N, 256, N)
+    for k in ("W1", "W2", "W3", "b1", "b2", "b3"):
+        p[k][:] = 0.0
+    p["b3"][P] = 1.0  # the network proposes these atoms whatever the signal
+    Y = (1 + np.abs(g.normal(size=(B, S)))).astype(np.float32) @ A[P]
+    dev = torch.device("cuda:0")
+    d = omp.Dictionary(torch.from_numpy(A).to(dev), "bf16")
+    print(f"case proposed atoms only S={S} value={value}", flush=True)
+    out, nacc = omp.learned_solve(d, omp.MLP(p), torch.from_numpy(Y).to(dev), S, 1e-2)
+    assert nacc == B
+    assert np.array_equal(out.support.cpu().numpy(), np.tile(P, (B, 1)))
