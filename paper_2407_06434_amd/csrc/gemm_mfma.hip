@@ -16,6 +16,7 @@
 // The tile description and the LDS-staged main loop are in mfma_tile.h.
 
 #include "../../include/batched_omp.h"
+#include "lds_limit.h"
 #include "mfma_tile.h"
 #include "omp_internal.h"
 
@@ -339,22 +340,12 @@ using Cfg3 = Tile<256, 256, 2, 4>;
 using Cfg4 = Tile<256, 128, 2, 2>;
 using Cfg5 = Tile<128, 64, 2, 2>;
 
-template <class K>
-hipError_t set_lds(K kernel, size_t bytes) {
-  static bool done = false;  // per kernel instantiation
-  if (done) return hipSuccess;
-  hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kernel),
-                                     hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
-  if (e == hipSuccess) done = true;
-  return e;
-}
-
 template <class Op, class T, bool TOP2, bool SECOND = false>
 hipError_t launch_corr_t(const typename Op::elem *Aop, const typename Op::elem *Rop, const DictView &d,
                          const WorkView &w, hipStream_t st) {
   auto kern = k_corr_select<Op, T, TOP2, SECOND>;
   const size_t lds_bytes = TOP2 ? SelectLds<T>::BYTES : T::LDS_BYTES;
-  hipError_t e = set_lds(kern, lds_bytes);
+  hipError_t e = lds_limit(kern, lds_bytes);
   if (e != hipSuccess) return e;
   const int ntile = (int)(d.Np / T::TN);
   // the epilogue scores |c| by 1/||a_n|| (FP16 form: divided by the atom's storage scale)
@@ -418,7 +409,7 @@ hipError_t gram_product(const float *X, int64_t rows, const float *Z, int64_t co
   const bool half = (2 * t + 255) / 256 * 105 < (t + 255) / 256 * 200;
   auto kern = half ? k_gram<GramHalf> : k_gram<GramTile>;
   const size_t lds = half ? GramHalf::LDS_BYTES : GramTile::LDS_BYTES;
-  hipError_t e = half ? set_lds(k_gram<GramHalf>, lds) : set_lds(k_gram<GramTile>, lds);
+  hipError_t e = half ? lds_limit(k_gram<GramHalf>, lds) : lds_limit(k_gram<GramTile>, lds);
   if (e != hipSuccess) return e;
   const int ntn = (int)(rows / (half ? GramHalf::TN : GramTile::TN)), ntm = (int)(cols / 128);
   hipLaunchKernelGGL(kern, dim3((unsigned)((int64_t)ntn * ntm * ks)), dim3(GramTile::NTHR), lds, st, X, Z, Mp, ntn, ntm,
@@ -474,10 +465,10 @@ hipError_t launch_corr_cfg(const DictView &d, const WorkView &w, int precision, 
 
 template <class T>
 hipError_t prepare_corr_cfg(int precision, bool second) {
-  if (precision == OMP_PREC_BF16) return set_lds(k_corr_select<OpBF16, T, true>, SelectLds<T>::BYTES);
-  if (precision == OMP_PREC_FP16) return set_lds(k_corr_select<OpF16, T, true>, SelectLds<T>::BYTES);
-  if (second) return set_lds(k_corr_select<OpF32, T, false, true>, T::LDS_BYTES);
-  return set_lds(k_corr_select<OpF32, T, false>, T::LDS_BYTES);
+  if (precision == OMP_PREC_BF16) return lds_limit(k_corr_select<OpBF16, T, true>, SelectLds<T>::BYTES);
+  if (precision == OMP_PREC_FP16) return lds_limit(k_corr_select<OpF16, T, true>, SelectLds<T>::BYTES);
+  if (second) return lds_limit(k_corr_select<OpF32, T, false, true>, T::LDS_BYTES);
+  return lds_limit(k_corr_select<OpF32, T, false>, T::LDS_BYTES);
 }
 
 hipError_t prepare_corr(const DictView &d, const WorkView &w, int precision) {

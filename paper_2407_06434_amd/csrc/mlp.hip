@@ -25,6 +25,7 @@
 #include <utility>
 
 #include "../../include/batched_omp.h"
+#include "lds_limit.h"
 #include "mfma_tile.h"
 #include "mlp_internal.h"
 #include "omp_internal.h"
@@ -631,13 +632,6 @@ __global__ __launch_bounds__(64) void k_scatter_fallback(const int32_t *__restri
     status_out[b] = st_r[i];
     rnorm_out[b] = rn_r[i];
   }
-}
-
-template <class K>
-hipError_t lds_limit(K kernel, size_t bytes) {
-  if (bytes <= 64 * 1024) return hipSuccess;
-  return hipFuncSetAttribute(reinterpret_cast<const void *>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
-                             (int)bytes);
 }
 
 // Tile size of an M x N product with `splits` slices of K: the largest that still gives

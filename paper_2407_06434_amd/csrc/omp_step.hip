@@ -45,6 +45,7 @@
 #include <type_traits>
 
 #include "../../include/batched_omp.h"
+#include "lds_limit.h"
 #include "mfma_tile.h"
 #include "omp_internal.h"
 #include "wave_ops.h"
@@ -2747,13 +2748,6 @@ __global__ __launch_bounds__(256) void k_finalize(WorkView w, int64_t N, float *
   }
 }
 
-template <class K>
-hipError_t allow_lds(K kernel, size_t bytes) {
-  if (bytes <= 64 * 1024) return hipSuccess;
-  return hipFuncSetAttribute(reinterpret_cast<const void *>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
-                             (int)bytes);
-}
-
 // Dense X [nsig][N] from the compact outputs: one 256-lane block per signal
 // zero-fills its row, then scatters the coefficients (the barrier orders the
 // two passes' stores within the block).
@@ -2779,19 +2773,19 @@ hipError_t launch_solve_t(const DictView &d, const WorkView &w, const SlotView &
     if (solve_rr(d, w)) {
       if constexpr (RPL == 1) {
         if (w.fuse_res) {
-          hipError_t e = allow_lds(k_solve<1, BF16, false, true, true>, lds);
+          hipError_t e = lds_limit(k_solve<1, BF16, false, true, true>, lds);
           if (e != hipSuccess) return e;
           hipLaunchKernelGGL((k_solve<1, BF16, false, true, true>), dim3(blocks), dim3(64 * nw), lds, st, d, w, sv);
           return hipGetLastError();
         }
       }
-      hipError_t e = allow_lds(k_solve<RPL, BF16, false, true>, lds);
+      hipError_t e = lds_limit(k_solve<RPL, BF16, false, true>, lds);
       if (e != hipSuccess) return e;
       hipLaunchKernelGGL((k_solve<RPL, BF16, false, true>), dim3(blocks), dim3(64 * nw), lds, st, d, w, sv);
       return hipGetLastError();
     }
   }
-  hipError_t e = allow_lds(k_solve<RPL, BF16, SLOTS, false>, lds);
+  hipError_t e = lds_limit(k_solve<RPL, BF16, SLOTS, false>, lds);
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL((k_solve<RPL, BF16, SLOTS, false>), dim3(blocks), dim3(64 * nw), lds, st, d, w, sv);
   return hipGetLastError();
@@ -2909,7 +2903,7 @@ hipError_t launch_solve_loop(const DictView &d, const WorkView &w0, int precisio
               : G == 2                     ? k_solve_loop<OpF32, false, 2, LOOP_WAVES, LOOP_BUFS>
               : G <= 4                     ? k_solve_loop<OpF32, false, 4, LOOP_WAVES, LOOP_BUFS>
                                            : k_solve_loop<OpF32, false, 8, LOOP_WAVES, LOOP_BUFS>;
-  hipError_t e = allow_lds(kern, lds);
+  hipError_t e = lds_limit(kern, lds);
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(kern, dim3((unsigned)((w.B + G - 1) / G)), dim3(64 * LOOP_WAVES * (wide ? 2 : 1)), lds, st, d, w,
                      none, G);
@@ -2932,11 +2926,11 @@ hipError_t launch_residual_lp(const DictView &d, const WorkView &w, int precisio
   const size_t lds = residual_lds(w, LP);
   const dim3 grid((unsigned)(groups * w.nslice)), block(256);
   if (is_half(precision)) {
-    hipError_t e = allow_lds(k_residual<true>, lds);
+    hipError_t e = lds_limit(k_residual<true>, lds);
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(k_residual<true>, grid, block, lds, st, d, w, LP, kbound);
   } else {
-    hipError_t e = allow_lds(k_residual<false>, lds);
+    hipError_t e = lds_limit(k_residual<false>, lds);
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(k_residual<false>, grid, block, lds, st, d, w, LP, kbound);
   }
@@ -2947,7 +2941,7 @@ namespace {
 template <bool TIES>
 hipError_t launch_gram_panel(const DictView &d, const WorkView &w, hipStream_t st) {
   const size_t lds = (size_t)d.Np * GPANEL * 4;
-  hipError_t e = allow_lds(k_gram_panel<TIES>, lds);
+  hipError_t e = lds_limit(k_gram_panel<TIES>, lds);
   if (e != hipSuccess) return e;
   // Signal groups: one workgroup per CU, two where two panels fit, none with fewer than 64
   // signals (one turn of its wavefronts).
@@ -2983,7 +2977,7 @@ hipError_t launch_v0_first(const DictView &d, const WorkView &w, hipStream_t st)
 hipError_t launch_v0_step(const DictView &d, const WorkView &w, hipStream_t st) {
   if (!w.v0 || !w.P || !w.D || w.Np != d.Np || d.Np % 4 || w.B == 0) return w.B == 0 ? hipSuccess : hipErrorInvalidValue;
   const size_t lds = (size_t)(w.S + d.Np / 32) * 4;
-  hipError_t e = allow_lds(k_v0_step, lds);
+  hipError_t e = lds_limit(k_v0_step, lds);
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(k_v0_step, dim3((unsigned)w.B), dim3(V0_THREADS), lds, st, d, w);
   return hipGetLastError();
@@ -3025,7 +3019,7 @@ hipError_t launch_v0_parts64(const DictView &d, const WorkView &w, int first, in
   if (w.B == 0) return hipSuccess;
   if (!w.P64 || !w.D64 || !w.V64 || !w.u64 || !d.G64 || !d.inv_nu64 || w.Np != d.Np) return hipErrorInvalidValue;
   const size_t lds = (size_t)(2 * w.S + d.Np / 32) * 4;
-  hipError_t e = allow_lds(k_v0_solve64, lds);
+  hipError_t e = lds_limit(k_v0_solve64, lds);
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(k_v0_solve64, dim3((unsigned)w.B), dim3(V0_THREADS), lds, st, d, w, first, steps, last);
   return hipGetLastError();
@@ -3060,13 +3054,13 @@ hipError_t prepare_kernels(const DictView &d, const WorkView &w, int precision, 
   const bool bf = is_half(precision);
   hipError_t e = hipSuccess;
   if (w.S <= 64)
-    e = bf ? allow_lds(k_solve<1, true, true, false>, slds) : allow_lds(k_solve<1, false, true, false>, slds);
+    e = bf ? lds_limit(k_solve<1, true, true, false>, slds) : lds_limit(k_solve<1, false, true, false>, slds);
   else if (w.S <= 128)
-    e = bf ? allow_lds(k_solve<2, true, true, false>, slds) : allow_lds(k_solve<2, false, true, false>, slds);
-  else e = bf ? allow_lds(k_solve<4, true, true, false>, slds) : allow_lds(k_solve<4, false, true, false>, slds);
+    e = bf ? lds_limit(k_solve<2, true, true, false>, slds) : lds_limit(k_solve<2, false, true, false>, slds);
+  else e = bf ? lds_limit(k_solve<4, true, true, false>, slds) : lds_limit(k_solve<4, false, true, false>, slds);
   if (e != hipSuccess) return e;
   const size_t rlds = residual_lds(w, residual_lanes(w, lanes));
-  e = bf ? allow_lds(k_residual<true>, rlds) : allow_lds(k_residual<false>, rlds);
+  e = bf ? lds_limit(k_residual<true>, rlds) : lds_limit(k_residual<false>, rlds);
   if (e != hipSuccess) return e;
   return prepare_corr(d, w, precision);
 }
