@@ -215,7 +215,12 @@ __global__ __launch_bounds__(256) void k_pad_rows16(const uint16_t *__restrict__
 // for a batch of 1024 on 1024-wide layers, where six transposes of 4.4 us and three column
 // sums of 16.5 us (64 threads' serial loads per column) took 75.
 __global__ __launch_bounds__(256) void k_transposes16(TransposeBatch g, int64_t R, int64_t rpc) {
-  __shared__ uint16_t t[64][72];
+  // rows of nine 16-byte pieces: a row is written by pieces and read by columns
+  struct alignas(16) Row {
+    uint16_t v[72];
+  };
+  static_assert(sizeof(Row) == 144, "every row starts at a 16-byte piece");
+  __shared__ Row t[64];
   __shared__ float red[8][64];
   int m = 0;
   while (m < 5 && (int64_t)blockIdx.x >= g.end[m]) ++m;
@@ -229,7 +234,7 @@ __global__ __launch_bounds__(256) void k_transposes16(TransposeBatch g, int64_t 
 #pragma unroll
     for (int q = 0; q < 2; ++q) {
       const int f = tid + 256 * q, row = f >> 3, c8 = f & 7;
-      *reinterpret_cast<uint4 *>(&t[row][c8 * 8]) =
+      *reinterpret_cast<uint4 *>(&t[row].v[c8 * 8]) =
           *reinterpret_cast<const uint4 *>(g.src[m] + (r + row) * C + tc * 64 + c8 * 8);
     }
     __syncthreads();
@@ -240,7 +245,7 @@ __global__ __launch_bounds__(256) void k_transposes16(TransposeBatch g, int64_t 
       float s8 = 0.f;
 #pragma unroll
       for (int i = 0; i < 8; ++i) {
-        v[i] = t[r8 * 8 + i][col];
+        v[i] = t[r8 * 8 + i].v[col];
         s8 += bf16_to_f32(v[i]);
       }
       red[r8][col] = s8;
