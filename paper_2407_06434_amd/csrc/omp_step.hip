@@ -1506,12 +1506,13 @@ __host__ __device__ inline size_t loop_lds(int64_t Mp, int64_t Np, int G, bool h
 
 // A wavefront's 8 KiB of a slice: eight loads of 1 KiB, load i from base + off[i] to LDS
 // chunk 64 i after `l`, M0 moved on between them (dma16 saves and restores it each time).
-// No load destination is a register; the caller waits (vmcnt) before it reads.
+// No load destination is a register; the caller waits (vmcnt) before it reads. The wavefront's
+// own LDS reads of what lay there before are waited for first.
 __device__ inline void dma16x8(const void *base, const uint32_t (&off)[8], lds_void_t *l) {
   const uint32_t la = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)l);
   uint32_t saved;
   asm volatile(
-      "s_mov_b32 %0, m0\n\ts_mov_b32 m0, %2\n\ts_nop 0\n\t"
+      "s_waitcnt lgkmcnt(0)\n\ts_mov_b32 %0, m0\n\ts_mov_b32 m0, %2\n\ts_nop 0\n\t"
       "global_load_lds_dwordx4 %3, %1\n\ts_add_u32 m0, m0, 0x400\n\ts_nop 0\n\t"
       "global_load_lds_dwordx4 %4, %1\n\ts_add_u32 m0, m0, 0x400\n\ts_nop 0\n\t"
       "global_load_lds_dwordx4 %5, %1\n\ts_add_u32 m0, m0, 0x400\n\ts_nop 0\n\t"
