@@ -16,7 +16,7 @@
 // fused epilogue; every layout below keeps the reduction index contiguous:
 //   forward   H1[b][o]  = F[b][:]   . W1[o][:]          (+ b1, relu)
 //   backward  dH2[b][i] = dZ[b][:]  . W3T[i][:]         (x (H2 > 0))
-//   weights   dW3[o][i] = dZT[o][:] . H2T[i][:]         (split over the batch)
+//   weights   dW3[o][i] = dZT[o][:] . H2T[i][:]         (one launch for the three layers)
 // with W_lT the transposed BF16 copy kept by the optimiser and the activation
 // transposes made per step.
 
@@ -137,8 +137,8 @@ __device__ inline void gemm_nt_tile(const uint16_t *__restrict__ P, int64_t ldp,
 template <int EPI, class T>
 __global__ __launch_bounds__(T::NTHR) void k_gemm_nt(const uint16_t *__restrict__ P, int64_t ldp,
                                                     const uint16_t *__restrict__ Q, int64_t ldq, int64_t Mrows,
-                                                    int64_t Ncols, int64_t K, int splits, GemmEpi e) {
-  gemm_nt_tile<EPI, T>(P, ldp, Q, ldq, Mrows, Ncols, K, splits, blockIdx.x, e);
+                                                    int64_t Ncols, int64_t K, GemmEpi e) {
+  gemm_nt_tile<EPI, T>(P, ldp, Q, ldq, Mrows, Ncols, K, 1, blockIdx.x, e);
 }
 
 // The weight gradients of all three layers, dW_l = dOutT_l InT_l^T, in one launch: block
@@ -639,55 +639,54 @@ __global__ __launch_bounds__(64) void k_scatter_fallback(const int32_t *__restri
   }
 }
 
-// Tile size of an M x N product with `splits` slices of K: the largest that still gives
+// Tile size of an M x N product: the largest that still gives
 // the 256 CUs about one workgroup each (a workgroup of the larger tiles fills a CU).
 // Measured: 16384 x 1024 x 1024 with bias and ReLU 47 us on 128 x 128 tiles, 39 us on
 // 256 x 256; 1024 x 1024 x 1024 14.9 us on 128 x 128 (64 workgroups), 11.6 us on 64 x 64
 // with two LDS buffers and 9.5 us with four (64 MB through L2 at 7 TB/s).
-int gemm_tile(int64_t M, int64_t N, int splits) {
-  const int64_t t256 = (M / 256) * (N / 256) * splits;
+int gemm_tile(int64_t M, int64_t N) {
+  const int64_t t256 = (M / 256) * (N / 256);
   if (M % 256 == 0 && N % 256 == 0 && t256 >= 192) return 256;
-  return (M / 128) * (N / 128) * splits >= 192 ? 128 : 64;
+  return (M / 128) * (N / 128) >= 192 ? 128 : 64;
 }
 
 template <int EPI, class T>
 hipError_t gemm_t(const uint16_t *P, int64_t ldp, const uint16_t *Q, int64_t ldq, int64_t M, int64_t N, int64_t K,
-                  int splits, const GemmEpi &e, hipStream_t st) {
+                  const GemmEpi &e, hipStream_t st) {
   hipError_t err = lds_limit(k_gemm_nt<EPI, T>, gemm_lds<T>());
   if (err != hipSuccess) return err;
-  const unsigned grid = (unsigned)((M / T::TN) * (N / T::TB) * splits);
-  hipLaunchKernelGGL((k_gemm_nt<EPI, T>), dim3(grid), dim3(T::NTHR), gemm_lds<T>(), st, P, ldp, Q, ldq, M, N, K, splits,
-                     e);
+  const unsigned grid = (unsigned)((M / T::TN) * (N / T::TB));
+  hipLaunchKernelGGL((k_gemm_nt<EPI, T>), dim3(grid), dim3(T::NTHR), gemm_lds<T>(), st, P, ldp, Q, ldq, M, N, K, e);
   return hipGetLastError();
 }
 
 template <int EPI>
 hipError_t gemm_any(const uint16_t *P, int64_t ldp, const uint16_t *Q, int64_t ldq, int64_t M, int64_t N, int64_t K,
-                    int splits, const GemmEpi &e, hipStream_t st) {
-  switch (gemm_tile(M, N, splits)) {
-    case 256: return gemm_t<EPI, GT256>(P, ldp, Q, ldq, M, N, K, splits, e, st);
-    case 128: return gemm_t<EPI, GT128>(P, ldp, Q, ldq, M, N, K, splits, e, st);
-    default: return gemm_t<EPI, GT64>(P, ldp, Q, ldq, M, N, K, splits, e, st);
+                    const GemmEpi &e, hipStream_t st) {
+  switch (gemm_tile(M, N)) {
+    case 256: return gemm_t<EPI, GT256>(P, ldp, Q, ldq, M, N, K, e, st);
+    case 128: return gemm_t<EPI, GT128>(P, ldp, Q, ldq, M, N, K, e, st);
+    default: return gemm_t<EPI, GT64>(P, ldp, Q, ldq, M, N, K, e, st);
   }
 }
 
 }  // namespace
 
-int64_t gemm_blocks(int64_t M, int64_t N, int splits) {
-  const int64_t t = gemm_tile(M, N, splits);
-  return (M / t) * (N / t) * splits;
+int64_t gemm_blocks(int64_t M, int64_t N) {
+  const int64_t t = gemm_tile(M, N);
+  return (M / t) * (N / t);
 }
 
 hipError_t launch_gemm_bf16(int epi, const uint16_t *P, int64_t ldp, const uint16_t *Q, int64_t ldq, int64_t M,
-                            int64_t N, int64_t K, int splits, const GemmEpi &e, hipStream_t st) {
-  if (M % 128 || N % 128 || K % (64 * splits) || ldp % 8 || ldq % 8) return hipErrorInvalidValue;
+                            int64_t N, int64_t K, const GemmEpi &e, hipStream_t st) {
+  if (M % 128 || N % 128 || K % 64 || ldp % 8 || ldq % 8) return hipErrorInvalidValue;
   switch (epi) {
-    case EPI_FEATURES: return gemm_any<EPI_FEATURES>(P, ldp, Q, ldq, M, N, K, splits, e, st);
-    case EPI_BIAS_RELU: return gemm_any<EPI_BIAS_RELU>(P, ldp, Q, ldq, M, N, K, splits, e, st);
-    case EPI_BIAS: return gemm_any<EPI_BIAS>(P, ldp, Q, ldq, M, N, K, splits, e, st);
-    case EPI_BCE: return gemm_any<EPI_BCE>(P, ldp, Q, ldq, M, N, K, splits, e, st);
-    case EPI_RELU_MASK: return gemm_any<EPI_RELU_MASK>(P, ldp, Q, ldq, M, N, K, splits, e, st);
-    default: return gemm_any<EPI_PARTIAL>(P, ldp, Q, ldq, M, N, K, splits, e, st);
+    case EPI_FEATURES: return gemm_any<EPI_FEATURES>(P, ldp, Q, ldq, M, N, K, e, st);
+    case EPI_BIAS_RELU: return gemm_any<EPI_BIAS_RELU>(P, ldp, Q, ldq, M, N, K, e, st);
+    case EPI_BIAS: return gemm_any<EPI_BIAS>(P, ldp, Q, ldq, M, N, K, e, st);
+    case EPI_BCE: return gemm_any<EPI_BCE>(P, ldp, Q, ldq, M, N, K, e, st);
+    case EPI_RELU_MASK: return gemm_any<EPI_RELU_MASK>(P, ldp, Q, ldq, M, N, K, e, st);
+    default: return hipErrorInvalidValue;  // (EPI_PARTIAL: launch_wgrad)
   }
 }
 
@@ -738,7 +737,7 @@ hipError_t wgrad_t(WgradBatch g, int64_t K, int splits, hipStream_t st) {
   return hipGetLastError();
 }
 
-// 128 x 128 tiles of the three layers together, or 64 x 64 ones where those are too few
+// Entries of the three layers' weights
 int64_t wgrad_area(const WgradBatch &g) { return g.rows[0] * g.in[0] + g.rows[1] * g.in[1] + g.rows[2] * g.in[2]; }
 }  // namespace
 
@@ -752,6 +751,7 @@ int wgrad_splits(const WgradBatch &g, int64_t K) {
   return sp;
 }
 
+// 128 x 128 tiles of the three layers together, or 64 x 64 ones where those are too few
 hipError_t launch_wgrad(const WgradBatch &g, int64_t K, int splits, hipStream_t st) {
   for (int l = 0; l < 3; ++l)
     if (g.rows[l] % 128 || g.in[l] % 128) return hipErrorInvalidValue;

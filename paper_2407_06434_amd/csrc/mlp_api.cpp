@@ -141,18 +141,18 @@ hipError_t forward(const Net &n, const NetWork &w, int64_t B, bool train, hipStr
   e.out = w.H1;
   e.ldo = n.nh;
   e.bias = n.L[0].b32;
-  hipError_t err = launch_gemm_bf16(EPI_BIAS_RELU, w.F, n.ni, n.L[0].W16, n.ni, Bp, n.nh, n.ni, 1, e, st);
+  hipError_t err = launch_gemm_bf16(EPI_BIAS_RELU, w.F, n.ni, n.L[0].W16, n.ni, Bp, n.nh, n.ni, e, st);
   if (err != hipSuccess) return err;
   e.out = w.H2;
   e.bias = n.L[1].b32;
-  err = launch_gemm_bf16(EPI_BIAS_RELU, w.H1, n.nh, n.L[1].W16, n.nh, Bp, n.nh, n.nh, 1, e, st);
+  err = launch_gemm_bf16(EPI_BIAS_RELU, w.H1, n.nh, n.L[1].W16, n.nh, Bp, n.nh, n.nh, e, st);
   if (err != hipSuccess) return err;
   e = epi0();
   e.bias = n.L[2].b32;
   e.ldo = n.no;
   if (!train) {
     e.out = w.Z;
-    return launch_gemm_bf16(EPI_BIAS, w.H2, n.nh, n.L[2].W16, n.nh, Bp, n.no, n.nh, 1, e, st);
+    return launch_gemm_bf16(EPI_BIAS, w.H2, n.nh, n.L[2].W16, n.nh, Bp, n.no, n.nh, e, st);
   }
   e.out = w.dZ;
   e.labels = w.labels;
@@ -160,7 +160,7 @@ hipError_t forward(const Net &n, const NetWork &w, int64_t B, bool train, hipStr
   e.mvalid = B;
   e.scale = 1.f / (float)B;
   e.loss_part = w.Z;
-  return launch_gemm_bf16(EPI_BCE, w.H2, n.nh, n.L[2].W16, n.nh, Bp, n.no, n.nh, 1, e, st);
+  return launch_gemm_bf16(EPI_BCE, w.H2, n.nh, n.L[2].W16, n.nh, Bp, n.no, n.nh, e, st);
 }
 
 // Backward pass after forward(train): dH2, dH1, the activation transposes with the bias
@@ -173,11 +173,11 @@ hipError_t backward(const Net &n, const NetWork &w, float *const grads[3], int *
   e.out = w.dH2;
   e.ldo = n.nh;
   e.mask = w.H2;
-  hipError_t err = launch_gemm_bf16(EPI_RELU_MASK, w.dZ, n.no, n.L[2].W16T, n.no, Bp, n.nh, n.no, 1, e, st);
+  hipError_t err = launch_gemm_bf16(EPI_RELU_MASK, w.dZ, n.no, n.L[2].W16T, n.no, Bp, n.nh, n.no, e, st);
   if (err != hipSuccess) return err;
   e.out = w.dH1;
   e.mask = w.H1;
-  err = launch_gemm_bf16(EPI_RELU_MASK, w.dH2, n.nh, n.L[1].W16T, n.nh, Bp, n.nh, n.nh, 1, e, st);
+  err = launch_gemm_bf16(EPI_RELU_MASK, w.dH2, n.nh, n.L[1].W16T, n.nh, Bp, n.nh, n.nh, e, st);
   if (err != hipSuccess) return err;
   // db_l[o] = sum_b dOut[b][o], summed while dOut is transposed
   const TransposeBatch t = {{w.F, w.H1, w.H2, w.dZ, w.dH2, w.dH1},
@@ -287,7 +287,7 @@ int omp_mlp_features(const omp_dict_t *dict, const float *Y, int64_t B, int64_t 
   g.colscale = d.inv_nu;
   g.rowscale = w.yinv;
   g.scale = (float)std::sqrt((double)d.M);
-  if (e == hipSuccess) e = launch_gemm_bf16(EPI_FEATURES, w.Y16, d.Mp, d.A16, d.Mp, w.Bp, d.Np, d.Mp, 1, g, st);
+  if (e == hipSuccess) e = launch_gemm_bf16(EPI_FEATURES, w.Y16, d.Mp, d.A16, d.Mp, w.Bp, d.Np, d.Mp, g, st);
   if (e == hipSuccess) e = launch_pad_rows16(w.F, d.Np, nullptr, B, d.N, B, F, st);
   if (e != hipSuccess) return device_error(e);
   return OMP_OK;
@@ -356,7 +356,7 @@ int omp_mlp_grad(const omp_mlp_t *mlp, const uint16_t *F, const int32_t *support
     g.n[3 + l] = n.L[l].n_out;
     g.parts[3 + l] = groups;
   }
-  hipError_t e = launch_grad_sums(g, w.Z, gemm_blocks(w.Bp, n.no, 1), 1.f / (float)B, loss_out, st);
+  hipError_t e = launch_grad_sums(g, w.Z, gemm_blocks(w.Bp, n.no), 1.f / (float)B, loss_out, st);
   if (e != hipSuccess) return device_error(e);
   return OMP_OK;
 }
@@ -375,7 +375,7 @@ int omp_mlp_train_step(omp_mlp_t *mlp, const uint16_t *F, const int32_t *support
   const float c2 = (float)(1.0 / (1.0 - std::pow((double)ADAM_B2, (double)t)));
   SumBatch none;
   std::memset(&none, 0, sizeof(none));
-  hipError_t e = launch_grad_sums(none, w.Z, gemm_blocks(w.Bp, n.no, 1), 1.f / (float)B, loss_out, st);
+  hipError_t e = launch_grad_sums(none, w.Z, gemm_blocks(w.Bp, n.no), 1.f / (float)B, loss_out, st);
   for (int l = 0; l < 3 && e == hipSuccess; ++l) {
     e = launch_adam_w(n.L[l], w.gW[l], splits, lr, ADAM_B1, ADAM_B2, ADAM_EPS, c1, c2, 1, st);
     if (e == hipSuccess) e = launch_adam_b(n.L[l], w.gb[l], groups, lr, ADAM_B1, ADAM_B2, ADAM_EPS, c1, c2, st);
@@ -479,7 +479,7 @@ int omp_learned_solve(const omp_dict_t *dict, const omp_mlp_t *mlp, const float 
   g.colscale = d.inv_nu;
   g.rowscale = w.yinv;
   g.scale = (float)std::sqrt((double)d.M);
-  if (e == hipSuccess) e = launch_gemm_bf16(EPI_FEATURES, w.Y16, d.Mp, d.A16, d.Mp, w.Bp, d.Np, d.Mp, 1, g, st);
+  if (e == hipSuccess) e = launch_gemm_bf16(EPI_FEATURES, w.Y16, d.Mp, d.A16, d.Mp, w.Bp, d.Np, d.Mp, g, st);
   if (e == hipSuccess) e = forward(n, w, B, false, st);
   if (e == hipSuccess) e = launch_topk(w.Z, n.no, n.no, B, S, P, st);
   if (e == hipSuccess)

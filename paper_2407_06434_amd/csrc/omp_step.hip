@@ -191,30 +191,11 @@ __device__ inline float keep_lanes(float v, uint64_t mask) {
   return __builtin_amdgcn_inverse_ballot_w64(mask) ? v : 0.f;
 }
 
-// Select element p (wave-uniform) of a small per-lane register array without
-// dynamic register indexing.
-template <int R>
-__device__ inline float pick(const float (&a)[R], int p) {
-  float v = a[0];
-#pragma unroll
-  for (int i = 1; i < R; ++i) v = (p == i) ? a[i] : v;
-  return v;
-}
-
-template <int R>
-__device__ inline int pick_i(const int (&a)[R], int p) {
-  int v = a[0];
-#pragma unroll
-  for (int i = 1; i < R; ++i) v = (p == i) ? a[i] : v;
-  return v;
-}
-
 // Element j (wave-uniform) of an array held one element per lane, rows
 // j = lane + 64 p: lane j mod 64 of every register is read first and the
-// register chosen by j / 64 afterwards, among the read (uniform) values. Unlike
-// readlane(pick(a, j >> 6), j & 63) this is exact where some lanes are inactive:
-// pick's per-lane select is not executed by inactive lanes, whose stale values
-// readlane would then return.
+// register chosen by j / 64 afterwards, among the read (uniform) values. (A
+// select before the read would not be executed by inactive lanes, whose stale
+// values the read would then return.)
 template <int R>
 __device__ inline int lane_elem(const int (&a)[R], int j) {
   int v = __builtin_amdgcn_readlane(a[0], j & 63);
@@ -1367,7 +1348,7 @@ __device__ __attribute__((always_inline)) inline void solve_step(const DictView 
     // Rounds of four atoms, their loads issued together; the sums run in support
     // order. The row's address is wave-uniform (scalar) and the lane's offset 32 bits,
     // so an atom costs a lane two broadcasts and, per chunk, one load and four FMAs.
-    // (Lanes past nc4 are inactive in the last pass: lane_elem, not pick.)
+    // (Lanes past nc4 are inactive in the last pass, which lane_elem allows.)
     auto chunks = [&](auto cn, uint32_t c) {
       constexpr int CN = decltype(cn)::value;  // chunks per lane: c, c + 64
       float4 r[CN];
