@@ -639,15 +639,28 @@ __global__ __launch_bounds__(64) void k_scatter_fallback(const int32_t *__restri
   }
 }
 
-// Tile size of an M x N product: the largest that still gives
-// the 256 CUs about one workgroup each (a workgroup of the larger tiles fills a CU).
-// Measured: 16384 x 1024 x 1024 with bias and ReLU 47 us on 128 x 128 tiles, 39 us on
-// 256 x 256; 1024 x 1024 x 1024 14.9 us on 128 x 128 (64 workgroups), 11.6 us on 64 x 64
-// with two LDS buffers and 9.5 us with four (64 MB through L2 at 7 TB/s).
-int gemm_tile(int64_t M, int64_t N) {
-  const int64_t t256 = (M / 256) * (N / 256);
-  if (M % 256 == 0 && N % 256 == 0 && t256 >= 192) return 256;
-  return (M / 128) * (N / 128) >= 192 ? 128 : 64;
+// Tile size of an M x N x K product. A workgroup of the 256 x 256 tiles fills a CU, two of the
+// others share one. 256 x 256 from 192 tiles on, except where a second round would run on less
+// than half of the CUs; 64 x 64 where 128 x 128 would leave CUs idle. The features (one product
+// into many 16-bit stores) keep 128 x 128 for short signals and wherever the rounds of the others
+// are not well filled (a 256 x 256 tile takes 3.3 times a 128 x 128 one's time), the loss epilogue
+// always: with the accumulators of a 256 x 256 tile its exponential and logarithm do not fit the
+// registers (576 bytes of scratch a lane). Measured, us, 128 x 128 against 256 x 256: the three
+// layers of 2048, B = 8192 (256 tiles) 292 and 241, B = 8704 (272) 359 and 397, B = 10,240 (320)
+// 404 and 411, B = 17,408 (544) 682 and 658; features of 1000 samples, N = 4096, B = 4096 (256)
+// 63 and 57, B = 5120 (320) 76 and 86, B = 8704 (544) 131 and 136, of 64 samples, N = 2048, B =
+// 10,240 35 and 39; 5120 x 4096 x 1024 with the loss 149 and 608. 64 x 64 against 128 x 128: the
+// layers of 1024, B = 2048 (128 tiles of 128 x 128) 41 and 57, with gradients 117 and 176, B =
+// 2816 (176) 60 and 62, 173 and 192; features of 1000 samples, N = 1024, B = 2304 31 and 29.
+int gemm_tile(int epi, int64_t M, int64_t N, int64_t K) {
+  const int64_t t256 = (M / 256) * (N / 256), t128 = (M / 128) * (N / 128);
+  const bool whole = M % 256 == 0 && N % 256 == 0 && t256 >= 192;
+  if (epi == EPI_FEATURES) {
+    if (whole && K >= 256 && 332 * ((t256 + 255) / 256) < 100 * ((4 * t256 + 255) / 256)) return 256;
+    return t128 > 128 ? 128 : 64;
+  }
+  if (whole && epi != EPI_BCE && !(t256 > 256 && t256 <= 384)) return 256;
+  return t128 >= 192 ? 128 : 64;
 }
 
 template <int EPI, class T>
@@ -663,17 +676,17 @@ hipError_t gemm_t(const uint16_t *P, int64_t ldp, const uint16_t *Q, int64_t ldq
 template <int EPI>
 hipError_t gemm_any(const uint16_t *P, int64_t ldp, const uint16_t *Q, int64_t ldq, int64_t M, int64_t N, int64_t K,
                     const GemmEpi &e, hipStream_t st) {
-  switch (gemm_tile(M, N)) {
-    case 256: return gemm_t<EPI, GT256>(P, ldp, Q, ldq, M, N, K, e, st);
-    case 128: return gemm_t<EPI, GT128>(P, ldp, Q, ldq, M, N, K, e, st);
-    default: return gemm_t<EPI, GT64>(P, ldp, Q, ldq, M, N, K, e, st);
-  }
+  const int tile = gemm_tile(EPI, M, N, K);
+  if (tile == 64) return gemm_t<EPI, GT64>(P, ldp, Q, ldq, M, N, K, e, st);
+  if constexpr (EPI != EPI_BCE)
+    if (tile == 256) return gemm_t<EPI, GT256>(P, ldp, Q, ldq, M, N, K, e, st);
+  return gemm_t<EPI, GT128>(P, ldp, Q, ldq, M, N, K, e, st);
 }
 
 }  // namespace
 
-int64_t gemm_blocks(int64_t M, int64_t N) {
-  const int64_t t = gemm_tile(M, N);
+int64_t loss_blocks(int64_t M, int64_t N) {
+  const int64_t t = gemm_tile(EPI_BCE, M, N, 64);
   return (M / t) * (N / t);
 }
 

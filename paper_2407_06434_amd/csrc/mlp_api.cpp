@@ -356,7 +356,7 @@ int omp_mlp_grad(const omp_mlp_t *mlp, const uint16_t *F, const int32_t *support
     g.n[3 + l] = n.L[l].n_out;
     g.parts[3 + l] = groups;
   }
-  hipError_t e = launch_grad_sums(g, w.Z, gemm_blocks(w.Bp, n.no), 1.f / (float)B, loss_out, st);
+  hipError_t e = launch_grad_sums(g, w.Z, loss_blocks(w.Bp, n.no), 1.f / (float)B, loss_out, st);
   if (e != hipSuccess) return device_error(e);
   return OMP_OK;
 }
@@ -375,7 +375,7 @@ int omp_mlp_train_step(omp_mlp_t *mlp, const uint16_t *F, const int32_t *support
   const float c2 = (float)(1.0 / (1.0 - std::pow((double)ADAM_B2, (double)t)));
   SumBatch none;
   std::memset(&none, 0, sizeof(none));
-  hipError_t e = launch_grad_sums(none, w.Z, gemm_blocks(w.Bp, n.no), 1.f / (float)B, loss_out, st);
+  hipError_t e = launch_grad_sums(none, w.Z, loss_blocks(w.Bp, n.no), 1.f / (float)B, loss_out, st);
   for (int l = 0; l < 3 && e == hipSuccess; ++l) {
     e = launch_adam_w(n.L[l], w.gW[l], splits, lr, ADAM_B1, ADAM_B2, ADAM_EPS, c1, c2, 1, st);
     if (e == hipSuccess) e = launch_adam_b(n.L[l], w.gb[l], groups, lr, ADAM_B1, ADAM_B2, ADAM_EPS, c1, c2, st);

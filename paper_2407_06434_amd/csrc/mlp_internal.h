@@ -45,7 +45,7 @@ struct LayerView {
   float *mb, *vb;  // Adam moments of b
 };
 
-int64_t gemm_blocks(int64_t M, int64_t N);
+int64_t loss_blocks(int64_t M, int64_t N);  // workgroups, so loss partials, of an EPI_BCE product
 hipError_t launch_gemm_bf16(int epi, const uint16_t *P, int64_t ldp, const uint16_t *Q, int64_t ldq, int64_t M,
                             int64_t N, int64_t K, const GemmEpi &e, hipStream_t st);
 hipError_t launch_prep_signals(const float *Y, int64_t ldy, int64_t B, int64_t M, int64_t Mp, int64_t Bp,

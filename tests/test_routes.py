@@ -12,6 +12,7 @@ PREC = {"fp32": 0, "bf16": 1, "fp64": 2, "fp16": 3}
 PROBE = r"""
 #include "batched_omp.h"
 #include "omp_internal.h"
+#include "mlp_internal.h"
 #include <cstdio>
 using namespace bomp;
 int main(int argc, char **) {
@@ -35,8 +36,8 @@ int main(int argc, char **) {
   char *mem = reinterpret_cast<char *>(1 << 20);  // addresses only, nothing is read
   while (std::scanf("%d %ld %ld %ld %d", &prec, &M, &N, &B, &S) == 5) {
     const WorkView w = work_view(mem, M, N, B, S, prec, 0);
-    std::printf("%d %d %d\n", w.tile_cfg, solve_loop_signals(dict_view(mem, M, N, prec), w, prec),
-                work_view(mem, M, N, B, S, prec, 1).tile_cfg);
+    std::printf("%d %d %d %ld\n", w.tile_cfg, solve_loop_signals(dict_view(mem, M, N, prec), w, prec),
+                work_view(mem, M, N, B, S, prec, 1).tile_cfg, (long)loss_blocks(round_up(B, BPAD), N));
   }
 }
 """
@@ -46,7 +47,7 @@ int main(int argc, char **) {
 def routes(tmp_path_factory):
     """Function from [(precision, M, N, B, S)] to [(tile configuration chosen by shape,
     signals per workgroup of the one-launch solve or 0, tile that configuration 1 stands
-    for)], and with `multi` to the (tile configuration or 0 for the choice by shape, slots) of
+    for, workgroups of a network's loss product of B rows and N columns)], and with `multi` to the (tile configuration or 0 for the choice by shape, slots) of
     these problems run side by side."""
     pkg = os.path.join(ROOT, "paper_2407_06434_amd")
     d = tmp_path_factory.mktemp("routes")
@@ -71,7 +72,7 @@ def test_half_tiles_only_where_they_relieve_the_fullest_cu(routes):
     up = lambda x: (x + 255) // 256 * 2  # 128-wide tiles of the padded size
     cases = [(p, M, N, B, 12) for p in ("fp32", "bf16", "fp16") for M in (64, 3000) for N in (200, 500, 1024, 2304, 4864)
              for B in range(256, 25000, 509)]
-    for (p, M, N, B, _), (cfg, _, one) in zip(cases, routes(cases)):
+    for (p, M, N, B, _), (cfg, _, one, _) in zip(cases, routes(cases)):
         t = up(N) * up(B)
         if t // 4 >= 192:
             assert cfg == 3, (p, M, N, B)
@@ -146,3 +147,11 @@ def test_half_tiles_beside_other_problems(routes):
     assert routes([("fp32", 64, 256, 10000, 16), ("fp32", 256, 1024, 10000, 32)], multi=True) == [(0, 4096)] * 2
     assert routes(pair[:1] + [("fp32", 512, 2048, 0, 32)], multi=True) == [(0, 8192)] * 2
     assert routes([("bf16", *c[1:]) for c in pair], multi=True) == [(0, 8192)] * 2
+
+
+def test_loss_products_keep_128_wide_tiles(routes):
+    """The loss epilogue on 256 x 256 tiles spilled its registers: four times slower than on
+    128 x 128, which large products run on; small ones run on 64 x 64."""
+    for B, n, t in ((5000, 4096, 128), (16384, 1024, 128), (20000, 4096, 128), (1024, 1024, 64), (100, 256, 64)):
+        Bp = -(-B // 256) * 256
+        assert routes([("bf16", 64, n, B, 8)])[0][3] == (Bp // t) * (n // t), (B, n)
