@@ -2011,6 +2011,7 @@ __global__ __launch_bounds__(V0_THREADS) void k_v0_step(DictView d, WorkView w) 
   extern __shared__ uint32_t v0s[];
   __shared__ uint64_t red[V0_THREADS / 64];
   __shared__ double zzs;
+  __shared__ float cs;  // c of the pick: its thread overwrites c below, so no other may read it there
   const int64_t b = blockIdx.x;
   const int tid = threadIdx.x;
   int fl = w.flags[b];
@@ -2043,7 +2044,10 @@ __global__ __launch_bounds__(V0_THREADS) void k_v0_step(DictView d, WorkView w) 
       zz += z * z;
     }
     zz = wave_sum(zz);
-    if (tid == 0) zzs = zz;
+    if (tid == 0) {
+      zzs = zz;
+      cs = c[nstar];
+    }
   }
   __syncthreads();
   const double nu2 = d.nu2[nstar];
@@ -2054,7 +2058,7 @@ __global__ __launch_bounds__(V0_THREADS) void k_v0_step(DictView d, WorkView w) 
   }
   const double gd = 1.0 / sqrt(d2);
   const float g = (float)gd;
-  const float uk = (float)(gd * (double)c[nstar]);
+  const float uk = (float)(gd * (double)cs);
   // new column of F: f_i = -g sum_{j=i}^{k-1} F[i][j] z_j (i < k), f_k = g
   const float *Fb = w.V + b * w.vstride;
   float *Fk = w.V + b * w.vstride + (int64_t)k * (k + 1) / 2;
@@ -2319,7 +2323,10 @@ __device__ inline bool v0_step64(const DictView &d, const WorkView &w, uint32_t 
     double zz = 0.0;
     for (int j = tid; j < k; j += 64) zz += zs[j] * zs[j];
     zz = wave_sum(zz);
-    if (tid == 0) part4[0] = zz;
+    if (tid == 0) {
+      part4[0] = zz;
+      part4[1] = c[nstar];  // read here: its thread overwrites c below
+    }
   }
   __syncthreads();
   const double nu2 = d.nu2[nstar];
@@ -2329,7 +2336,7 @@ __device__ inline bool v0_step64(const DictView &d, const WorkView &w, uint32_t 
     return false;
   }
   const double g = 1.0 / sqrt(d2);
-  const double uk = g * c[nstar];
+  const double uk = g * part4[1];
   const double *Fb = w.V64 + b * w.vstride;
   double *Fk = w.V64 + b * w.vstride + (int64_t)k * (k + 1) / 2;
   for (int i = tid; i <= k; i += V0_THREADS) {
