@@ -450,8 +450,8 @@ def run_v0_forms(w_main, steps=3, warmup=1):
     the residual-vector FP32 form and its re-factorising variant (ablation A3 of the
     paper: inverse Cholesky against re-factorisation), the Gram-domain form forced on
     these wide dictionaries (M < N: where it stops paying) and the FP16 form, on the
-    benchmark workload and on the 256 x 1024 workload. Graph-replayed calls; supports compared with the FP32 form;
-    one more direct call per form gives the v0 step kernel's launch time."""
+    benchmark workload and on the 256 x 1024 workload. Supports compared with the FP32 form;
+    one more, timed call gives the FP32 v0 step kernel's launch time."""
     import torch
     from paper_2407_06434_amd import omp, workloads
     dev = torch.device("cuda:0")
@@ -474,17 +474,29 @@ def run_v0_forms(w_main, steps=3, warmup=1):
             torch.cuda.synchronize()
             dt = (time.perf_counter() - t0) / steps
             r = dict(value=round(w.B / dt, 1), ms_per_call=round(1e3 * dt, 3), support=out.support.cpu().numpy())
-            if name in ("v0_fp32", "fp64"):
+            if name == "v0_fp32":
                 tim = {}
                 omp.solve(A, Y, w.S, w.eps, precision=prec, dictionary=d, dense=False, timing=tim, **flags)
                 ms, n = tim["update"]
                 avg = ms / max(n, 1)
-                byt = v0_bytes_per_launch(w.N, w.S, w.B, 8 if prec == "fp64" else 4)
+                byt = v0_bytes_per_launch(w.N, w.S, w.B, 4)
                 r["k_v0_step"] = dict(bound="hbm", avg_launch_ms=round(avg, 5), launches=n,
                                       algorithmic_per_launch=float(f"{byt:.5e}"),
                                       achieved_GBps=round(byt / (avg * 1e-3) / 1e9, 1),
                                       frac=round(byt / (avg * 1e-3) / 1e9 / PEAK["hbm"], 4))
                 r["projection_and_first_pick_ms"] = round(tim["init"][0], 4)
+            elif name == "fp64":
+                # all steps are one launch (a timed call would run other kernels): the whole call's rate
+                Np = -(-w.N // 256) * 256
+                us = 1e6 * dt / w.S
+                if Np <= 1024 and w.S <= (64 if Np <= 512 else 32):
+                    r["step"] = dict(bound="latency", state="registers and LDS", us_per_step=round(us, 2))
+                else:
+                    byt = v0_bytes_per_launch(w.N, w.S, w.B, 8)
+                    r["step"] = dict(bound="hbm", state="memory", us_per_step=round(us, 2),
+                                     algorithmic_per_step=float(f"{byt:.5e}"),
+                                     achieved_GBps=round(byt / (us * 1e-6) / 1e9, 1),
+                                     frac=round(byt / (us * 1e-6) / 1e9 / PEAK["hbm"], 4))
             res[name] = r
             del d
             torch.cuda.empty_cache()

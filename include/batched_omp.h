@@ -136,13 +136,24 @@ typedef struct omp_opts {
   float *phase_ms;              /* HOST [OMP_NPHASE], optional profiling: when set, every kernel
                                    launch is bracketed by hipEvents on `stream`, the call waits for
                                    the stream, and phase_ms[p] receives the summed kernel time (ms)
-                                   of phase p; NULL (default) keeps the call asynchronous */
+                                   of phase p; NULL (default) keeps the call asynchronous. A timed
+                                   call runs step by step, with a launch per phase and step. Calls
+                                   that otherwise run all steps in one launch (small batches in the
+                                   residual-vector forms, and the FP64 form) are timed on these
+                                   other kernels, so the phases then add up to more than the
+                                   untimed call takes (2 to 4 times for the smallest). The results
+                                   are the same bit for bit. */
   int32_t *phase_launches;      /* HOST [OMP_NPHASE], optional: launches per phase (with phase_ms) */
   int32_t use_graph;            /* 1 (the default of omp_opts_default): the solve's launches are
                                    captured once into a hipGraph, cached per device and per
                                    argument set (every pointer and size of the call), and replayed
                                    with one graph launch; 0: the kernels are launched one by one.
-                                   A call with phase_ms set always launches one by one. */
+                                   A call with phase_ms set always launches one by one, and so do
+                                   calls of a few launches: the FP64 form, and small batches whose
+                                   steps run in one launch (FP32: up to 2048 signals, 16-bit forms
+                                   up to 8192, S <= 64, M <= 1024, N <= 2048, less for larger
+                                   dictionaries). Naming a tile_config keeps a small batch on the
+                                   step-by-step kernels and their graph. */
   int32_t gram_on_the_fly;      /* ablation A2 of the paper (measurement only): 1 = the solve
                                    computes the Gram row A_S^T a_n* of each pick from the atoms
                                    (exact products, FP64 sums) instead of reading the prepared

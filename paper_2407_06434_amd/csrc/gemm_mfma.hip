@@ -333,10 +333,10 @@ __global__ __launch_bounds__(T::NTHR) void k_corr_select(
 //   2: 256 x 256, 2 x 2 wavefronts of 128 x 128 (accumulators in AGPRs)
 //   3: 256 x 256, 2 x 4 wavefronts of 128 x 64
 //   4: 256 x 128, 2 x 2 wavefronts of 128 x 64
+//   5: 128 x 64, 2 x 2 wavefronts of 64 x 32 (chosen by shape only; keys as in 1)
 using Cfg1 = Tile<128, 128, 2, 2>;
 using Cfg2 = Tile<256, 256, 2, 2>;
 using Cfg3 = Tile<256, 256, 2, 4>;
-//   5: 128 x 64, 2 x 2 wavefronts of 64 x 32 (chosen by shape only; keys as in 1)
 using Cfg4 = Tile<256, 128, 2, 2>;
 using Cfg5 = Tile<128, 64, 2, 2>;
 

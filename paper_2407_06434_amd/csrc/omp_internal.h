@@ -254,7 +254,8 @@ hipError_t launch_solve(const DictView &d, const WorkView &w, int precision, hip
 // 0 where it is not used.
 int solve_loop_signals(const DictView &d, const WorkView &w, int precision);
 hipError_t launch_solve_loop(const DictView &d, const WorkView &w, int precision, hipStream_t st);
-// Whether the solve holds the residual in registers (its own variant, which does not fuse the residual).
+// Whether the solve holds the residual in registers (variants of its own; the one for S <= 64
+// can form the next residual, too), and whether it forms the next residual itself.
 bool solve_rr(const DictView &d, const WorkView &w);
 bool residual_in_solve(const DictView &d, int64_t B);
 // Residual r = y - A_S x (and its BF16 copy and per-slice norms) for the signals just updated;

@@ -240,8 +240,12 @@ def solve(A: torch.Tensor, Y: torch.Tensor, S: int, eps: float = 0.0, *, precisi
     Work is enqueued on `stream` (default: torch's current stream); the call does
     not synchronise, unless `timing` is a dict: then each kernel launch is timed
     with HIP events inside the library, the call waits for the stream, and
-    timing[phase] accumulates (milliseconds, launches) per phase. With `graph` (default)
-    the library replays the solve from a captured hipGraph cached per argument set.
+    timing[phase] accumulates (milliseconds, launches) per phase. A timed call runs step
+    by step, so where an untimed one runs all steps in one launch (small batches, the
+    FP64 form) the phases add up to more than that takes; the results are the same.
+    With `graph` (default) the library replays the solve from a captured hipGraph cached
+    per argument set, except where it consists of a few launches (small batches without
+    a `tile_config`, the FP64 form).
     `gram_on_the_fly` (ablation only) computes each pick's Gram row from the atoms
     instead of reading the prepared Gram matrix; `refactor` (ablation only) rebuilds
     the Cholesky factor of the support's Gram block at every step instead of

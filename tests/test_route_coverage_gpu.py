@@ -81,7 +81,8 @@ def test_residual_formed_in_the_step_solve(orc, M, N, B, S, prec):
 @pytest.mark.parametrize("prec,M,N,B,S", [("fp32", 640, 700, 300, 20), ("fp32", 1000, 500, 44, 40), ("fp32", 1000, 1000, 1000, 6),
                                           ("fp32", 513, 257, 513, 33), ("bf16", 1000, 200, 500, 24),
                                           ("fp16", 1000, 200, 100, 24), ("bf16", 700, 300, 2048, 9),
-                                          ("bf16", 64, 2048, 8192, 6), ("fp16", 50, 2000, 7900, 12)])
+                                          ("bf16", 64, 2048, 8192, 6), ("fp16", 50, 2000, 7900, 12),
+                                          ("bf16", 128, 1000, 5000, 7), ("fp16", 180, 700, 6000, 7)])
 def test_one_launch_solve_equals_the_steps(prec, M, N, B, S):
     """Signals of more than 512 samples, where the steps hold the residual in registers, and
     batches whose own tiles would be 256 x 256."""
