@@ -2316,6 +2316,7 @@ __device__ inline bool v0_step64(const DictView &d, const WorkView &w, uint32_t 
   if (w.flag_ties && s2 >= 0.0 && s2 >= (1.0 - TIE_REL) * s1) fl |= OMP_SIG_NEARTIE;
   double *Db = w.D64 + b * (int64_t)S * Np;
   double *c = w.P64 + b * Np;
+  const double cn = c[nstar];  // read here: its thread overwrites c below
   for (int j = tid; j < k; j += V0_THREADS) zs[j] = Db[(int64_t)j * Np + nstar];
   for (int64_t t = tid; t < mwords; t += V0_THREADS) mk[t] = w.mask[b * mwords + t];
   __syncthreads();
@@ -2325,7 +2326,7 @@ __device__ inline bool v0_step64(const DictView &d, const WorkView &w, uint32_t 
     zz = wave_sum(zz);
     if (tid == 0) {
       part4[0] = zz;
-      part4[1] = c[nstar];  // read here: its thread overwrites c below
+      part4[1] = cn;
     }
   }
   __syncthreads();
@@ -2366,10 +2367,10 @@ __device__ inline bool v0_step64(const DictView &d, const WorkView &w, uint32_t 
     a *= g;
     Dk[n] = a;
     const bool taken = n == nstar || ((mk[n >> 5] >> (n & 31)) & 1u);
-    const double cn = taken ? 0.0 : fma(-uk, a, c[n]);
-    c[n] = cn;
+    const double ck = taken ? 0.0 : fma(-uk, a, c[n]);
+    c[n] = ck;
     const double iv = d.inv_nu64[n];
-    if (!taken && iv > 0.0) pick_insert(fabs(cn) * iv, (int)n, p1, p2);
+    if (!taken && iv > 0.0) pick_insert(fabs(ck) * iv, (int)n, p1, p2);
   }
   v0_store_pick64(w, b, p1, p2, red);
   const int K = k + 1;
